@@ -117,6 +117,10 @@ typedef struct {
  *   precision    CDI_FP32: populations stored in FP32 relative to the rest
  *                equilibrium of a reference density per x plane,
  *                f - w_i (1 + R[x]), with R[x] the plane mean of rho - 1,
+ *                (at tau = 1 without a body force, where those populations
+ *                are the equilibrium of the node's moments, the moments are
+ *                held instead, in FP32 and relative to the same references:
+ *                the same state in fewer bytes, at the same accuracy),
  *                renewed at every residual check of cdi_flow_step_to_steady
  *                (zero until then): the stored values carry only the local
  *                fluctuations, which FP32 rounds finely;

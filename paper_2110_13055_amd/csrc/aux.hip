@@ -37,17 +37,17 @@ __global__ __launch_bounds__(256) void moments_kernel(Grid g, Phys p, int nee, c
     for (int i = 1; i < Q; ++i)
         nb[i] = (ODD || !kPlain<ST>) ? nb_map<L>(g, sx, y, z, i, g.periodic_x) : kOutside;
     float f[Q];
-    // FP32 storage: relative to the plane reference of the node read (see PlaneRef)
-    const PlaneRef pr = kPlain<ST> ? plane_ref<0>(g, rref, rref, sx) : PlaneRef{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+    // relative to the plane reference of the node read (see PlaneRef)
+    const PlaneRef pr = kRefs<ST> ? plane_ref<0>(g, rref, rref, sx) : PlaneRef{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
     float ref = pr.rout;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        f[i] = gather<L, ST, ODD>(F, g.P, nb, src, i, M, p);
+        f[i] = gather<L, ST, ODD>(F, g.P, nb, src, i, M, p, pr);
         if (kPlain<ST>) f[i] = rel_pop<L, ODD>(f[i], i, nb, pr);
     }
     if (src != n) {
         float fb[Q];
-        const float rb = kPlain<ST> ? plane_ref<0>(g, rref, rref, x).rout : 0.f;
+        const float rb = kRefs<ST> ? plane_ref<0>(g, rref, rref, x).rout : 0.f;
         nee_populations<L>(p, inlet, f, fb, ref, rb);
         ref = rb;
 #pragma unroll
@@ -79,7 +79,8 @@ __global__ __launch_bounds__(256) void moments_kernel(Grid g, Phys p, int nee, c
 // One workgroup per x plane: the mean of drho over the plane's fluid voxels,
 // summed in FP64 in a fixed order (each thread a fixed set of voxels, then a
 // fixed tree over the threads).
-__global__ __launch_bounds__(256) void plane_means_kernel(Grid g, const float *drho, float *rref)
+__global__ __launch_bounds__(256) void plane_means_kernel(Grid g, const float *drho, int stride, const float *base,
+                                                          float *rref)
 {
     __shared__ double ss[256];
     __shared__ int sc[256];
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(256) void plane_means_kernel(Grid g, const float *d
         const int y = (int)(k % g.ny), z = (int)(k / g.ny);
         const int m = g.map[brick_index(g.bk, x, y, z)];
         if (m >= 0) {
-            sum += (double)ldu(drho, (uint32_t)m);
+            sum += (double)drho[(size_t)m * stride];
             ++cnt;
         }
     }
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(256) void plane_means_kernel(Grid g, const float *d
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) rref[x] = sc[0] > 0 ? (float)(ss[0] / sc[0]) : 0.f;
+    if (threadIdx.x == 0) rref[x] = sc[0] > 0 ? (float)((base ? (double)base[x] : 0.0) + ss[0] / sc[0]) : 0.f;
 }
 
 template <class L>
@@ -128,12 +129,17 @@ __global__ void tile_heads_kernel(Grid g, uint32_t *heads)
 }
 
 template <int D>
-__global__ void j_from_m_kernel(Grid g, const float4 *M, float *j)
+__global__ void j_from_m_kernel(Grid g, const float4 *M, const float *rref, float *j)
 {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= g.n_f) return;
     const float4 m = M[n];
-    const float r = 1.f + m.x;
+    float r = 1.f + m.x;
+    if (rref) {
+        int x, y, z;
+        unpack_xyz(g, g.fluid[n], x, y, z);
+        r = 1.f + rref[x] + m.x;
+    }
     j[n] = r * m.y;
     j[g.P + n] = r * m.z;
     if (D == 3) j[2 * (size_t)g.P + n] = r * m.w;
@@ -296,7 +302,7 @@ void launch_moments_l(int st, int odd, unsigned blocks, int nee, const Grid &g, 
 {
 #define MK(S, O) moments_kernel<L, S, O><<<blocks, 256, 0, s>>>(g, p, nee, f, M, rref, rho, u, j)
     if (st == kMom)
-        MK(kMom, 0);
+        rref ? MK(kMomR, 0) : MK(kMom, 0);
     else if (st == kH16)
         odd == kPull ? MK(kH16, kPull) : odd ? MK(kH16, 1) : MK(kH16, 0);
     else if (st == kF16)
@@ -322,21 +328,22 @@ hipError_t launch_moments(int dim, int st, int odd, int nee, const Grid &g, cons
     return hipGetLastError();
 }
 
-hipError_t launch_plane_means(const Grid &g, const float *drho, float *rref, hipStream_t s)
+hipError_t launch_plane_means(const Grid &g, const float *drho, int stride, const float *base, float *rref,
+                              hipStream_t s)
 {
     if (g.nx <= 0) return hipSuccess;
-    plane_means_kernel<<<g.nx, 256, 0, s>>>(g, drho, rref);
+    plane_means_kernel<<<g.nx, 256, 0, s>>>(g, drho, stride, base, rref);
     return hipGetLastError();
 }
 
-hipError_t launch_j_from_m(int dim, const Grid &g, const float4 *M, float *j, hipStream_t s)
+hipError_t launch_j_from_m(int dim, const Grid &g, const float4 *M, const float *rref, float *j, hipStream_t s)
 {
     const unsigned blocks = (unsigned)((g.n_f + 255) / 256);
     if (blocks == 0) return hipSuccess;
     if (dim == 2)
-        j_from_m_kernel<2><<<blocks, 256, 0, s>>>(g, M, j);
+        j_from_m_kernel<2><<<blocks, 256, 0, s>>>(g, M, rref, j);
     else
-        j_from_m_kernel<3><<<blocks, 256, 0, s>>>(g, M, j);
+        j_from_m_kernel<3><<<blocks, 256, 0, s>>>(g, M, rref, j);
     return hipGetLastError();
 }
 

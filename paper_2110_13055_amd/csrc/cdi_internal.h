@@ -157,7 +157,14 @@ struct Bufs {
 // populations and FP16 populations (both relative to the plane references,
 // the FP16 ones scaled; the ions' flux in its own buffer), FP16 deviations
 // from the emitter's equilibrium with FP32 moment buffers, moments only.
-constexpr int kF32 = 0, kF16 = 1, kMom = 2, kH16 = 3;
+// kMomR: moments only, with rho - 1 relative to the plane references (see
+// PlaneRef): the kernels of an FP32 instance held as moments once its
+// references have been renewed.
+constexpr int kF32 = 0, kF16 = 1, kMom = 2, kH16 = 3, kMomR = 4, kForms = 5;
+template <int ST>
+constexpr bool kMoments = ST == kMom || ST == kMomR;  // no populations stored
+template <int ST>
+constexpr bool kRefs = ST == kF32 || ST == kH16 || ST == kMomR;  // relative to the plane references
 template <int ST>
 constexpr bool kPlain = ST == kF32 || ST == kH16;  // populations relative to the plane references
 template <int ST>
@@ -170,10 +177,12 @@ struct BatchInst {
     Phys p;
     Bufs b;
 };
-// Step classes of a batched step (kernel variants): LBM only or fused, by AA
-// parity, and ions only.
-constexpr int kClassFlowEven = 0, kClassFlowOdd = 1, kClassFusedEven = 2, kClassFusedOdd = 3,
-              kClassIons = 4, kClassFlowPull = 5, kClassFusedPull = 6, kClasses = 7;
+// Step classes of a batched step (kernel variants): per storage form, LBM
+// only or fused by parity (class kClassesPerForm * form + ...; the moment
+// forms have no parity and use the even ones), and ions only.
+constexpr int kClassFlowEven = 0, kClassFlowOdd = 1, kClassFlowPull = 2, kClassFusedEven = 3, kClassFusedOdd = 4,
+              kClassFusedPull = 5, kClassesPerForm = 6, kClassIons = kForms * kClassesPerForm,
+              kClasses = kClassIons + 1;
 
 // Value of the kernels' parity argument for pull streaming (AA uses 0 / 1).
 constexpr int kPull = 2;
@@ -211,14 +220,14 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_f64(double *p, double v, int64_t n, hipStream_t s);
 
 // One LBM and/or Nernst-Planck step over all fluid nodes.
-//   dim 2/3, st = kF32/kF16/kMom, odd = AA parity of the stored state or
-//   kPull, lbm/np switches.
+//   dim 2/3, st = storage form (kF32 ...), odd = AA parity of the stored state
+//   or kPull, lbm/np switches.
 hipError_t launch_step(int dim, int st, int odd, int lbm, int np, const Grid &g, const Phys &p,
                        const Bufs &b, hipStream_t s);
 // One step of the instances of one step class in one persistent launch of
 // `workgroups` workgroups over the class's (instance, tile) list (inst and
 // tiles in device memory).
-hipError_t launch_batch(int dim, int st, int cls, const BatchInst *inst, const int2 *tiles, int ntiles,
+hipError_t launch_batch(int dim, int cls, const BatchInst *inst, const int2 *tiles, int ntiles,
                         int workgroups, int lds_pad, hipStream_t s);
 // Moments of the stored state: rho (nullable), u (nullable, d planes),
 // j (nullable, d planes); rref: the FP32 plane references of the state
@@ -226,16 +235,19 @@ hipError_t launch_batch(int dim, int st, int cls, const BatchInst *inst, const i
 hipError_t launch_moments(int dim, int st, int odd, int nee, const Grid &g, const Phys &p,
                           const void *f, const float4 *M, const float *rref, float *rho, float *u, float *j,
                           hipStream_t s);
-// Plane references: rref[x] = mean of drho (rho - 1 of the fluid nodes, one
-// plane of P values in node order) over the fluid voxels of plane x, 0 where
-// the plane holds none; FP64 sums in a fixed order (one workgroup per plane).
-hipError_t launch_plane_means(const Grid &g, const float *drho, float *rref, hipStream_t s);
+// Plane references: rref[x] = base[x] + mean of drho (rho - 1 - base of the
+// fluid nodes in node order, value n at drho[n * stride]; base nullptr: zero)
+// over the fluid voxels of plane x, 0 where the plane holds none; FP64 sums
+// in a fixed order (one workgroup per plane).
+hipError_t launch_plane_means(const Grid &g, const float *drho, int stride, const float *base, float *rref,
+                              hipStream_t s);
 // Packed coordinates of the first node of every tile (host-side tile schedule).
 hipError_t launch_tile_heads(const Grid &g, uint32_t *heads, hipStream_t s);
 // Neighbour list of every fluid node (see Grid::nbr), Q-1 planes of P.
 hipError_t launch_build_nbr(int dim, const Grid &g, int *nbr, hipStream_t s);
-// j = (1 + drho) u from the moments buffer (FP16 and moment storage).
-hipError_t launch_j_from_m(int dim, const Grid &g, const float4 *M, float *j, hipStream_t s);
+// j = rho u from the moments buffer (FP16 and moment storage; rref: the
+// plane references its densities are relative to, nullptr: zero).
+hipError_t launch_j_from_m(int dim, const Grid &g, const float4 *M, const float *rref, float *j, hipStream_t s);
 // Deterministic single-block sums: out[k] = sum_t in[t*stride + k], k < width.
 hipError_t launch_reduce_tiles(const double *in, int ntiles, int stride, int width, double *out,
                                hipStream_t s);

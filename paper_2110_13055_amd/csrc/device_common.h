@@ -336,7 +336,7 @@ __device__ __forceinline__ void st_pair(void *F, int a, int na, int b, int nb, b
 template <class L, int ST, int ODD>
 __device__ inline float gather_raw(const void *F, int P, const int *nb, int n, int i)
 {
-    if (ST == kMom) return 0.f;
+    if (kMoments<ST>) return 0.f;
     constexpr bool H = kHalfPop<ST>;
     const int j = L::opp[i];
     const bool fl = (i != 0) && nb[j] >= 0;
@@ -350,30 +350,36 @@ __device__ inline float gather_raw(const void *F, int P, const int *nb, int n, i
 // moments m. The emitter x - e_i sent it along e_i; a reflected one (fl
 // false) was sent by x along e_opp(i) = -e_i, which only flips the sign of
 // e.u (w_opp(i) = w_i).
+// kMomR: m.x is relative to the emitter's plane, and the result to Rout of
+// the node's (f_i - w_i (1 + pr.rout)).
 template <class L, int ST>
-__device__ inline float from_emitter(float raw, int i, bool fl, float4 m, const Phys &p)
+__device__ inline float from_emitter(float raw, int i, bool fl, float4 m, const Phys &p, const PlaneRef &pr)
 {
     // the full product, zeros included: with every component of m used, the
     // compiler keeps each emitter's float4 one load (lat_dot let it narrow the
     // loads of directions that need fewer components into several, and the
     // moment storage's fused step took 7 % longer)
     const float eu = L::ex[i] * m.y + L::ey[i] * m.z + L::ez[i] * m.w;
+    if (ST == kMomR) {
+        const float dr = m.x + (fl ? pr.dIn[L::ex[i] + 1] : pr.dIn[1]);
+        return feq_rel_eu(L::w[i], dr, 1.f + pr.rout + dr, fl ? eu : -eu, m.y, m.z, m.w, p.linear_eq);
+    }
     const float fe = feq_bar_eu(L::w[i], m.x, fl ? eu : -eu, m.y, m.z, m.w, p.linear_eq);
     return ST == kMom ? fe : fe + raw * p.hs_inv;
 }
 
 // Incoming f_i - w_i of node n (nb: map values of n's neighbours; M: the
-// emitters' moments, FP16 and moment storage; ST: kF32, kF16 or kMom).
+// emitters' moments, FP16 and moment storage; pr: kMomR).
 template <class L, int ST, int ODD>
 __device__ inline float gather(const void *F, int P, const int *nb, int n, int i, const float4 *M,
-                               const Phys &p)
+                               const Phys &p, const PlaneRef &pr)
 {
     const float raw = gather_raw<L, ST, ODD>(F, P, nb, n, i);
     if (ST == kF32) return raw;
     if (ST == kH16) return raw * p.hs_inv;
     const int j = L::opp[i];
     const bool fl = (i != 0) && nb[j] >= 0;
-    return from_emitter<L, ST>(raw, i, fl, ldu(M, (uint32_t)(fl ? nb[j] : n)), p);
+    return from_emitter<L, ST>(raw, i, fl, ldu(M, (uint32_t)(fl ? nb[j] : n)), p, pr);
 }
 
 // Store the outgoing value of direction i (FP32: f* - w_i; FP16: scaled
@@ -381,7 +387,7 @@ __device__ inline float gather(const void *F, int P, const int *nb, int n, int i
 template <class L, int ST, int ODD>
 __device__ inline void scatter(void *F, int P, const int *nb, int n, int i, float v)
 {
-    if (ST == kMom) return;
+    if (kMoments<ST>) return;
     constexpr bool H = kHalfPop<ST>;
     const int j = L::opp[i];
     if (ODD == kPull)

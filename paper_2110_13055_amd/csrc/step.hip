@@ -174,7 +174,7 @@ __device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, co
         stu(b.jout + P, (uint32_t)n, jy);
         if (D == 3) stu(b.jout + 2 * (size_t)P, (uint32_t)n, jz);
     }
-    if (ST == kMom) return;  // the post-collision state is the equilibrium of Mout
+    if (kMoments<ST>) return;  // the post-collision state is the equilibrium of Mout
     const EqTerms eq = eq_terms(drho, rho, ux, uy, uz, p.linear_eq);
     const float om = p.omega;
     // FP16 populations are stored times hs
@@ -331,8 +331,9 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
     // the flow's incoming populations (the collision follows the ions)
     float f[Q];
     bool do_flow = false;
-    PlaneRef pr{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};  // FP32: the node's plane references
+    PlaneRef pr{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};  // the node's plane references
     {
+        if (ST == kMomR && active) pr = plane_ref<0>(g, b.rin, b.rout, x);
         if (LBM && active) {
             // a boundary node with a fluid interior neighbour is advanced by that neighbour
             const bool by_partner = edge && ((x == 0 && nb[1] >= 0) || (x == g.nx - 1 && nb[2] >= 0));
@@ -375,7 +376,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
                             if (i >= Q) break;
                             const int j = L::opp[i];
                             const bool fl = (i != 0) && nb[j] >= 0;
-                            f[i] = from_emitter<L, ST>(gather_raw<L, ST, ODD>(b.f, P, nb, n, i), i, fl, mg[u], p);
+                            f[i] = from_emitter<L, ST>(gather_raw<L, ST, ODD>(b.f, P, nb, n, i), i, fl, mg[u], p, pr);
                         }
                     }
                 } else if (!kPlain<ST>) {
@@ -400,7 +401,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
                             if (i >= Q) break;
                             const int j = L::opp[i];
                             const bool fl = (i != 0) && nb[j] >= 0;
-                            f[i] = from_emitter<L, ST>(gather_raw<L, ST, ODD>(b.f, P, nb, n, i), i, fl, mg[u], p);
+                            f[i] = from_emitter<L, ST>(gather_raw<L, ST, ODD>(b.f, P, nb, n, i), i, fl, mg[u], p, pr);
                         }
                     }
                 } else {
@@ -414,7 +415,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
                     } else {
 #pragma unroll
                         for (int i = 0; i < Q; ++i)
-                            f[i] = rel_pop<L, ODD>(gather<L, ST, ODD>(b.f, P, nb, n, i, b.Min, p), i, nb, pr);
+                            f[i] = rel_pop<L, ODD>(gather<L, ST, ODD>(b.f, P, nb, n, i, b.Min, p, pr), i, nb, pr);
                     }
                 }
             }
@@ -429,7 +430,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
             const bool jm = !kPlain<ST> && (b.flags & kJFromM);
             if (jm) {
                 const float4 m = have_m ? mown : ldu(b.Min, (uint32_t)n);
-                const float r = 1.f + m.x;
+                const float r = ST == kMomR ? 1.f + (pr.rout + pr.dIn[1]) + m.x : 1.f + m.x;
                 jP[0] = r * m.y;
                 jP[1] = r * m.z;
                 jP[2] = r * m.w;
@@ -496,7 +497,11 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
                     float jN;
                     if (jm) {
                         const float4 mm = (have_m && !xb) ? mface[k] : ldu(b.Min, (uint32_t)m);
-                        jN = (1.f + mm.x) * (axis == 0 ? mm.y : (axis == 1 ? mm.z : mm.w));
+                        float r = 1.f + mm.x;
+                        if (ST == kMomR)  // the neighbour's plane (a periodic re-lookup: the other end's)
+                            r = 1.f + (xb ? ldu(b.rin, (uint32_t)(x + sgi < 0 ? g.nx - 1 : 0))
+                                          : pr.rout + pr.dIn[axis == 0 ? (sgi > 0 ? 0 : 2) : 1]) + mm.x;
+                        jN = r * (axis == 0 ? mm.y : (axis == 1 ? mm.z : mm.w));
                     } else {
                         jN = (early && kEarlyJ) ? ejn[k] : ldu(b.jin + (size_t)axis * P, (uint32_t)m);
                     }
@@ -544,7 +549,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
             for (int i = 1; i < Q; ++i) nbb[i] = nb_map<L>(g, xb, y, z, i, false);  // rare path
             float fb[Q];
             PlaneRef pb{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
-            if (kPlain<ST>) pb = plane_ref<ODD>(g, b.rin, b.rout, xb);
+            if (kRefs<ST>) pb = plane_ref<ODD>(g, b.rin, b.rout, xb);
             nee_populations<L>(p, inl, f, fb, pr.rout, pb.rout);
             lbm_node<L, ST, ODD, NP, kStage>(p, b, P, bn, nbb, fb, pb, res, stg, base, false);
         }
@@ -677,16 +682,20 @@ void launch_batch_t(int cls, const BatchInst *inst, const int2 *tiles, int ntile
                     hipStream_t s)
 {
     const size_t lds = (size_t)pad;
-    constexpr int O1 = ST == kMom ? 0 : 1;      // moment storage has no AA parity
-    constexpr int OP = ST == kMom ? 0 : kPull;  // nor streaming of populations
-    switch (cls) {
-    case kClassFlowEven: batch_kernel<L, ST, 0, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-    case kClassFlowOdd: batch_kernel<L, ST, O1, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-    case kClassFlowPull: batch_kernel<L, ST, OP, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-    case kClassFusedEven: batch_kernel<L, ST, 0, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-    case kClassFusedOdd: batch_kernel<L, ST, O1, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-    case kClassFusedPull: batch_kernel<L, ST, OP, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-    default: batch_kernel<L, kF32, 0, 0, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+    if constexpr (kMoments<ST>) {  // no parity
+        if (cls == kClassFlowEven)
+            batch_kernel<L, ST, 0, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles);
+        else
+            batch_kernel<L, ST, 0, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles);
+    } else {
+        switch (cls) {
+        case kClassFlowEven: batch_kernel<L, ST, 0, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        case kClassFlowOdd: batch_kernel<L, ST, 1, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        case kClassFlowPull: batch_kernel<L, ST, kPull, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        case kClassFusedEven: batch_kernel<L, ST, 0, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        case kClassFusedOdd: batch_kernel<L, ST, 1, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        default: batch_kernel<L, ST, kPull, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        }
     }
 }
 
@@ -714,61 +723,63 @@ void launch_mode(int lbm, int np, const Grid &g, const Phys &p, const Bufs &b, h
         launch_t<L, kF32, 0, 0, 1>(g, p, b, s);
 }
 
-template <class L>
-void launch_prec(int st, int odd, int lbm, int np, const Grid &g, const Phys &p, const Bufs &b,
-                 hipStream_t s)
+template <class L, int ST>
+void launch_form(int odd, int lbm, int np, const Grid &g, const Phys &p, const Bufs &b, hipStream_t s)
 {
-    if (st == kMom) {
-        launch_mode<L, kMom, 0>(lbm, np, g, p, b, s);
-    } else if (st == kH16) {
-        if (odd == kPull)
-            launch_mode<L, kH16, kPull>(lbm, np, g, p, b, s);
-        else if (odd)
-            launch_mode<L, kH16, 1>(lbm, np, g, p, b, s);
-        else
-            launch_mode<L, kH16, 0>(lbm, np, g, p, b, s);
-    } else if (st == kF16) {
-        if (odd == kPull)
-            launch_mode<L, kF16, kPull>(lbm, np, g, p, b, s);
-        else if (odd)
-            launch_mode<L, kF16, 1>(lbm, np, g, p, b, s);
-        else
-            launch_mode<L, kF16, 0>(lbm, np, g, p, b, s);
+    if constexpr (kMoments<ST>) {  // no parity
+        launch_mode<L, ST, 0>(lbm, np, g, p, b, s);
     } else {
         if (odd == kPull)
-            launch_mode<L, kF32, kPull>(lbm, np, g, p, b, s);
+            launch_mode<L, ST, kPull>(lbm, np, g, p, b, s);
         else if (odd)
-            launch_mode<L, kF32, 1>(lbm, np, g, p, b, s);
+            launch_mode<L, ST, 1>(lbm, np, g, p, b, s);
         else
-            launch_mode<L, kF32, 0>(lbm, np, g, p, b, s);
+            launch_mode<L, ST, 0>(lbm, np, g, p, b, s);
     }
 }
 
 template <class L>
-void launch_batch_l(int st, int cls, const BatchInst *inst, const int2 *tiles, int ntiles, int wg, int pad,
+void launch_prec(int st, int odd, int lbm, int np, const Grid &g, const Phys &p, const Bufs &b,
+                 hipStream_t s)
+{
+    switch (st) {
+    case kMom: launch_form<L, kMom>(odd, lbm, np, g, p, b, s); break;
+    case kMomR: launch_form<L, kMomR>(odd, lbm, np, g, p, b, s); break;
+    case kH16: launch_form<L, kH16>(odd, lbm, np, g, p, b, s); break;
+    case kF16: launch_form<L, kF16>(odd, lbm, np, g, p, b, s); break;
+    default: launch_form<L, kF32>(odd, lbm, np, g, p, b, s); break;
+    }
+}
+
+template <class L>
+void launch_batch_l(int cls, const BatchInst *inst, const int2 *tiles, int ntiles, int wg, int pad,
                     hipStream_t s)
 {
-    if (st == kMom)
-        launch_batch_t<L, kMom>(cls, inst, tiles, ntiles, wg, pad, s);
-    else if (st == kH16)
-        launch_batch_t<L, kH16>(cls, inst, tiles, ntiles, wg, pad, s);
-    else if (st == kF16)
-        launch_batch_t<L, kF16>(cls, inst, tiles, ntiles, wg, pad, s);
-    else
-        launch_batch_t<L, kF32>(cls, inst, tiles, ntiles, wg, pad, s);
+    if (cls == kClassIons) {
+        batch_kernel<L, kF32, 0, 0, 1><<<wg, kTile, (size_t)pad, s>>>(inst, tiles, ntiles);
+        return;
+    }
+    const int k = cls % kClassesPerForm;
+    switch (cls / kClassesPerForm) {
+    case kMom: launch_batch_t<L, kMom>(k, inst, tiles, ntiles, wg, pad, s); break;
+    case kMomR: launch_batch_t<L, kMomR>(k, inst, tiles, ntiles, wg, pad, s); break;
+    case kH16: launch_batch_t<L, kH16>(k, inst, tiles, ntiles, wg, pad, s); break;
+    case kF16: launch_batch_t<L, kF16>(k, inst, tiles, ntiles, wg, pad, s); break;
+    default: launch_batch_t<L, kF32>(k, inst, tiles, ntiles, wg, pad, s); break;
+    }
 }
 
 }  // namespace
 
-hipError_t launch_batch(int dim, int st, int cls, const BatchInst *inst, const int2 *tiles, int ntiles,
+hipError_t launch_batch(int dim, int cls, const BatchInst *inst, const int2 *tiles, int ntiles,
                         int workgroups, int lds_pad, hipStream_t s)
 {
     if (ntiles <= 0 || workgroups <= 0) return hipSuccess;
-    if (cls < 0 || cls >= kClasses || st < kF32 || st > kH16) return hipErrorInvalidValue;
+    if (cls < 0 || cls >= kClasses) return hipErrorInvalidValue;
     if (dim == 2)
-        launch_batch_l<D2Q9>(st, cls, inst, tiles, ntiles, workgroups, lds_pad, s);
+        launch_batch_l<D2Q9>(cls, inst, tiles, ntiles, workgroups, lds_pad, s);
     else
-        launch_batch_l<D3Q19>(st, cls, inst, tiles, ntiles, workgroups, lds_pad, s);
+        launch_batch_l<D3Q19>(cls, inst, tiles, ntiles, workgroups, lds_pad, s);
     return hipGetLastError();
 }
 
@@ -776,7 +787,7 @@ hipError_t launch_step(int dim, int st, int odd, int lbm, int np, const Grid &g,
                        const Bufs &b, hipStream_t s)
 {
     if (g.P <= 0) return hipSuccess;
-    if (st < kF32 || st > kH16) return hipErrorInvalidValue;
+    if (st < 0 || st >= kForms) return hipErrorInvalidValue;
     if (dim == 2)
         launch_prec<D2Q9>(st, odd, lbm, np, g, p, b, s);
     else
