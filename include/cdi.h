@@ -288,13 +288,10 @@ typedef struct {
                               walking a contiguous run of the curve (a brick's neighbours along
                               every axis are mostly a few bricks away in that XCD's sweep);
                               either takes precedence over band_rows. 0: off */
-    int32_t nbr_list;      /* 1 (the default): the ion-only steps and the fused steps with FP16 or moment
-                              storage read each node's neighbours from a list built at init (4 (Q-1)
-                              bytes per node of extra reads) instead of looking them up through the
-                              voxel map after the node's coordinates (flow-only and fused FP32 steps
-                              always look them up: measured no faster with the list); 0: map lookups
-                              everywhere */
-    int32_t stage_odd;     /* odd AA steps with FP32 or FP16 populations: each workgroup stages its
+    int32_t nbr_list;      /* 1 (the default): the ion-only steps read each node's face neighbours from a
+                              list built at init (8 d bytes per node of extra reads) instead of looking them
+                              up after the node's coordinates; 0: lookups everywhere */
+    int32_t stage_odd;     /* odd AA steps on FP32 or FP16 populations: each workgroup stages its
                               tile's population slots in LDS
                               (the slots whose reader is in the tile are then read and written there,
                               and the tile's own slots move as coalesced loads and stores). 0 (the

@@ -31,11 +31,12 @@ __global__ __launch_bounds__(256) void moments_kernel(Grid g, Phys p, int nee, c
             inlet = x == 0;
         }
     }
-    int nb[Q];
-    nb[0] = src;
+    Nbrs<L> nb;
+    nb.n[0] = src;
+    nb.fl[0] = true;
 #pragma unroll
     for (int i = 1; i < Q; ++i)
-        nb[i] = (ODD || !kPlain<ST>) ? nb_map<L>(g, sx, y, z, i, g.periodic_x) : kOutside;
+        set_nbr<L>(nb, i, (ODD || !kPlain<ST>) ? nb_map<L>(g, sx, y, z, i, g.periodic_x) : kOutside, src);
     float f[Q];
     // relative to the plane reference of the node read (see PlaneRef)
     const PlaneRef pr = kRefs<ST> ? plane_ref<0>(g, rref, rref, sx) : PlaneRef{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
@@ -119,7 +120,57 @@ __global__ __launch_bounds__(256) void build_nbr_kernel(Grid g, int *nbr)
     NbCtx c;
     nb_ctx<L>(g, x, y, z, g.periodic_x, c);
 #pragma unroll
-    for (int i = 1; i < L::Q; ++i) nbr[(size_t)(i - 1) * g.P + n] = nb_get<L>(g, c, i);
+    for (int i = 1; i <= 2 * L::D; ++i) nbr[(size_t)(i - 1) * g.P + n] = nb_get<L>(g, c, i);
+}
+
+// One thread per row (see cdi_internal.h).
+__global__ __launch_bounds__(256) void build_rows_kernel(Grid g, int4 *rows, int64_t nrows)
+{
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= nrows) return;
+    const Bricks &k = g.bk;
+    const int S = k.bsy + k.bsz, w = 1 << k.bsx;
+    const int64_t b = r >> S;
+    const int bx = (int)(b % k.nbx), by = (int)((b / k.nbx) % k.nby), bz = (int)(b / ((int64_t)k.nbx * k.nby));
+    const int y = (by << k.bsy) | (int)(r & ((1 << k.bsy) - 1)), z = (bz << k.bsz) | (int)((r >> k.bsy) & ((1 << k.bsz) - 1));
+    int4 out = make_int4(0, 0, kOutside, kOutside);
+    if (y < g.ny && z < g.nz) {
+        const int x0 = bx << k.bsx, len = min(w, g.nx - x0);
+        uint32_t bits = 0;
+        int base = -1;
+        for (int i = 0; i < len; ++i) {
+            const int m = g.map[brick_index(k, x0 + i, y, z)];
+            if (m >= 0) {
+                bits |= 2u << i;
+                if (base < 0) base = m;
+            } else if (m == kInert) {
+                bits |= 0x80000000u;
+            }
+        }
+        out.x = base < 0 ? 0 : base;
+        const int xl = x0 > 0 ? x0 - 1 : (g.periodic_x ? g.nx - 1 : -1);
+        const int xr = x0 + len < g.nx ? x0 + len : (g.periodic_x ? 0 : -1);
+        if (xl >= 0) out.z = g.map[brick_index(k, xl, y, z)];
+        if (xr >= 0) out.w = g.map[brick_index(k, xr, y, z)];
+        if (out.z >= 0) bits |= 1u;
+        if (out.w >= 0) bits |= 2u << len;
+        if (out.z == kInert || out.w == kInert) bits |= 0x80000000u;
+        out.y = (int)bits;
+    }
+    rows[r] = out;
+}
+
+__global__ __launch_bounds__(256) void pair_planes_kernel(const float *src, float *dst, int P, int to_pairs)
+{
+    const int n = blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= P) return;
+    if (to_pairs)
+        reinterpret_cast<float2 *>(dst)[n] = make_float2(src[n], src[P + n]);
+    else {
+        const float2 v = reinterpret_cast<const float2 *>(src)[n];
+        dst[n] = v.x;
+        dst[P + n] = v.y;
+    }
 }
 
 __global__ void tile_heads_kernel(Grid g, uint32_t *heads)
@@ -178,14 +229,15 @@ __global__ __launch_bounds__(1024) void max_tiles_kernel(const double *in, int n
     if (threadIdx.x == 0) out[0] = sm[0];
 }
 
-__global__ __launch_bounds__(kTile) void mass_kernel(Grid g, const float *C, const __half2 *Clo, double *part)
+__global__ __launch_bounds__(kTile) void mass_kernel(Grid g, const float2 *C, const __half2 *Clo, double *part)
 {
     const int n = blockIdx.x * kTile + threadIdx.x;
     double v[2] = {0, 0};
     if (n < g.n_f) {
         const __half2 lo = Clo[n];
-        v[0] = (double)C[n] + lo_decode(__low2half(lo));
-        v[1] = (double)C[g.P + n] + lo_decode(__high2half(lo));
+        const float2 c = C[n];
+        v[0] = (double)c.x + lo_decode(__low2half(lo));
+        v[1] = (double)c.y + lo_decode(__high2half(lo));
     }
     __shared__ double sm[(kTile / 64) * 2];
     double s[2];
@@ -286,6 +338,21 @@ hipError_t launch_build_nbr(int dim, const Grid &g, int *nbr, hipStream_t s)
     return hipGetLastError();
 }
 
+int64_t row_count(const Bricks &bk) { return brick_enum_size(bk) >> bk.bsx; }
+
+hipError_t launch_build_rows(const Grid &g, int4 *rows, hipStream_t s)
+{
+    const int64_t n = row_count(g.bk);
+    if (n > 0) build_rows_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(g, rows, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_pair_planes(const float *src, float *dst, int P, int to_pairs, hipStream_t s)
+{
+    if (P > 0) pair_planes_kernel<<<(unsigned)((P + 255) / 256), 256, 0, s>>>(src, dst, P, to_pairs);
+    return hipGetLastError();
+}
+
 hipError_t launch_tile_heads(const Grid &g, uint32_t *heads, hipStream_t s)
 {
     const int tiles = g.P / kTile;
@@ -354,7 +421,7 @@ hipError_t launch_reduce_tiles(const double *in, int ntiles, int stride, int wid
     return hipGetLastError();
 }
 
-hipError_t launch_mass(const Grid &g, const float *C, const __half2 *Clo, double *part, double *out, hipStream_t s)
+hipError_t launch_mass(const Grid &g, const float2 *C, const __half2 *Clo, double *part, double *out, hipStream_t s)
 {
     const int tiles = g.P / kTile;
     if (tiles == 0) return hipSuccess;

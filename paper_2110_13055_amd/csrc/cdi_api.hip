@@ -234,7 +234,7 @@ struct NodeLayout {
     float4 *M[2];
     float *j[2];
     float *ubuf;
-    float *C[2];
+    float2 *C[2];
     __half2 *Clo[2];  // the concentrations' FP16 remainders (both species per node)
     float *tmp;
     float *xfer;  // lexicographic staging for host copies (4 planes of N_f)
@@ -242,7 +242,8 @@ struct NodeLayout {
     float *rref[2];  // FP32 storage: plane reference tables (nx values each; see PlaneRef)
     double *acc, *resid, *part, *red;
     int *sched;
-    int *nbr;    // neighbour list (Q-1 planes of P), built once
+    int *nbr;    // face neighbour list (2 d planes of P), built once
+    int4 *rows;  // the lattice's rows, built once
     double *diag;  // diagnostics scratch (per-tile and per-plane-chunk sums)
     void *base;  // start of the state a checkpoint carries (state_bytes from here)
     uint64_t state_bytes, bytes;
@@ -252,22 +253,26 @@ struct NodeLayout {
 static int pop_bytes(int st) { return st == kF32 ? 4 : (st == kF16 || st == kH16) ? 2 : 0; }
 // the storages with FP32 moment buffers (their fused steps carry j there)
 static bool moment_buffers(int st) { return st == kF16 || st == kMom; }
-// The form an FP32 instance's state is held in. With tau = 1 and no body
-// force the BGK post-collision populations are the equilibrium of the node's
-// moments (the same fact that defines moment storage), so the moments, in FP32
-// and relative to the plane references like the populations, hold the same
-// state: 32 B per node and step read and written instead of 152 (D3Q19), with
-// four values rounded per node instead of 19. Measured on the 512^3 electrode:
-// fused step 2.83 -> 2.03 ms, velocity error against FP64 after 100 steps
-// 7.7e-7 either way. Elsewhere the populations are kept. The moments lie in
-// the population array's place, so sizes and offsets are those of FP32
-// populations; beyond 2^28 nodes a moment's 32-bit byte offset would not fit.
-static int fp32_form(double tau, int drive, int64_t P)
-{
-    return tau == 1.0 && drive == CDI_INLET_OUTLET && P * 16 <= 4294967295LL ? kMom : kF32;
-}
 // the storages relative to plane references
 static bool plain_pops(int st) { return st == kF32 || st == kH16; }
+// The form an instance's state is held in. With tau = 1 and no body force the
+// BGK post-collision populations are the equilibrium of the node's moments (the
+// same fact that defines moment storage), so the moments, in FP32 and relative
+// to the plane references like the populations, hold the state of an FP32
+// instance: 32 B per node and step read and written instead of 152 (D3Q19),
+// with four values rounded per node instead of 19. Measured on the 512^3
+// electrode: fused step 2.83 -> 2.03 ms, velocity error against FP64 after 100
+// steps 7.7e-7 either way. The moments lie in the population array's place, so
+// sizes and offsets are those of FP32 populations; beyond 2^28 nodes a moment's
+// 32-bit byte offset would not fit. FP16 deviations from the equilibrium are
+// zero there, and moment storage is the same computation without them (bit for
+// bit; 3.21 -> 1.99 ms). FP16 populations stay as asked for: their rounding is
+// part of the result.
+static int held_form(int prec, double tau, int drive, int64_t P)
+{
+    const bool eq = tau == 1.0 && drive == CDI_INLET_OUTLET && P * 16 <= 4294967295LL;
+    return eq && (prec == kF32 || prec == kF16) ? kMom : prec;
+}
 
 // Doubles of the diagnostics scratch: per-tile sums (3 per tile) or the
 // vertical-profile partials (3 per x plane and z chunk) plus its result (3 nx).
@@ -279,7 +284,7 @@ static uint64_t diag_doubles(const cdi_geometry *g, int64_t P)
     return (uint64_t)(prof > tiles ? prof : tiles);
 }
 
-static NodeLayout node_layout(void *ws, int dim, int st, int pull, int64_t P, int64_t plane,
+static NodeLayout node_layout(void *ws, int dim, int st, int pull, int64_t P, int64_t nrows,
                               uint64_t ndiag, int64_t nx)
 {
     const int Q = dim == 2 ? 9 : 19;
@@ -295,15 +300,15 @@ static NodeLayout node_layout(void *ws, int dim, int st, int pull, int64_t P, in
     L.M[1] = c.take<float4>(mb ? 16ull * P : 0);
     if (!mb) L.M[0] = L.M[1] = nullptr;
     if (st == kMom) L.f = nullptr;
-    if (st == kF32) {  // the moment form's buffers (see fp32_form)
+    if (st == kF32) {  // the moment form's buffers (see held_form)
         L.M[0] = (float4 *)L.f;
         L.M[1] = ws ? L.M[0] + P : nullptr;
     }
     L.j[0] = c.take<float>(4ull * dim * P);
     L.j[1] = c.take<float>(4ull * dim * P);
     L.ubuf = c.take<float>(4ull * (dim + 1) * P);
-    L.C[0] = c.take<float>(8ull * P);
-    L.C[1] = c.take<float>(8ull * P);
+    L.C[0] = c.take<float2>(8ull * P);
+    L.C[1] = c.take<float2>(8ull * P);
     L.Clo[0] = c.take<__half2>(4ull * P);
     L.Clo[1] = c.take<__half2>(4ull * P);
     L.tmp = c.take<float>(4ull * (1 + dim) * P);
@@ -318,7 +323,8 @@ static NodeLayout node_layout(void *ws, int dim, int st, int pull, int64_t P, in
     L.red = c.take<double>(64 * 8);
     L.state_bytes = c.off;  // everything a checkpoint must carry ends here
     L.sched = c.take<int>(4ull * ntiles);
-    L.nbr = c.take<int>(4ull * (Q - 1) * P);
+    L.nbr = c.take<int>(8ull * dim * P);
+    L.rows = c.take<int4>(16ull * nrows);
     L.diag = c.take<double>(8ull * ndiag);
     L.bytes = c.off;
     return L;
@@ -331,7 +337,7 @@ struct cdi_solver {
     cdi_params params;
     int dim, Q, inout;
     int prec;  // storage asked for: kF32, kF16, kMom or kH16
-    int st;    // form the state is held in: prec, or kMom for FP32 (see fp32_form)
+    int st;    // form the state is held in (see held_form)
     int pull;  // pull streaming (two population arrays; fcur holds the state)
     int mb;  // moment buffers in use (kF16, kMom): j of a fused step lives in them
     int64_t nvox, nf;
@@ -357,7 +363,8 @@ struct SnapHeader {
     uint64_t magic, bytes;
     int32_t parity, mcur, jcur, ccur, jstate, fcur;
     int32_t psi_on;  // the potential in use is the field in the state (else the ramp)
-    int32_t rstate;  // rcur | rpend << 1 | rlive << 2 | (FP32 held as moments) << 3
+    int32_t rstate;  // rcur | rpend << 1 | rlive << 2 | (FP32 held as moments) << 3 |
+                     // (concentrations in pairs) << 4
     int64_t flow_steps, np_steps, nf;
 };
 constexpr uint64_t kSnapMagic = 0x43444931534e4150ull;
@@ -372,7 +379,7 @@ int stream_arg(const cdi_solver *s) { return s->pull ? kPull : s->parity; }
 // Storage form of the kernels that work on the state.
 int kernel_form(const cdi_solver *s) { return s->st == kMom && s->rlive ? kMomR : s->st; }
 
-// Sets the form the state is held in (the requested storage, or kMom for FP32).
+// Sets the form the state is held in.
 void set_form(cdi_solver *s, int st)
 {
     s->st = st;
@@ -730,10 +737,11 @@ int cdi_plan(const cdi_geometry *geom, const cdi_params *params, cdi_plan_info *
     // the per-node arrays of node_layout: populations, moments, flux (two
     // sets), previous velocity and density, concentrations and remainders,
     // scratch, host staging, potential and the neighbour list; plus about
-    // 1 B for the per-tile sums and the schedule
+    // 1 B for the per-tile sums and the schedule, and the rows' share
     out->node_bytes_per_fluid = (uint64_t)Q * pop_bytes(st) * (pull ? 2 : 1) + (moment_buffers(st) ? 32 : 0) +
                                 8ull * dim + 4ull * (dim + 1) + 16 + 8 + 4ull * (1 + dim) + 16 + 4 +
-                                4ull * (Q - 1) + 1;
+                                8ull * dim + 1 +
+                                (nf_est > 0 ? (uint64_t)(16 * row_count(make_bricks(geom)) / nf_est) : 0);
     g_err[0] = 0;
     return CDI_OK;
 }
@@ -797,7 +805,7 @@ int cdi_node_bytes(const cdi_geometry *geom, const cdi_params *params, int64_t n
     if (!bytes || n_fluid <= 0) return fail(CDI_E_INVALID, "bad n_fluid or bytes pointer");
     const int64_t P = (n_fluid + kTile - 1) / kTile * kTile;
     *bytes = node_layout(nullptr, geom->dim, params->precision, params->streaming == CDI_STREAM_PULL, P,
-                         (int64_t)geom->ny * (geom->dim == 2 ? 1 : geom->nz), diag_doubles(geom, P), geom->nx).bytes;
+                         row_count(make_bricks(geom)), diag_doubles(geom, P), geom->nx).bytes;
     return CDI_OK;
 }
 
@@ -836,8 +844,7 @@ int cdi_flow_init(const cdi_geometry *geom, const cdi_params *params, void *vox_
         return fail(CDI_E_INVALID,
                     "too many fluid nodes for one instance (limit 2^29 FP32, 2^30 FP16, 2^28 with moment buffers)");
     NodeLayout N = node_layout(node_ws, geom->dim, st_kind, params->streaming == CDI_STREAM_PULL, P,
-                               (int64_t)geom->ny * (geom->dim == 2 ? 1 : geom->nz), diag_doubles(geom, P),
-                               geom->nx);
+                               row_count(V.bk), diag_doubles(geom, P), geom->nx);
     if (node_ws_bytes < N.bytes) return fail(CDI_E_BUFFER, "node_ws too small: %llu < %llu",
                                              (unsigned long long)node_ws_bytes, (unsigned long long)N.bytes);
     if (params->np_x_bc != CDI_NPX_PERIODIC && params->np_x_bc != CDI_NPX_CLOSED && geom->nx < 2)
@@ -851,7 +858,7 @@ int cdi_flow_init(const cdi_geometry *geom, const cdi_params *params, void *vox_
     s->dim = geom->dim;
     s->Q = geom->dim == 2 ? 9 : 19;
     s->prec = st_kind;
-    set_form(s, st_kind == kF32 ? fp32_form(params->tau, params->drive, P) : st_kind);
+    set_form(s, held_form(st_kind, params->tau, params->drive, P));
     s->pull = params->streaming == CDI_STREAM_PULL && st_kind != kMom;
     s->inout = params->drive == CDI_INLET_OUTLET;
     s->nvox = nvox;
@@ -900,6 +907,19 @@ int cdi_flow_init(const cdi_geometry *geom, const cdi_params *params, void *vox_
     p.u_in = (float)params->u_in;
     p.rho_out = (float)params->rho_out;
     p.dpsi_dx = (float)(params->dpsi_vt / geom->nx);
+    double dmin = std::min(params->D[0], params->D[1]);
+    p.h2_max = (float)(dmin * dmin / 4.0);  // |Pe| = 2 |h| / D <= 1
+    p.steep = 0;
+    for (int k = 0; k < 2; ++k) {
+        const double D = params->D[k], i2 = 4.0 / (D * D);
+        const double c[4] = {D * i2 / 12, -D * i2 * i2 / 720, D * i2 * i2 * i2 / 30240,
+                             -D * i2 * i2 * i2 * i2 / 1209600};
+        for (int q = 0; q < 4; ++q)  // (finite for any D: a product with h = 0 stays 0)
+            p.sgc[k][q] = (float)std::max(-3e38, std::min(3e38, c[q]));
+        p.hr[k] = 0.5f * p.z[k] * p.D[k] * p.dpsi_dx;
+        // (half of the range is left to the flow)
+        if (!(std::fabs(p.hr[k]) <= 0.75 * dmin / 2)) p.steep = 1;
+    }
     p.npx = params->np_x_bc;
     p.dt = (float)(1.0 / params->np_substeps);
     p.psi = params->psi_field ? N.psi : nullptr;  // filled below in internal order
@@ -913,8 +933,8 @@ int cdi_flow_init(const cdi_geometry *geom, const cdi_params *params, void *vox_
     };
     // rest state: f - w_i = 0 (FP32) / zero deviations and zero moments (FP16, moments)
     if (moment_buffers(s->prec)) {
-        if (s->st == kF16) chk(launch_fill_u32((uint32_t *)N.f, 0u, (int64_t)s->Q * P / 2, st));
-        if (s->st == kF16 && s->pull) chk(launch_fill_u32((uint32_t *)N.f2, 0u, (int64_t)s->Q * P / 2, st));
+        if (s->prec == kF16) chk(launch_fill_u32((uint32_t *)N.f, 0u, (int64_t)s->Q * P / 2, st));
+        if (s->prec == kF16 && s->pull) chk(launch_fill_u32((uint32_t *)N.f2, 0u, (int64_t)s->Q * P / 2, st));
         chk(launch_fill_f32((float *)N.M[0], 0.f, 4 * P, st));
         chk(launch_fill_f32((float *)N.M[1], 0.f, 4 * P, st));
     } else if (s->st == kH16) {
@@ -933,14 +953,16 @@ int cdi_flow_init(const cdi_geometry *geom, const cdi_params *params, void *vox_
     }
     if (params->psi_field)
         chk(launch_permute(params->psi_field, N.psi, V.lex2int, (int)n_fluid, (int)P, 1, 0, st));
-    chk(launch_fill_f32(N.C[0], (float)params->c0, 2 * P, st));
-    chk(launch_fill_f32(N.C[1], (float)params->c0, 2 * P, st));
+    chk(launch_fill_f32((float *)N.C[0], (float)params->c0, 2 * P, st));
+    chk(launch_fill_f32((float *)N.C[1], (float)params->c0, 2 * P, st));
     chk(launch_fill_u32((uint32_t *)N.Clo[0], 0u, P, st));
     chk(launch_fill_u32((uint32_t *)N.Clo[1], 0u, P, st));
     chk(launch_fill_f64(N.acc, 0.0, 8ll * s->ntiles, st));
     chk(launch_fill_f64(N.resid, 0.0, 2ll * s->ntiles, st));
     chk(launch_build_nbr(s->dim, g, N.nbr, st));
-    // the ion-carrying steps read their neighbours from the list by default
+    chk(launch_build_rows(g, N.rows, st));
+    g.rows = N.rows;
+    // the ion-only steps read their neighbours from the list by default
     g.nbr = N.nbr;
     s->tuning.nbr_list = 1;
     if (err == CDI_OK) err = build_schedule(s, 0, 0);  // bricks already give locality
@@ -1162,14 +1184,16 @@ int cdi_set_np_velocity(cdi_solver *s, const float *j)
 int cdi_copy_concentration(cdi_solver *s, float *c)
 {
     if (!s || !c) return fail(CDI_E_INVALID, "NULL argument");
-    return planes_d2h(s, c, s->node.C[s->ccur], 2);
+    HIPCHK(launch_pair_planes((const float *)s->node.C[s->ccur], s->node.tmp, s->P, 0, s->stream));
+    return planes_d2h(s, c, s->node.tmp, 2);
 }
 
 int cdi_set_concentration(cdi_solver *s, const float *c)
 {
     if (!s || !c) return fail(CDI_E_INVALID, "NULL argument");
-    int rc = planes_h2d(s, s->node.C[s->ccur], c, 2);
+    int rc = planes_h2d(s, s->node.tmp, c, 2);
     if (rc) return rc;
+    HIPCHK(launch_pair_planes(s->node.tmp, (float *)s->node.C[s->ccur], s->P, 1, s->stream));
     HIPCHK(launch_fill_u32((uint32_t *)s->node.Clo[s->ccur], 0u, s->P, s->stream));  // no remainders
     return CDI_OK;
 }
@@ -1631,7 +1655,7 @@ int cdi_snapshot(cdi_solver *s, void *host, uint64_t bytes)
     if (bytes < sizeof(SnapHeader) + s->node.state_bytes) return fail(CDI_E_BUFFER, "snapshot buffer too small");
     SnapHeader h{kSnapMagic, s->node.state_bytes, s->parity, s->mcur, s->jcur, s->ccur, s->jstate, s->fcur,
                  s->p.psi != nullptr,
-                 s->rcur | (s->rpend << 1) | (s->rlive << 2) | ((s->prec == kF32 && s->st == kMom) << 3),
+                 s->rcur | (s->rpend << 1) | (s->rlive << 2) | ((s->prec == kF32 && s->st == kMom) << 3) | (1 << 4),
                  s->flow_steps, s->np_steps, s->nf};
     std::memcpy(host, &h, sizeof h);
     return d2h(s, (uint8_t *)host + sizeof h, s->node.base, s->node.state_bytes);
@@ -1646,11 +1670,19 @@ int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes)
     if (h.magic != kSnapMagic || h.bytes != s->node.state_bytes || h.nf != s->nf ||
         bytes < sizeof h + h.bytes)
         return fail(CDI_E_INVALID, "snapshot does not belong to this solver layout");
-    const int held = s->prec == kF32 ? ((h.rstate >> 3) & 1 ? kMom : kF32) : s->prec;
-    if (s->prec == kF32 && held == kMom && fp32_form(s->params.tau, s->params.drive, s->P) != kMom)
-        return fail(CDI_E_INVALID, "snapshot holds the moments of a tau = 1 flow");
+    int held = held_form(s->prec, s->params.tau, s->params.drive, s->P);
+    if (s->prec == kF32) {
+        const int saved = (h.rstate >> 3) & 1 ? kMom : kF32;
+        if (saved == kMom && held != kMom) return fail(CDI_E_INVALID, "snapshot holds the moments of a tau = 1 flow");
+        held = saved;
+    }
     int rc = h2d(s, s->node.base, (const uint8_t *)host + sizeof h, s->node.state_bytes);
     if (rc) return rc;
+    if (!((h.rstate >> 4) & 1))  // written with the species in planes
+        for (float2 *c : s->node.C) {
+            HIPCHK(hipMemcpyAsync(s->node.tmp, c, 8ull * s->P, hipMemcpyDeviceToDevice, s->stream));
+            HIPCHK(launch_pair_planes(s->node.tmp, (float *)c, s->P, 1, s->stream));
+        }
     // an FP32 snapshot may hold populations where this solver holds moments:
     // its state is stepped on as the populations it is
     set_form(s, held);

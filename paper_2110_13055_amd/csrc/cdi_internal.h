@@ -12,7 +12,8 @@
 //                belong to the emitters of the populations now stored)
 //   jbuf         advecting mass flux j = rho u for the ions, d planes of P,
 //                double buffered (fused steps read one and write the other)
-//   conc         2 species x P, double buffered (Jacobi update)
+//   conc         both species of a node as a float2, double buffered (Jacobi
+//                update)
 //   acc          per tile 8 doubles: A_na, A_cl, In_na, In_cl, Out_na, Out_cl
 #pragma once
 
@@ -101,10 +102,13 @@ struct Grid {
     // (band of rows, z) so the planes above and below a tile were visited
     // shortly before by the same XCD and are still in its L2.
     const int *sched;
-    // Optional neighbour list: map value of the neighbour of node n along
-    // direction i in nbr[(i - 1) * P + n] (i = 1 .. Q-1), so that a step reads
-    // it with the node's other data instead of after its coordinates.
+    // Optional neighbour list: map value of the face neighbour of node n along
+    // direction i in nbr[(i - 1) * P + n] (i = 1 .. 2 d), so that an ion-only
+    // step reads it with the node's other data instead of after its coordinates.
     const int *nbr;
+    // The lattice's rows (below): what the steps that do not read the list
+    // look their neighbours up in.
+    const int4 *rows;
     // dynamic LDS reserved per step workgroup: caps the workgroups resident
     // per CU (and so the working set the L2 must hold); 0 = no cap
     int lds_pad;
@@ -112,6 +116,20 @@ struct Grid {
     // slots in LDS (set by the host from the tuning and the tile count)
     int stage_odd;
 };
+
+// A row: the 2^bsx voxels along x at one (y, z) of a brick, in the order of
+// the brick enumeration, as one int4:
+//   x  node index of the row's first fluid voxel (its fluid voxels are
+//      consecutive nodes)
+//   y  fluid bits: bit 0 the voxel before the row, bit 1 + i voxel i, then the
+//      voxel after the row's last one; bit 31: the row holds an inert solid
+//   z  map value of the voxel before the row (wrapped, or kOutside beyond an
+//      open x end)
+//   w  map value of the voxel after it
+// A node's three neighbours in one row are its rank among the row's bits and
+// the nodes beside it, so a step loads 9 rows (D3Q19) instead of 18 map
+// entries, and 1 B per voxel instead of 4.
+static_assert(sizeof(int4) == 16, "a row is 16 bytes");
 
 struct Phys {
     float omega;       // 1 / tau
@@ -124,6 +142,12 @@ struct Phys {
     float c0, c_out, u_in;
     float rho_out;     // outlet density of the flow
     float dpsi_dx;     // ramp drop per cell (dpsi / nx)
+    // Scharfetter-Gummel series in the half drift h (see sg_series): D Bs =
+    // D + c1 h^2 + .. + c4 h^8 per species, valid while h^2 <= h2_max (|Pe| <= 1
+    // for both species); hr: the ramp's half drift across an x face; steep: the
+    // ramp alone comes near that bound
+    float sgc[2][4], h2_max, hr[2];
+    int steep;
     int npx;
     float dt;
     const float *psi;  // optional field (fluid order), else ramp
@@ -139,8 +163,8 @@ struct Bufs {
     float4 *Mout;
     const float *jin;
     float *jout;
-    const float *Cin;
-    float *Cout;
+    const float2 *Cin;  // both species of a node together: a neighbour's pair is one load
+    float2 *Cout;
     const __half2 *Clin;  // the concentrations' FP16 remainders (see lo_encode), per node
     __half2 *Clout;
     double *acc;
@@ -243,7 +267,13 @@ hipError_t launch_plane_means(const Grid &g, const float *drho, int stride, cons
                               hipStream_t s);
 // Packed coordinates of the first node of every tile (host-side tile schedule).
 hipError_t launch_tile_heads(const Grid &g, uint32_t *heads, hipStream_t s);
-// Neighbour list of every fluid node (see Grid::nbr), Q-1 planes of P.
+// The rows of the lattice (Grid::rows), brick_enum_size / 2^bsx of them.
+int64_t row_count(const Bricks &bk);
+hipError_t launch_build_rows(const Grid &g, int4 *rows, hipStream_t s);
+// Both species between a float2 per node and two planes of P (in either order
+// of nodes): to_pairs: dst is the float2 array.
+hipError_t launch_pair_planes(const float *src, float *dst, int P, int to_pairs, hipStream_t s);
+// Neighbour list of every fluid node (see Grid::nbr), 2 d planes of P.
 hipError_t launch_build_nbr(int dim, const Grid &g, int *nbr, hipStream_t s);
 // j = rho u from the moments buffer (FP16 and moment storage; rref: the
 // plane references its densities are relative to, nullptr: zero).
@@ -252,7 +282,7 @@ hipError_t launch_j_from_m(int dim, const Grid &g, const float4 *M, const float 
 hipError_t launch_reduce_tiles(const double *in, int ntiles, int stride, int width, double *out,
                                hipStream_t s);
 // FP64 sum of each concentration field with its remainders (solute mass): out[0..1].
-hipError_t launch_mass(const Grid &g, const float *C, const __half2 *Clo, double *part, double *out, hipStream_t s);
+hipError_t launch_mass(const Grid &g, const float2 *C, const __half2 *Clo, double *part, double *out, hipStream_t s);
 // max over nodes/species of dt * (sum of outflow coefficients); out[0].
 hipError_t launch_stability(int dim, const Grid &g, const Phys &p, const float *j, double *part,
                             double *out, hipStream_t s);

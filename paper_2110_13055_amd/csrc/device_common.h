@@ -50,6 +50,11 @@ __device__ __forceinline__ void stu(T *base, uint32_t idx, T v)
     *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + idx * (uint32_t)sizeof(T)) = v;
 }
 
+// No instruction is scheduled across this point: loads written before it are
+// issued before what uses them. (Left alone, the scheduler moves each load down
+// to its use to save registers, two in flight at a time.)
+__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
+
 // blockIdx -> tile: workgroups are dealt round-robin over the 8 XCDs, each
 // with its own L2; this keeps consecutive tiles on one XCD so that the y/z
 // neighbours a tile touches were mostly fetched by the same L2.
@@ -99,7 +104,8 @@ __device__ inline void unpack_xyz(const Grid &g, uint32_t c, int &x, int &y, int
 // that axis's share of the neighbour's brick-ordered index. The brick part
 // (above the in-brick bits) and the in-brick part occupy disjoint bits, so a
 // neighbour's index is the plain sum of its three axis shares: one three-way
-// add per lattice direction. Coordinates wrap on every axis (the index is
+// add per lattice direction (the shares are kept as byte offsets into the
+// map, below 2^32 for 2^30 voxels). Coordinates wrap on every axis (the index is
 // always in range); xo marks offsets beyond an open x end.
 struct NbCtx {
     uint32_t X[3], Y[3], Z[3];
@@ -120,19 +126,19 @@ __device__ inline void nb_ctx(const Grid &g, int x, int y, int z, bool periodic_
             xn = xn < 0 ? xn + g.nx : xn - g.nx;
         }
         c.xo[d] = out;
-        c.X[d] = ((uint32_t)(xn >> k.bsx) << V) | (uint32_t)(xn & ((1 << k.bsx) - 1));
+        c.X[d] = (((uint32_t)(xn >> k.bsx) << V) | (uint32_t)(xn & ((1 << k.bsx) - 1))) << 2;
         int yn = y + d - 1;
         yn = yn < 0 ? yn + g.ny : (yn >= g.ny ? yn - g.ny : yn);
         // brick-row products as 24-bit multiplies (full rate; the 32-bit
         // multiply issues at a quarter): below 2^30 voxels, no brick count or
         // brick index reaches 2^24
-        c.Y[d] = (__umul24((uint32_t)(yn >> k.bsy), (uint32_t)k.nbx) << V) |
-                 ((uint32_t)(yn & ((1 << k.bsy) - 1)) << k.bsx);
+        c.Y[d] = ((__umul24((uint32_t)(yn >> k.bsy), (uint32_t)k.nbx) << V) |
+                  ((uint32_t)(yn & ((1 << k.bsy) - 1)) << k.bsx)) << 2;
         if (L::D == 3) {
             int zn = z + d - 1;
             zn = zn < 0 ? zn + g.nz : (zn >= g.nz ? zn - g.nz : zn);
-            c.Z[d] = (__umul24((uint32_t)(zn >> k.bsz), (uint32_t)(k.nbx * k.nby)) << V) |
-                     ((uint32_t)(zn & ((1 << k.bsz) - 1)) << (k.bsx + k.bsy));
+            c.Z[d] = ((__umul24((uint32_t)(zn >> k.bsz), (uint32_t)(k.nbx * k.nby)) << V) |
+                      ((uint32_t)(zn & ((1 << k.bsz) - 1)) << (k.bsx + k.bsy))) << 2;
         } else {
             c.Z[d] = 0;
         }
@@ -145,8 +151,94 @@ template <class L>
 __device__ inline int nb_get(const Grid &g, const NbCtx &c, int i)
 {
     const int dx = L::ex[i] + 1, dy = L::ey[i] + 1, dz = L::ez[i] + 1;
-    const int m = ldu(g.map, c.X[dx] + c.Y[dy] + c.Z[dz]);
+    const int m = *reinterpret_cast<const int *>(reinterpret_cast<const char *>(g.map) + (c.X[dx] + c.Y[dy] + c.Z[dz]));
     return (L::ex[i] != 0 && c.xo[dx]) ? kOutside : m;
+}
+
+// A node's neighbours: n[i] the node along direction i, the node itself where
+// that voxel is not fluid (fl[i] false).
+template <class L>
+struct Nbrs {
+    int n[L::Q];
+    bool fl[L::Q];
+};
+
+template <class L>
+__device__ __forceinline__ void set_nbr(Nbrs<L> &nb, int i, int m, int self)
+{
+    nb.fl[i] = m >= 0;
+    nb.n[i] = m >= 0 ? m : self;
+}
+
+// Neighbours of node n at (x, y, z) from the lattice's rows (see cdi_internal.h): all
+// directions (ALL) or the faces. inert: a row of its faces holds an inert solid.
+template <class L, int ALL>
+__device__ __forceinline__ void nb_rows(const Grid &g, int x, int y, int z, int n, Nbrs<L> &nb, bool &inert)
+{
+    const Bricks &k = g.bk;
+    const int S = k.bsy + k.bsz, xi = x & ((1 << k.bsx) - 1);
+    uint32_t Y[3], Z[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {  // row shares of the three y and z, as byte offsets
+        int yn = y + d - 1;
+        yn = yn < 0 ? yn + g.ny : (yn >= g.ny ? yn - g.ny : yn);
+        Y[d] = ((__umul24((uint32_t)(yn >> k.bsy), (uint32_t)k.nbx) << S) | (uint32_t)(yn & ((1 << k.bsy) - 1))) << 4;
+        if (L::D == 3) {
+            int zn = z + d - 1;
+            zn = zn < 0 ? zn + g.nz : (zn >= g.nz ? zn - g.nz : zn);
+            Z[d] = ((__umul24((uint32_t)(zn >> k.bsz), (uint32_t)(k.nbx * k.nby)) << S) |
+                    ((uint32_t)(zn & ((1 << k.bsz) - 1)) << k.bsy)) << 4;
+        } else {
+            Z[d] = 0;
+        }
+    }
+    const uint32_t X = (uint32_t)(x >> k.bsx) << (S + 4);
+    // rows by (ey + 1) + 3 (ez + 1); the edges and corners of the y-z square
+    // hold one direction each with ALL, none otherwise
+    int4 r[9];
+    uint32_t t[9];
+    int c[9];
+#pragma unroll
+    for (int q = 0; q < (L::D == 3 ? 9 : 3); ++q) {
+        const int s = L::D == 3 ? q : q + 3;
+        const int dy = s % 3, dz = s / 3;
+        const bool corner = dy != 1 && dz != 1;
+        if (corner && !ALL) continue;
+        const char *at = reinterpret_cast<const char *>(g.rows) + (X + Y[dy] + Z[dz]);
+        if (s == 4 || (!corner && ALL)) {
+            r[s] = *reinterpret_cast<const int4 *>(at);
+        } else {
+            const int2 h = *reinterpret_cast<const int2 *>(at);
+            r[s] = make_int4(h.x, h.y, 0, 0);
+        }
+    }
+    const bool first = xi == 0, last = xi == (1 << k.bsx) - 1 || x == g.nx - 1;
+#pragma unroll
+    for (int q = 0; q < (L::D == 3 ? 9 : 3); ++q) {
+        const int s = L::D == 3 ? q : q + 3;
+        const bool corner = s % 3 != 1 && s / 3 != 1;
+        if (corner && !ALL) continue;
+        t[s] = (uint32_t)r[s].y >> xi;  // bits 0, 1, 2: x - 1, x, x + 1
+        c[s] = s == 4 ? n : r[s].x + __popc(((uint32_t)r[s].y >> 1) & ((1u << xi) - 1u));
+    }
+    nb.n[0] = n;
+    nb.fl[0] = true;
+#pragma unroll
+    for (int i = 1; i < (ALL ? L::Q : 2 * L::D + 1); ++i) {
+        const int s = (L::ey[i] + 1) + 3 * (L::ez[i] + 1);
+        int m;
+        if (L::ex[i] == 0)
+            m = c[s];
+        else if (L::ex[i] < 0)
+            m = first ? r[s].z : c[s] - 1;
+        else
+            m = last ? r[s].w : c[s] + (int)((t[s] >> 1) & 1u);
+        nb.fl[i] = (t[s] >> (L::ex[i] + 1)) & 1u;
+        nb.n[i] = nb.fl[i] ? m : n;
+    }
+    int any = r[4].y | r[3].y | r[5].y;
+    if (L::D == 3) any |= r[1].y | r[7].y;
+    inert = any < 0;
 }
 
 // acc + c v for a lattice vector component c (-1, 0 or 1 on D2Q9 and D3Q19;
@@ -213,22 +305,6 @@ __device__ __forceinline__ float feq_dir(int i, const EqTerms &t, float ux, floa
     return feq_eu(L::w[i], t, lat_dot<L>(i, ux, uy, uz));
 }
 
-// one direction of weight w, from dr = rho - 1 - R, rho and e.u, where each
-// direction has its own moments (the emitters' equilibria of the FP16 and
-// moment storages): the same polynomial, evaluated directly
-__device__ inline float feq_rel_eu(float w, float dr, float rho, float eu, float ux, float uy, float uz, int linear)
-{
-    if (linear) return w * (dr + 3.f * rho * eu);
-    const float uu = ux * ux + uy * uy + uz * uz;
-    return w * (dr + rho * (3.f * eu + 4.5f * eu * eu - 1.5f * uu));
-}
-
-// The same with R = 0 (equilibrium minus w_i, from rho - 1).
-__device__ inline float feq_bar_eu(float w, float drho, float eu, float ux, float uy, float uz, int linear)
-{
-    return feq_rel_eu(w, drho, 1.f + drho, eu, ux, uy, uz, linear);
-}
-
 // FP32 population storage holds f_i - w_i (1 + R[x_s]), where x_s is the x
 // plane of the node whose slot holds the value (pull streaming: the emitter,
 // the node that collided it; AA: the node written to) and R[x] is a reference
@@ -267,19 +343,19 @@ __device__ inline PlaneRef plane_ref(const Grid &g, const float *rin, const floa
 // g_i from the stored value read for direction i (ODD: the kernels' parity
 // argument) of a node whose neighbours are nb.
 template <class L, int ODD>
-__device__ __forceinline__ float rel_pop(float raw, int i, const int *nb, const PlaneRef &r)
+__device__ __forceinline__ float rel_pop(float raw, int i, const Nbrs<L> &nb, const PlaneRef &r)
 {
-    const bool fl = (i != 0) && nb[L::opp[i]] >= 0;
+    const bool fl = (i != 0) && nb.fl[L::opp[i]];
     const bool there = ODD != 0 && fl;  // pull or odd parity: read in the emitter's slot
     return raw + L::w[i] * (there ? r.dIn[L::ex[i] + 1] : r.dIn[1]);
 }
 
 // The value to store for outgoing g_i (relative to Rout[x]).
 template <class L, int ODD>
-__device__ __forceinline__ float stored_pop(float g, int i, const int *nb, const PlaneRef &r)
+__device__ __forceinline__ float stored_pop(float g, int i, const Nbrs<L> &nb, const PlaneRef &r)
 {
     if (ODD != 1 || i == 0) return g;  // written into the node's own slot
-    return nb[i] >= 0 ? g + L::w[i] * r.dOut[L::ex[i] + 1] : g;
+    return nb.fl[i] ? g + L::w[i] * r.dOut[L::ex[i] + 1] : g;
 }
 
 // Populations are stored in blocks of 64 nodes, one wave: block k holds the
@@ -311,20 +387,19 @@ __device__ __forceinline__ const T *pop_at(const void *F, int q, int n)
     return node + (q << kPopBlockLog);
 }
 
-// Value of direction a at node na, or of direction b at node nb (one of the
-// two per lane).
+// Value of direction a or b (one of the two per lane) at node m.
 template <int FP16, int Q>
-__device__ __forceinline__ float ld_pair(const void *F, int a, int na, int b, int nb, bool first)
+__device__ __forceinline__ float ld_pair(const void *F, int a, int b, int m, bool first)
 {
-    const int q = first ? a : b, m = first ? na : nb;
+    const int q = first ? a : b;
     if (FP16) return __half2float(*pop_at<Q, __half>(F, q, m));
     return *pop_at<Q, float>(F, q, m);
 }
 
 template <int FP16, int Q>
-__device__ __forceinline__ void st_pair(void *F, int a, int na, int b, int nb, bool first, float v)
+__device__ __forceinline__ void st_pair(void *F, int a, int b, int m, bool first, float v)
 {
-    const int q = first ? a : b, m = first ? na : nb;
+    const int q = first ? a : b;
     if (FP16)
         *pop_at<Q, __half>(F, q, m) = __float2half_rn(v);
     else
@@ -334,68 +409,109 @@ __device__ __forceinline__ void st_pair(void *F, int a, int na, int b, int nb, b
 // Stored value behind the incoming population i of node n (FP32 f - w_i or
 // the scaled FP16 deviation; nothing with moment storage).
 template <class L, int ST, int ODD>
-__device__ inline float gather_raw(const void *F, int P, const int *nb, int n, int i)
+__device__ inline float gather_raw(const void *F, int P, const Nbrs<L> &nb, int n, int i)
 {
     if (kMoments<ST>) return 0.f;
     constexpr bool H = kHalfPop<ST>;
     const int j = L::opp[i];
-    const bool fl = (i != 0) && nb[j] >= 0;
+    const bool fl = i != 0 && nb.fl[j];
     // pull: plane i of the emitter x - e_i, or the node's own reflected plane j
-    if (ODD == kPull) return ld_pair<H, L::Q>(F, i, nb[j], j, n, fl);
+    if (ODD == kPull) return ld_pair<H, L::Q>(F, i, j, i == 0 ? n : nb.n[j], fl);
     // AA: plane i of the node itself, or (odd parity, fluid emitter) plane j of the emitter
-    return ld_pair<H, L::Q>(F, i, n, j, nb[j], !ODD || i == 0 || !fl);
+    return ld_pair<H, L::Q>(F, i, j, !ODD || i == 0 ? n : nb.n[j], !ODD || i == 0 || !fl);
 }
 
-// FP16 and moment storage: f_i - w_i from the stored value and the emitter's
-// moments m. The emitter x - e_i sent it along e_i; a reflected one (fl
-// false) was sent by x along e_opp(i) = -e_i, which only flips the sign of
-// e.u (w_opp(i) = w_i).
-// kMomR: m.x is relative to the emitter's plane, and the result to Rout of
-// the node's (f_i - w_i (1 + pr.rout)).
+// FP16 and moment storage: the incoming population of direction i before its
+// weight, (f_i - w_i) / w_i less the FP16 deviation, from the emitter's
+// moments m: dr + rho (E (+-3 + 4.5 E) - 1.5 u.u), E = e_i . u. The emitter
+// x - e_i sent it along e_i; a reflected one (fl false) was sent by x along
+// e_opp(i) = -e_i, which only flips the sign of e.u (w_opp(i) = w_i). The
+// linear (Stokes) equilibrium drops the squares by uniform factors, without a
+// branch per direction (in which the compiler also split the moments' loads).
+// kMomR: m.x is relative to the emitter's plane, the result to Rout of the
+// node's.
 template <class L, int ST>
-__device__ inline float from_emitter(float raw, int i, bool fl, float4 m, const Phys &p, const PlaneRef &pr)
+__device__ __forceinline__ float emitter_g(int i, bool fl, float4 m, const Phys &p, const PlaneRef &pr)
 {
-    // the full product, zeros included: with every component of m used, the
-    // compiler keeps each emitter's float4 one load (lat_dot let it narrow the
-    // loads of directions that need fewer components into several, and the
-    // moment storage's fused step took 7 % longer)
-    const float eu = L::ex[i] * m.y + L::ey[i] * m.z + L::ez[i] * m.w;
+    const float c2 = p.linear_eq ? 0.f : 4.5f, c1 = p.linear_eq ? 0.f : -1.5f;
+    float dr = m.x, rho;
     if (ST == kMomR) {
-        const float dr = m.x + (fl ? pr.dIn[L::ex[i] + 1] : pr.dIn[1]);
-        return feq_rel_eu(L::w[i], dr, 1.f + pr.rout + dr, fl ? eu : -eu, m.y, m.z, m.w, p.linear_eq);
+        dr = m.x + (fl ? pr.dIn[L::ex[i] + 1] : pr.dIn[1]);
+        rho = 1.f + pr.rout + dr;
+    } else {
+        rho = 1.f + m.x;
     }
-    const float fe = feq_bar_eu(L::w[i], m.x, fl ? eu : -eu, m.y, m.z, m.w, p.linear_eq);
-    return ST == kMom ? fe : fe + raw * p.hs_inv;
+    const float uu = fmaf(m.w, m.w, fmaf(m.z, m.z, m.y * m.y));
+    if (i == 0) return fmaf(rho, c1 * uu, dr);
+    const float E = lat_dot<L>(i, m.y, m.z, m.w);
+    return fmaf(rho, fmaf(c1, uu, E * fmaf(c2, E, fl ? 3.f : -3.f)), dr);
 }
 
-// Incoming f_i - w_i of node n (nb: map values of n's neighbours; M: the
+// Zeroth and first moments accumulated from g, the rest direction and then
+// each direction i (odd) with its opposite i + 1: their sum and difference are
+// formed first, so that equal values cancel in the first moments exactly
+// (accumulated one by one with fused multiply-adds they leave the rounding of w
+// g: 40 % more velocity error after 100 steps); and from the FP16 deviations.
+struct MomSums {
+    float d = 0.f, jx = 0.f, jy = 0.f, jz = 0.f;
+};
+template <class L>
+__device__ __forceinline__ void add_rest(MomSums &s, float g)
+{
+    s.d = fmaf(L::w[0], g, s.d);
+}
+template <class L>
+__device__ __forceinline__ void add_pair(MomSums &s, int i, float g, float h)
+{
+    const float t = g - h;
+    s.d = fmaf(L::w[i], g + h, s.d);
+    if (L::ex[i]) s.jx = fmaf(L::w[i] * L::ex[i], t, s.jx);
+    if (L::ey[i]) s.jy = fmaf(L::w[i] * L::ey[i], t, s.jy);
+    if (L::ez[i]) s.jz = fmaf(L::w[i] * L::ez[i], t, s.jz);
+}
+template <class L>
+__device__ __forceinline__ void add_plain(MomSums &s, int i, float v)
+{
+    s.d += v;
+    s.jx = lat_add(s.jx, L::ex[i], v);
+    s.jy = lat_add(s.jy, L::ey[i], v);
+    s.jz = lat_add(s.jz, L::ez[i], v);
+}
+
+// f_i - w_i of an emitter with deviation dev (0 with moment storage).
+template <class L, int ST>
+__device__ __forceinline__ float from_emitter(float dev, int i, bool fl, float4 m, const Phys &p, const PlaneRef &pr)
+{
+    return fmaf(L::w[i], emitter_g<L, ST>(i, fl, m, p, pr), dev);
+}
+
+// Incoming f_i - w_i of node n (nb: n's neighbours; M: the
 // emitters' moments, FP16 and moment storage; pr: kMomR).
 template <class L, int ST, int ODD>
-__device__ inline float gather(const void *F, int P, const int *nb, int n, int i, const float4 *M,
+__device__ inline float gather(const void *F, int P, const Nbrs<L> &nb, int n, int i, const float4 *M,
                                const Phys &p, const PlaneRef &pr)
 {
     const float raw = gather_raw<L, ST, ODD>(F, P, nb, n, i);
     if (ST == kF32) return raw;
     if (ST == kH16) return raw * p.hs_inv;
     const int j = L::opp[i];
-    const bool fl = (i != 0) && nb[j] >= 0;
-    return from_emitter<L, ST>(raw, i, fl, ldu(M, (uint32_t)(fl ? nb[j] : n)), p, pr);
+    return from_emitter<L, ST>(raw * p.hs_inv, i, i != 0 && nb.fl[j], ldu(M, (uint32_t)(i == 0 ? n : nb.n[j])), p, pr);
 }
 
 // Store the outgoing value of direction i (FP32: f* - w_i; FP16: scaled
 // deviation; moment storage: nothing). F: the array written.
 template <class L, int ST, int ODD>
-__device__ inline void scatter(void *F, int P, const int *nb, int n, int i, float v)
+__device__ inline void scatter(void *F, int P, const Nbrs<L> &nb, int n, int i, float v)
 {
     if (kMoments<ST>) return;
     constexpr bool H = kHalfPop<ST>;
     const int j = L::opp[i];
     if (ODD == kPull)
-        st_pair<H, L::Q>(F, i, n, i, n, true, v);  // the node's own slot i
+        st_pair<H, L::Q>(F, i, i, n, true, v);  // the node's own slot i
     else
         // even parity (or the rest direction): the node's own plane opp(i); odd
         // parity: plane i of the fluid neighbour x + e_i, else (reflected) plane opp(i)
-        st_pair<H, L::Q>(F, j, n, i, nb[i], !ODD || i == 0 || nb[i] < 0, v);
+        st_pair<H, L::Q>(F, j, i, !ODD || i == 0 ? n : nb.n[i], !ODD || i == 0 || !nb.fl[i], v);
 }
 
 // Non-equilibrium extrapolation (Guo, Zheng & Shi 2002) for the inlet
@@ -421,6 +537,19 @@ __device__ inline void nee_populations(const Phys &p, bool inlet, const float (&
 #pragma unroll
     for (int i = 0; i < L::Q; ++i)
         fb[i] = feq_dir<L>(i, te, tx, ty, tz) + (fc[i] - feq_dir<L>(i, ce, ux, uy, uz));
+}
+
+// The moments of the populations nee_populations gives, from those of the
+// interior node (c, relative to rc): the target equilibrium's.
+__device__ __forceinline__ MomSums nee_moments(const Phys &p, bool inlet, const MomSums &c, float rc, float rb)
+{
+    const float rho = 1.f + rc + c.d, ri = __builtin_amdgcn_rcpf(rho);
+    MomSums t;
+    t.d = inlet ? (rc + c.d) - rb : (p.rho_out - 1.f) - rb;
+    t.jx = inlet ? rho * p.u_in : p.rho_out * (c.jx * ri);
+    t.jy = inlet ? 0.f : p.rho_out * (c.jy * ri);
+    t.jz = inlet ? 0.f : p.rho_out * (c.jz * ri);
+    return t;
 }
 
 // Concentrations are stored as an FP32 value and an FP16 remainder per
@@ -472,6 +601,17 @@ __device__ inline float sg_flux(float D, float invD2, float hw, float cp, float 
     return fmaf(D * bs, cp - cn, hw * (cp + cn));
 }
 
+// The same flux through a face in a ramp or no potential, in the steps' own
+// form: D Bs as a series in h^2 = (w / 2)^2 whose coefficients (c, per
+// species) carry D, so that it takes four fused multiply-adds. For |Pe| <= 1
+// (the next term of Bs is below 2.1e-8 there).
+__device__ __forceinline__ float sg_series(float D, const float (&c)[4], float h, float cp, float cn)
+{
+    const float h2 = h * h;
+    const float db = fmaf(h2, fmaf(h2, fmaf(h2, fmaf(h2, c[3], c[2]), c[1]), c[0]), D);
+    return fmaf(db, cp - cn, h * (cp + cn));
+}
+
 // Sum of v over the wave in a fixed order, the same value in every lane:
 // neighbouring pairs, then quads, then eights and rows of 16 by DPP lane
 // permutations within each row of 16 lanes (VALU only, no LDS), then the four
@@ -495,30 +635,51 @@ __device__ __forceinline__ float wave_sum(float v)
     return ((r0 + r1) + r2) + r3;
 }
 
-// Per-tile FP64 accumulation of N per-lane FP32 amounts: each wave sums its
-// lanes (wave_sum; a wave whose lanes all hold 0 skips it), thread 0 adds the
-// waves' sums in wave order in FP64 and adds the nonzero totals to acc[0..N).
-// Called by every thread of the block; sm holds (blockDim/64) * N doubles.
-template <int N>
-__device__ inline void tile_accumulate(const float (&v)[N], double *sm, double *acc)
+// Per-tile FP64 accumulation of the ions' six per-lane FP32 amounts (adsorbed,
+// in, out per species): each wave sums its lanes (wave_sum) and leaves the sums
+// in LDS; the wave that comes last adds them in wave order in FP64, lane k
+// amount k, to the tile's accumulators. No barrier: the other waves end at
+// once instead of waiting for the slowest (512^3 electrode, fused moment step:
+// 1.57 ms; 1.62 with the accumulators read early by every wave). sm: kTileSums
+// doubles, tile_sums_init before the first tile; a barrier between two tiles.
+constexpr int kTileWaves = kTile / 64, kTileSums = kTileWaves * 6 + 1;
+
+__device__ inline void tile_sums_init(double *sm)
 {
-    const int wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const float w = __ballot(v[k] != 0.f) ? wave_sum(v[k]) : 0.f;
-        if ((threadIdx.x & 63) == 0) sm[wave * N + k] = (double)w;
-    }
+    if (threadIdx.x == 0) *reinterpret_cast<int *>(sm + kTileWaves * 6) = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int nw = blockDim.x >> 6;
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            double t = 0;
-            for (int w = 0; w < nw; ++w) t += sm[w * N + k];
-            if (t != 0.0) acc[k] += t;
-        }
+}
+
+// at_end: this lane's node has an open x end (amounts 2 .. 5 are 0 elsewhere).
+__device__ inline void tile_accumulate(const float (&v)[6], bool at_end, double *sm, double *acc)
+{
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const bool ads = __any(v[0] != 0.f || v[1] != 0.f), ends = __any(at_end);
+    float w[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (ads) {
+        w[0] = wave_sum(v[0]);
+        w[1] = wave_sum(v[1]);
     }
-    __syncthreads();
+    if (ends) {
+#pragma unroll
+        for (int k = 2; k < 6; ++k) w[k] = wave_sum(v[k]);
+    }
+    int *count = reinterpret_cast<int *>(sm + kTileWaves * 6);
+    int before = 0;
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) sm[wave * 6 + k] = (double)w[k];
+        before = __hip_atomic_fetch_add(count, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    if (__builtin_amdgcn_readfirstlane(before) != kTileWaves - 1) return;
+    // the last wave
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    if (lane < 6) {
+        double t = 0;
+        for (int q = 0; q < kTileWaves; ++q) t += sm[q * 6 + lane];
+        if (t != 0.0) acc[lane] += t;
+    }
+    if (lane == 0) *count = 0;
 }
 
 // Sum over the block in a fixed order (wave shuffles, then the waves in

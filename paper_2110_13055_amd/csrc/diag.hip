@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kTile) void diag_kernel(Grid g, const float *ux, co
 }
 
 // Workgroup (x, chunk): the fluid voxels of plane x with z in the chunk.
-__global__ __launch_bounds__(256) void profile_part_kernel(Grid g, const float *C, double *part, int chunks)
+__global__ __launch_bounds__(256) void profile_part_kernel(Grid g, const float2 *C, double *part, int chunks)
 {
     __shared__ double sm[(256 / 64) * 3];
     const int x = blockIdx.x, zc = blockIdx.y;
@@ -48,8 +48,9 @@ __global__ __launch_bounds__(256) void profile_part_kernel(Grid g, const float *
         const int y = (int)(t % g.ny), z = z0 + (int)(t / g.ny);
         const int m = g.map[brick_index(g.bk, x, y, z)];
         if (m < 0) continue;
-        v[0] += C[m];
-        v[1] += C[(size_t)g.P + m];
+        const float2 c = C[m];
+        v[0] += c.x;
+        v[1] += c.y;
         v[2] += 1.0;
     }
     double out[3];
@@ -88,7 +89,7 @@ hipError_t launch_diag(int dim, const Grid &g, const float *ux, const int *nbr, 
 
 int profile_chunks(const Grid &g) { return (g.nz + kZChunk - 1) / kZChunk; }
 
-hipError_t launch_profile_x(const Grid &g, const float *C, double *part, double *out, hipStream_t s)
+hipError_t launch_profile_x(const Grid &g, const float2 *C, double *part, double *out, hipStream_t s)
 {
     const int chunks = profile_chunks(g);
     profile_part_kernel<<<dim3(g.nx, chunks), 256, 0, s>>>(g, C, part, chunks);

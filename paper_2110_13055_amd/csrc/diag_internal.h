@@ -16,6 +16,6 @@ hipError_t launch_diag(int dim, const Grid &g, const float *ux, const int *nbr, 
 // fluid voxels of plane x, out[2 nx + x] = their number. part: 3 nx zchunks
 // doubles (profile_chunks chunks per plane).
 int profile_chunks(const Grid &g);
-hipError_t launch_profile_x(const Grid &g, const float *C, double *part, double *out, hipStream_t s);
+hipError_t launch_profile_x(const Grid &g, const float2 *C, double *part, double *out, hipStream_t s);
 
 }  // namespace cdi

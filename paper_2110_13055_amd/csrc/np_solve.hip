@@ -43,6 +43,8 @@ enum { kRv = 0, kTs = 1, kTt = 2, kRho0 = 3, kRho1 = 4, kRr = 5, kBb = 6, kRegio
 
 __device__ inline double *reg(const NpsArgs &a, int r, int s) { return a.part + ((size_t)r * 2 + s) * gridDim.x; }
 
+__device__ __forceinline__ double of_species(float2 c, int s) { return s ? c.y : c.x; }
+
 // alpha, beta of a face from the half drift hw (the explicit step's Bs).
 __device__ inline void sg_coef(float D, float invD2, float hw, float &al, float &be)
 {
@@ -177,11 +179,11 @@ __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
             np_node<L>(a.g, a.p, a.j, n, c);
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                xv[s] = a.C[s * P + n];
+                xv[s] = of_species(a.C[n], s);
                 double ax = (c.diag[s] + a.idt) * xv[s];
 #pragma unroll
                 for (int k = 0; k < 2 * L::D; ++k)
-                    if (c.m[k] >= 0) ax -= (double)c.be[s][k] * a.C[s * P + c.m[k]];
+                    if (c.m[k] >= 0) ax -= (double)c.be[s][k] * of_species(a.C[c.m[k]], s);
                 const double rhs = a.idt * xv[s] + c.b[s];
                 rv[s] = rhs - ax;
                 dv[s] = (float)(c.diag[s] + a.idt);
@@ -453,19 +455,18 @@ __global__ __launch_bounds__(kTile) void nps_check_kernel(NpsArgs a, int k, int 
 }
 
 // The FP64 solution as FP32 concentrations with their remainders.
-__global__ __launch_bounds__(kTile) void nps_store_kernel(const double *x, float *C, __half2 *Clo, int P, int n_f)
+__global__ __launch_bounds__(kTile) void nps_store_kernel(const double *x, float2 *C, __half2 *Clo, int P, int n_f)
 {
     const int n = blockIdx.x * kTile + threadIdx.x;
     if (n >= n_f) return;
     const float c0 = (float)x[n], c1 = (float)x[P + n];
-    C[n] = c0;
-    C[P + n] = c1;
+    C[n] = make_float2(c0, c1);
     Clo[n] = __halves2half2(lo_encode((float)(x[n] - c0)), lo_encode((float)(x[P + n] - c1)));
 }
 
 // Rates of adsorption, inflow and outflow of C (per tile, FP64).
 template <class L>
-__global__ __launch_bounds__(kTile) void nps_rates_kernel(Grid g, Phys p, const float *C, const float *j, double scale,
+__global__ __launch_bounds__(kTile) void nps_rates_kernel(Grid g, Phys p, const float2 *C, const float *j, double scale,
                                                           double *acc, double *part)
 {
     __shared__ double sm[(kTile / 64) * 6];
@@ -478,7 +479,7 @@ __global__ __launch_bounds__(kTile) void nps_rates_kernel(Grid g, Phys p, const 
         np_node<L>(g, p, j, n, c);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const double cp = C[s * P + n];
+            const double cp = of_species(C[n], s);
 #pragma unroll
             for (int f = 0; f < 2 * L::D; ++f) {
                 const int m = c.m[f];
@@ -561,14 +562,14 @@ hipError_t launch_nps_check(const NpsArgs &a, int G, int k, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_nps_store(const NpsArgs &a, float *Cout, __half2 *Clo, hipStream_t s)
+hipError_t launch_nps_store(const NpsArgs &a, float2 *Cout, __half2 *Clo, hipStream_t s)
 {
     const int tiles = a.g.P / kTile;
     if (tiles > 0) nps_store_kernel<<<tiles, kTile, 0, s>>>(a.x, Cout, Clo, a.g.P, a.g.n_f);
     return hipGetLastError();
 }
 
-hipError_t launch_nps_rates(int dim, const Grid &g, const Phys &p, const float *C, const float *j, double scale,
+hipError_t launch_nps_rates(int dim, const Grid &g, const Phys &p, const float2 *C, const float *j, double scale,
                             double *acc, double *part, double *out, hipStream_t s)
 {
     const int tiles = g.P / kTile;

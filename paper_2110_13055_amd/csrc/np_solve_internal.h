@@ -26,7 +26,7 @@ enum {
 struct NpsArgs {
     Grid g;
     Phys p;
-    const float *C;    // concentrations of the state the step starts from (2 planes of P)
+    const float2 *C;   // concentrations of the state the step starts from
     const float *j;    // frozen advecting mass flux (d planes of P)
     double idt;        // 1 / dt of a backward-Euler step, 0 for the steady state
     // FP64 vectors, 2 planes (species) of P each
@@ -46,11 +46,11 @@ hipError_t launch_nps_iter(int dim, const NpsArgs &a, int G, int k, hipStream_t 
 // The stop test before iteration k (one workgroup).
 hipError_t launch_nps_check(const NpsArgs &a, int G, int k, hipStream_t s);
 // C_out = (float) x for the fluid nodes.
-hipError_t launch_nps_store(const NpsArgs &a, float *Cout, __half2 *Clo, hipStream_t s);
+hipError_t launch_nps_store(const NpsArgs &a, float2 *Cout, __half2 *Clo, hipStream_t s);
 // Rates of adsorption, inflow and outflow of the concentrations C (FP64 per
 // tile), times scale, added to acc (scale = dt of an implicit step) or
 // written to part and reduced into out[0..5] (out != nullptr).
-hipError_t launch_nps_rates(int dim, const Grid &g, const Phys &p, const float *C, const float *j, double scale,
+hipError_t launch_nps_rates(int dim, const Grid &g, const Phys &p, const float2 *C, const float *j, double scale,
                             double *acc, double *part, double *out, hipStream_t s);
 
 }  // namespace cdi

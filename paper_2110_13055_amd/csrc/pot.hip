@@ -115,8 +115,8 @@ __global__ __launch_bounds__(kTile) void pot_setup_kernel(PotArgs a)
                 diag += m[k] >= 0 ? 1
                                   : (m[k] == kElectrode ||
                                      (m[k] == kOutside && a.xbc[k & 1 ? 0 : 1] == kPsixDirichlet)) ? 2 : 0;
-            double b = a.src * ((double)a.z[0] * ldu(a.C, (uint32_t)n) +
-                                (double)a.z[1] * ldu(a.C, (uint32_t)(P + n)));
+            const float2 c = ldu(a.C, (uint32_t)n);
+            double b = a.src * ((double)a.z[0] * c.x + (double)a.z[1] * c.y);
             xv = a.psi0 ? (double)ldu(a.psi0, (uint32_t)n) : 0.0;
 #pragma unroll
             for (int k = 0; k < 2 * L::D; ++k) {
@@ -385,7 +385,8 @@ __global__ __launch_bounds__(kTile) void pot_refine_kernel(PotArgs a)
             int m[2 * L::D];
             face_maps<L, NBR>(a, n, m);
             const int diag = a.dg[n];
-            double b = a.src * ((double)a.z[0] * ldu(a.C, (uint32_t)n) + (double)a.z[1] * ldu(a.C, (uint32_t)(P + n)));
+            const float2 c = ldu(a.C, (uint32_t)n);
+            double b = a.src * ((double)a.z[0] * c.x + (double)a.z[1] * c.y);
             double ax = diag * ldu(a.x, (uint32_t)n);
             double xm[2 * L::D];  // loaded before use (index 0 where not fluid: unused)
 #pragma unroll

@@ -31,7 +31,7 @@ struct PotArgs {
     double psi_x[2];     // Dirichlet x-face values
     double src;          // kappa2 / (2 c0): charge term per unit sum z C
     float z[2];          // valences
-    const float *C;      // concentrations, 2 planes of P
+    const float2 *C;     // concentrations
     const float *psi0;   // start (the field in use) or nullptr (zero)
     double *x, *r, *q;   // CG vectors, P each
     double *p, *p2;      // search direction, alternating between two buffers

@@ -78,12 +78,11 @@ __device__ __forceinline__ StageT<ST> pop_stored(float v)
 // Where incoming population i of node n (odd parity) is stored: plane pl of
 // node nd; in: nd lies in the tile starting at base.
 template <class L>
-__device__ __forceinline__ bool staged_slot(const int *nb, int n, int i, int base, int &pl, uint32_t &loc)
+__device__ __forceinline__ bool staged_slot(const Nbrs<L> &nb, int n, int i, int base, int &pl, uint32_t &loc)
 {
     const int j = L::opp[i];
-    const bool fl = (i != 0) && nb[j] >= 0;
-    pl = fl ? j : i;
-    loc = (uint32_t)((fl ? nb[j] : n) - base);
+    pl = i != 0 && nb.fl[j] ? j : i;
+    loc = (uint32_t)((i == 0 ? n : nb.n[j]) - base);
     return loc < (uint32_t)kTile;
 }
 
@@ -92,7 +91,7 @@ __device__ __forceinline__ bool staged_slot(const int *nb, int n, int i, int bas
 // the tile (into the same registers, for those lanes only), so that the
 // stage reads are waited for once rather than before every global load.
 template <class L, int ST>
-__device__ __forceinline__ void staged_gather(const void *F, int P, const int *nb, int n, const LdsT<ST> *stage,
+__device__ __forceinline__ void staged_gather(const void *F, int P, const Nbrs<L> &nb, int n, const LdsT<ST> *stage,
                                               int base, StageT<ST> (&raw)[L::Q])
 {
 #pragma unroll
@@ -107,37 +106,46 @@ __device__ __forceinline__ void staged_gather(const void *F, int P, const int *n
         int pl;
         uint32_t loc;
         if (!staged_slot<L>(nb, n, i, base, pl, loc))  // a fluid emitter: plane opp(i) of it
-            raw[i] = *pop_at<L::Q, StageT<ST>>(F, L::opp[i], nb[L::opp[i]]);
+            raw[i] = *pop_at<L::Q, StageT<ST>>(F, L::opp[i], nb.n[L::opp[i]]);
     }
 }
 
 // Store outgoing value v of direction i (odd parity); lds_ok false for the
 // nodes whose slots go through global memory.
 template <class L, int ST>
-__device__ __forceinline__ void staged_scatter(void *F, int P, const int *nb, int n, int i, float v,
+__device__ __forceinline__ void staged_scatter(void *F, int P, const Nbrs<L> &nb, int n, int i, float v,
                                                LdsT<ST> *stage, int base, bool lds_ok)
 {
     const int j = L::opp[i];
-    const bool own = i == 0 || nb[i] < 0;
-    const uint32_t loc = (uint32_t)((own ? n : nb[i]) - base);
+    const bool own = i == 0 || !nb.fl[i];
+    const int m = i == 0 ? n : nb.n[i];
+    const uint32_t loc = (uint32_t)(m - base);
     const bool in = lds_ok && loc < (uint32_t)kTile;
     stage[in ? (own ? j : i) * kTile + (int)loc : L::Q * kTile + (int)threadIdx.x] = pop_stored<ST>(v);
-    if (!in) st_pair<kHalfPop<ST>, L::Q>(F, j, n, i, nb[i], own, v);
+    if (!in) st_pair<kHalfPop<ST>, L::Q>(F, j, i, m, own, v);
 }
 
 // Moments, residual terms, collision and the AA store of one node whose
-// incoming populations (minus w_i) are f; NP: also store the mass flux j for
+// incoming populations (minus w_i) are f (sums: their moments, where they were
+// summed already); NP: also store the mass flux j for
 // the ions of the next step (FP32; the other storages carry it in Mout).
 // FP32 storage: f_i - w_i (1 + pr.rout) on entry, and values stored relative
 // to the plane references of pr (see PlaneRef); the other storages pass zeros.
 template <class L, int ST, int ODD, int NP, bool STAGE = false>
-__device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, const Bufs &b, int P, int n, const int *nb,
-                                const float (&f)[L::Q], const PlaneRef &pr, double (&res)[2],
+__device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, const Bufs &b, int P, int n, const Nbrs<L> &nb,
+                                const float (&f)[L::Q], const PlaneRef &pr, double (&res)[2], const MomSums *sums,
                                 LdsT<ST> *stage = nullptr, int base = 0, bool lds_ok = false)
 {
     constexpr int Q = L::Q, D = L::D;
     float drho, jx, jy, jz;  // drho: rho - 1 - pr.rout
-    lat_moments<L>(f, drho, jx, jy, jz);
+    if (sums) {
+        drho = sums->d;
+        jx = sums->jx;
+        jy = sums->jy;
+        jz = sums->jz;
+    } else {
+        lat_moments<L>(f, drho, jx, jy, jz);
+    }
     if (p.forced) {  // Guo forcing: u = (sum e f + F/2) / rho
         jx += 0.5f * p.F[0];
         jy += 0.5f * p.F[1];
@@ -174,7 +182,6 @@ __device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, co
         stu(b.jout + P, (uint32_t)n, jy);
         if (D == 3) stu(b.jout + 2 * (size_t)P, (uint32_t)n, jz);
     }
-    if (kMoments<ST>) return;  // the post-collision state is the equilibrium of Mout
     const EqTerms eq = eq_terms(drho, rho, ux, uy, uz, p.linear_eq);
     const float om = p.omega;
     // FP16 populations are stored times hs
@@ -214,13 +221,202 @@ __device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, co
     }
 }
 
+// Moments of a node's state (dr: rho - 1 - rout) to the moments buffer, and
+// its residual terms: a whole flow step of the moment storages, whose
+// post-collision state is the equilibrium of Mout.
+template <class L>
+__device__ __forceinline__ void moment_node(const Bufs &b, int n, float dr, float jx, float jy, float jz, float rout,
+                                            double (&res)[2])
+{
+    const float rinv = __builtin_amdgcn_rcpf(1.f + rout + dr);
+    const float ux = jx * rinv, uy = jy * rinv, uz = jz * rinv;
+    if (b.flags & kResid) {
+        const float4 m = ldu(b.Min, (uint32_t)n);
+        const double dx = (double)ux - m.y, dy = (double)uy - m.z, dz = (double)uz - m.w;
+        res[0] += dx * dx + dy * dy + dz * dz;
+        res[1] += (double)ux * ux + (double)uy * uy + (double)uz * uz;
+    }
+    stu(b.Mout, (uint32_t)n, make_float4(dr, ux, uy, uz));
+}
+
+// Moments of the FP16 deviations, kept apart from those of the equilibria so
+// that with zero deviations (tau = 1) both storages round the same sums.
+template <int ST>
+struct DevSums : MomSums {
+    __device__ __forceinline__ void add_to(MomSums &s) const
+    {
+        if constexpr (!kMoments<ST>) {
+            s.d += this->d;
+            s.jx += this->jx;
+            s.jy += this->jy;
+            s.jz += this->jz;
+        }
+    }
+};
+
+// What leaves node n through its faces in one explicit ion step, per species
+// (out), and the part through open x ends (fi in, fo out).
+struct IonFlux {
+    float out[2] = {0.f, 0.f}, fi[2] = {0.f, 0.f}, fo[2] = {0.f, 0.f};
+    float ads = 0.f;  // adsorbing faces
+};
+
+// The fluxes to fluid cells with no potential field and a ramp that is not
+// steep. on: the faces to fluid cells; jn the neighbours' flux along the face's
+// axis, cn their concentrations (0 where the face is not fluid: its flux is
+// formed and multiplied by 0). Straight-line code, without a branch
+// per face; y and z faces, where the ramp has no gradient, share the half drift
+// h between the species. Returns whether every face of the lane is within the
+// series' range.
+template <class L>
+__device__ __forceinline__ bool ion_faces(const Phys &p, const bool (&on)[2 * L::D], const float (&cP)[2],
+                                          const float (&jP)[3], const float2 (&cn)[2 * L::D],
+                                          const float (&jn)[2 * L::D], IonFlux &f)
+{
+    float wx = 0.f, wyz = 0.f;
+#pragma unroll
+    for (int k = 0; k < 2 * L::D; ++k) {
+        const float h = ((k & 1) ? -0.25f : 0.25f) * (jP[k >> 1] + jn[k]);  // (x faces: less the ramp's part)
+        if (k < 2)
+            wx = fmaxf(wx, fabsf(h));
+        else
+            wyz = fmaxf(wyz, fabsf(h));
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const float F = sg_series(p.D[s], p.sgc[s], k < 2 ? h + ((k & 1) ? -p.hr[s] : p.hr[s]) : h, cP[s],
+                                      s ? cn[k].y : cn[k].x);
+            f.out[s] = fmaf(on[k] ? 1.f : 0.f, F, f.out[s]);
+        }
+    }
+    const float w = fmaxf(wyz, wx + fmaxf(fabsf(p.hr[0]), fabsf(p.hr[1])));
+    return w * w <= p.h2_max;
+}
+
+// The same fluxes where ion_faces was out of its range: a rolled loop that
+// looks everything up again, so that the rare case costs the steps no
+// registers. Faces within the series' range take the series, as their other
+// cell does.
+template <class L, int ST>
+__device__ __forceinline__ void ion_faces_wide(const Grid &g, const Phys &p, const Bufs &b, int x, int y, int z, bool jm,
+                                               const bool (&end)[2], float c0, float c1, float j0, float j1, float j2,
+                                               IonFlux &f)
+{
+    f.out[0] = f.out[1] = 0.f;
+#pragma unroll 1
+    for (int k = 0; k < 2 * L::D; ++k) {
+        const int m = nb_map<L>(g, x, y, z, k + 1, g.periodic_x);
+        if (m < 0 || (k == 0 && end[0]) || (k == 1 && end[1])) continue;
+        const int axis = k >> 1;
+        float jN;
+        if (jm) {
+            const float4 mm = ldu(b.Min, (uint32_t)m);
+            float r = 1.f + mm.x;
+            if (ST == kMomR) {
+                int xm = x + (k == 0) - (k == 1);
+                xm = xm < 0 ? g.nx - 1 : (xm >= g.nx ? 0 : xm);
+                r = 1.f + ldu(b.rin, (uint32_t)xm) + mm.x;
+            }
+            jN = r * (axis == 0 ? mm.y : (axis == 1 ? mm.z : mm.w));
+        } else {
+            jN = ldu(b.jin + (size_t)axis * g.P, (uint32_t)m);
+        }
+        const float sg = (k & 1) ? -1.f : 1.f;
+        const float h = 0.25f * sg * ((axis == 0 ? j0 : (axis == 1 ? j1 : j2)) + jN);
+        const float2 cm = ldu(b.Cin, (uint32_t)m);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const float hs = axis == 0 ? h + sg * p.hr[s] : h, cp = s ? c1 : c0, cn = s ? cm.y : cm.x;
+            f.out[s] += hs * hs <= p.h2_max ? sg_series(p.D[s], p.sgc[s], hs, cp, cn)
+                                            : sg_flux(p.D[s], 2.f * p.invD[s], hs, cp, cn);
+        }
+    }
+}
+
+// The same in a potential field (psi; the migration of every face from the
+// potential's difference) or in a steep ramp.
+template <class L>
+__device__ __forceinline__ void ion_faces_any(const Phys &p, bool psi, const bool (&on)[2 * L::D], const float (&cP)[2],
+                                              const float (&jP)[3], float psiP, const float2 (&cn)[2 * L::D],
+                                              const float (&jn)[2 * L::D], const float (&psin)[2 * L::D], IonFlux &f)
+{
+    const float invD2[2] = {2.f * p.invD[0], 2.f * p.invD[1]};
+    const float hzD[2] = {0.5f * p.z[0] * p.D[0], 0.5f * p.z[1] * p.D[1]};
+#pragma unroll
+    for (int k = 0; k < 2 * L::D; ++k) {
+        if (on[k]) {
+            const float q = ((k & 1) ? -0.25f : 0.25f) * (jP[k >> 1] + jn[k]);
+            const float d = psi ? psin[k] - psiP : (k == 0 ? -p.dpsi_dx : (k == 1 ? p.dpsi_dx : 0.f));
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                f.out[s] += sg_flux(p.D[s], invD2[s], q - hzD[s] * d, cP[s], s ? cn[k].y : cn[k].x);
+        }
+    }
+}
+
+// The x-end face on side sgi of a node at (x, y, z) on that end, where the
+// ions' treatment of the end is not the lattice's own wrap: the inlet ghost,
+// the open or Dirichlet outlet, or (periodic ions, open flow) the cell at the
+// other end. jm: the neighbours' flux comes from the moments buffer.
+template <class L, int ST>
+__device__ __forceinline__ void ion_end_face(const Grid &g, const Phys &p, const Bufs &b, int sgi, int x, int y,
+                                                       int z, bool jm, bool psi, float c0, float c1, float jP0,
+                                                       float psiP, IonFlux &f)
+{
+    if (p.npx == kNpxClosed) return;
+    const float sg = (float)sgi, cP[2] = {c0, c1};
+    const float hzD[2] = {0.5f * p.z[0] * p.D[0], 0.5f * p.z[1] * p.D[1]};
+    float dpsi = psi ? 0.f : -sg * p.dpsi_dx;
+    if (p.npx == kNpxPeriodic) {
+        const int m = nb_map<L>(g, x, y, z, sgi > 0 ? 1 : 2, true);
+        if (m == kElectrode) f.ads += 1.f;
+        if (m < 0) return;
+        float jN;
+        if (jm) {
+            const float4 mm = ldu(b.Min, (uint32_t)m);
+            // (relative to the other end's plane, with plane references)
+            jN = (ST == kMomR ? 1.f + ldu(b.rin, (uint32_t)(sgi < 0 ? g.nx - 1 : 0)) + mm.x : 1.f + mm.x) * mm.y;
+        } else {
+            jN = ldu(b.jin, (uint32_t)m);
+        }
+        if (psi) dpsi = ldu(p.psi, (uint32_t)m) - psiP;
+        const float2 cm = ldu(b.Cin, (uint32_t)m);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            f.out[s] += sg_flux(p.D[s], 2.f * p.invD[s], 0.25f * (jP0 + jN) * sg - hzD[s] * dpsi, cP[s], s ? cm.y : cm.x);
+        return;
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        if (sgi < 0) {  // inlet face: ghost at c0, inflow u_in
+            const float F = sg_flux(p.D[s], 2.f * p.invD[s], -0.5f * p.u_in - hzD[s] * dpsi, cP[s], p.c0);
+            f.out[s] += F;
+            f.fi[s] -= F;
+        } else {  // outlet face
+            const float hw = 0.5f * jP0 - hzD[s] * dpsi;
+            float F;
+            if (p.npx == kNpxDirichlet) {
+                F = sg_flux(p.D[s], 2.f * p.invD[s], hw, cP[s], p.c_out);
+            } else {  // open: drift carries C_P out, or feed c0 in
+                const float w = 2.f * hw;
+                F = fmaxf(w, 0.f) * cP[s] + fminf(w, 0.f) * p.c0;
+            }
+            f.out[s] += F;
+            f.fo[s] += F;
+        }
+    }
+}
+
 // One 256-node tile of one instance (all threads of the workgroup call it;
 // sm: (kTile/64)*6 doubles of LDS; stg: the stage of kStageOdd steps).
-template <class L, int ST, int ODD, int LBM, int NP, int BATCH = 0, int STG = 0>
+// PSI: whether the ions migrate in a potential field or a steep ramp, kPsiAny:
+// as p says.
+constexpr int kPsiAny = 2;
+
+template <class L, int ST, int ODD, int LBM, int NP, int PSI, int STG = 0>
 __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, const Phys &p, const Bufs &b, int tile, double *sm,
                                                              StageT<ST> *stage)
 {
-    constexpr int Q = L::Q, D = L::D;
+    constexpr int Q = L::Q, D = L::D, F = 2 * L::D;
     constexpr bool kStage = STG && kStageOdd<L, ST, ODD, LBM, NP>;
     LdsT<ST> *const stg = (LdsT<ST> *)stage;
     const int base = tile * kTile;
@@ -228,49 +424,58 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
     const bool active = n < g.n_f;
     const int P = g.P;
     float acc[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    bool at_end = false;
     double res[2] = {0, 0};
 
-    // coordinates and neighbour map values of the node
+    // coordinates and neighbours of the node
     int x = 0, y = 0, z = 0;
-    int nb[Q];
+    Nbrs<L> nb;
+    bool inert = false;             // a face may be an inert solid
+    bool end[2] = {false, false};  // the +x / -x face is an end of the ions' own
     bool edge = false;
     // odd parity, staged: the node's own slots are loaded between its
-    // coordinates and its neighbours' map values (the three in flight
-    // together: each wait is for the earliest), and stored into the stage
-    // after the lookups are issued
+    // coordinates and its neighbours' rows (the three in flight together: each
+    // wait is for the earliest), and stored into the stage after the lookups
+    // are issued
     StageT<ST> own[kStage ? Q : 1];
+    // ion-only steps read their faces' neighbours from the list, when the
+    // instance has one: one dependent load fewer (512^3 electrode: 0.82 ms
+    // against 0.87 through the rows). Steps with a flow, whose nodes need their
+    // coordinates anyway, look them up in the rows (fused: moments 1.61 ms
+    // against 1.80, FP32 2.73 against 2.88, FP16 2.29 against 2.30)
+    constexpr bool need_all = LBM && (ODD || !kPlain<ST>);
+    const bool list = !LBM && g.nbr;
+    const bool coords = LBM || !list;
     if (active) {
-        const uint32_t packed = ldu(g.fluid, (uint32_t)n);
+        uint32_t packed = 0;
+        if (coords) packed = ldu(g.fluid, (uint32_t)n);
         if constexpr (kStage) {
 #pragma unroll
             for (int q = 0; q < Q; ++q) own[q] = *pop_at<Q, StageT<ST>>(b.f, q, n);
         }
-        unpack_xyz(g, packed, x, y, z);
-        constexpr bool need_all = LBM && (ODD || !kPlain<ST>);
+        if (coords) unpack_xyz(g, packed, x, y, z);
         edge = LBM && g.inout && (b.flags & kNee) && (x <= 1 || x >= g.nx - 2);
-        nb[0] = n;
-        // the list, when the instance has one, for the steps that carry the ions
-        // (measured on the 512^3 electrode: ion-only -6 %, fused moments -5 %,
-        // FP16 deviations -3 %, FP16 populations -1.5 % AA / -5.5 % pull); the
-        // fused FP32 step runs equally fast either way and moves 59 B/node less
-        // without it, and flow-only steps stream their populations at the copy
-        // rate already and only pay for the list's bytes (+10 %): those two
-        // look their neighbours up
-        constexpr bool kList = NP && !(LBM && ST == kF32);
-        if (kList && g.nbr) {  // precomputed: independent of the coordinates
+        if (list) {  // precomputed: independent of the coordinates
+            nb.n[0] = n;
+            nb.fl[0] = true;
+            int m[F + 1];
 #pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                const bool want = need_all || (NP && i <= 2 * D) || (edge && i <= 2);
-                nb[i] = want ? ldu(g.nbr + (size_t)(i - 1) * P, (uint32_t)n) : kOutside;
-            }
-        } else {
-            NbCtx ctx;
-            nb_ctx<L>(g, x, y, z, g.periodic_x, ctx);
+            for (int i = 1; i <= F; ++i) m[i] = ldu(g.nbr + (size_t)(i - 1) * P, (uint32_t)n);
+            keep_order();
 #pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                const bool want = need_all || (NP && i <= 2 * D) || (edge && i <= 2);
-                nb[i] = want ? nb_get<L>(g, ctx, i) : kOutside;
+            for (int i = 1; i <= F; ++i) {
+                set_nbr<L>(nb, i, m[i], n);
+                inert = inert || m[i] == kInert;
             }
+            end[0] = !g.periodic_x && m[1] == kOutside;
+            end[1] = !g.periodic_x && m[2] == kOutside;
+        } else if (need_all || NP) {
+            nb_rows<L, need_all>(g, x, y, z, n, nb, inert);
+            end[0] = !g.periodic_x && x == g.nx - 1;
+            end[1] = !g.periodic_x && x == 0;
+        } else if (edge) {  // an even flow step looks at its x neighbours only there
+            set_nbr<L>(nb, 1, nb_map<L>(g, x, y, z, 1, g.periodic_x), n);
+            set_nbr<L>(nb, 2, nb_map<L>(g, x, y, z, 2, g.periodic_x), n);
         }
         if constexpr (kStage) {
 #pragma unroll
@@ -279,279 +484,246 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
     }
 
     // Fused step, in this order: the ions' own and face-neighbour
-    // concentrations (and with FP32 storage their mass fluxes) are loaded;
+    // concentrations (and with FP32 populations their mass fluxes) are loaded;
     // the flow's incoming populations are gathered; the ion update (which
     // needs only the previous step's flux) is computed and stored; then the
     // collision. The ions' loads overlap the flow's, and the ions' inputs
-    // are dead before the collision's register peak. With FP16 and moment
-    // storage the face neighbours' moments are loaded once for both parts
-    // (the flow's emitters, the ions' mass flux). Measured on the 512^3
-    // electrode against loading the ions' inputs after the flow's stores:
-    // FP32 -16 %, moments -17 %, FP16 -16 % per fused step. An ion-only step
-    // loads them the same way, all before its face loop, where a load inside
-    // a divergent branch would wait for its data before the next face starts
-    // (its flux is always the stored one): -27 % per ion-only step.
-    constexpr bool kEarly = NP;
-    constexpr bool kEarlyJ = kEarly && (kPlain<ST> || !LBM);
+    // are dead before the collision's register peak. With the moment buffers
+    // the face neighbours' moments are loaded once for both parts (the flow's
+    // emitters, the ions' mass flux). Measured on the 512^3 electrode against
+    // loading the ions' inputs after the flow's stores: FP32 -16 %, moments
+    // -17 %, FP16 deviations -16 % per fused step. An ion-only step loads them
+    // the same way, all before its faces.
+    constexpr bool kEarlyJ = kPlain<ST> || !LBM;  // the ions' flux is the stored one
     // with a potential field, the neighbours' potential too, where the flux
     // is loaded early (ion-only step 1.18 -> 0.96 ms, FP32 fused 3.50 ->
     // 3.27 ms on the 512^3 electrode, same waves per SIMD); not in the
     // batched kernels, whose per-instance descriptor leaves no registers to
     // spare (their ion-only and FP16 / moment fused forms lose a wave per
     // SIMD, which costs the served requests, all in the ramp, 10 %)
-    constexpr bool kEarlyPsi = kEarlyJ && !BATCH;
-    float ec[2] = {0.f, 0.f}, ej[3] = {0.f, 0.f, 0.f};
+    constexpr bool kEarlyPsi = kEarlyJ && PSI == 1;
+    const bool psi = PSI && p.psi, any = PSI == kPsiAny ? p.psi || p.steep : PSI == 1;
+    float cP[2] = {0.f, 0.f}, jP[3] = {0.f, 0.f, 0.f};
     __half2 elo = __floats2half2_rn(0.f, 0.f);
-    float ecn[2 * D][2], ejn[2 * D], epsi[2 * D];
-    if (kEarly && active) {
-        ec[0] = ldu(b.Cin, (uint32_t)n);
-        ec[1] = ldu(b.Cin + P, (uint32_t)n);
+    float2 cn[F];
+    float jn[F], psin[F];
+    if (NP && active) {
+        const float2 c = ldu(b.Cin, (uint32_t)n);
+        cP[0] = c.x;
+        cP[1] = c.y;
         elo = ldu(b.Clin, (uint32_t)n);
         if (kEarlyJ) {
-            ej[0] = ldu(b.jin, (uint32_t)n);
-            ej[1] = ldu(b.jin + P, (uint32_t)n);
-            ej[2] = D == 3 ? ldu(b.jin + 2 * (size_t)P, (uint32_t)n) : 0.f;
+            jP[0] = ldu(b.jin, (uint32_t)n);
+            jP[1] = ldu(b.jin + P, (uint32_t)n);
+            jP[2] = D == 3 ? ldu(b.jin + 2 * (size_t)P, (uint32_t)n) : 0.f;
         }
 #pragma unroll
-        for (int k = 0; k < 2 * D; ++k) {
-            const int m = nb[k + 1];
-            const bool fl = m >= 0;
-            ecn[k][0] = fl ? ldu(b.Cin, (uint32_t)m) : 0.f;
-            ecn[k][1] = fl ? ldu(b.Cin + P, (uint32_t)m) : 0.f;
-            ejn[k] = (fl && kEarlyJ) ? ldu(b.jin + (size_t)(k >> 1) * P, (uint32_t)m) : 0.f;
-            epsi[k] = (kEarlyPsi && p.psi) ? ldu(p.psi, (uint32_t)(fl ? m : n)) : 0.f;
+        for (int k = 0; k < F; ++k) {
+            const uint32_t q = (uint32_t)nb.n[k + 1];
+            // (loaded for the lanes whose face is fluid: with the node's own
+            // values in the others, FP32 fused steps took 2 % longer)
+            cn[k] = make_float2(0.f, 0.f);
+            jn[k] = 0.f;
+            if (nb.fl[k + 1]) {
+                cn[k] = ldu(b.Cin, q);
+                if (kEarlyJ) jn[k] = ldu(b.jin + (size_t)(k >> 1) * P, q);
+            }
+            psin[k] = kEarlyPsi && p.psi ? ldu(p.psi, q) : 0.f;
         }
+        keep_order();
     }
     if (kStage) __syncthreads();
     const bool nee = g.inout && (b.flags & kNee);
-    // FP16 / moment storage, fused: the node's own and its face neighbours' moments
-    float4 mface[2 * D], mown = make_float4(0.f, 0.f, 0.f, 0.f);
-    bool have_m = false;
+    // fused, with the moment buffers: the ions' flux is in the moments (else,
+    // on the first step of a call, in jin)
+    const bool jm = LBM && !kPlain<ST> && (b.flags & kJFromM);
 
     // the flow's incoming populations (the collision follows the ions)
-    float f[Q];
+    float f[kMoments<ST> ? 1 : Q];
+    MomSums sums;  // with the moment buffers: their moments
     bool do_flow = false;
     PlaneRef pr{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};  // the node's plane references
-    {
-        if (ST == kMomR && active) pr = plane_ref<0>(g, b.rin, b.rout, x);
-        if (LBM && active) {
-            // a boundary node with a fluid interior neighbour is advanced by that neighbour
-            const bool by_partner = edge && ((x == 0 && nb[1] >= 0) || (x == g.nx - 1 && nb[2] >= 0));
-            if (!by_partner) {
-                do_flow = true;
-                if (!kPlain<ST> && NP) {
-#pragma unroll
-                    for (int k = 0; k < 2 * D; ++k)
-                        mface[k] = nb[k + 1] >= 0 ? ldu(b.Min, (uint32_t)nb[k + 1]) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    mown = ldu(b.Min, (uint32_t)n);
-                    have_m = true;
-                    // the incoming populations in groups of 6 directions: the
-                    // group's edge emitters' moments are loaded together (the
-                    // node's own where the emitter is solid, the same values as
-                    // mown), then used; one at a time each load waited for its
-                    // data before the next was issued. Measured on the 512^3
-                    // electrode: moments 2.45 -> 2.01 ms, FP16 3.48 -> 3.25 ms
-                    // per fused step (groups of 4: 2.10 / 3.38; of 10 the
-                    // registers cost a wave per SIMD)
-                    constexpr int kG = 6;
-#pragma unroll
-                    for (int i0 = 0; i0 < Q; i0 += kG) {
-                        float4 mg[kG];
-#pragma unroll
-                        for (int u = 0; u < kG; ++u) {
-                            const int i = i0 + u;
-                            if (i >= Q) break;
-                            const int j = L::opp[i];
-                            const bool fl = (i != 0) && nb[j] >= 0;
-                            if (i == 0)
-                                mg[u] = mown;
-                            else if (j <= 2 * D)
-                                mg[u] = fl ? mface[j - 1] : mown;
-                            else
-                                mg[u] = ldu(b.Min, (uint32_t)(fl ? nb[j] : n));
-                        }
-#pragma unroll
-                        for (int u = 0; u < kG; ++u) {
-                            const int i = i0 + u;
-                            if (i >= Q) break;
-                            const int j = L::opp[i];
-                            const bool fl = (i != 0) && nb[j] >= 0;
-                            f[i] = from_emitter<L, ST>(gather_raw<L, ST, ODD>(b.f, P, nb, n, i), i, fl, mg[u], p, pr);
-                        }
-                    }
-                } else if (!kPlain<ST>) {
-                    // flow only: all emitters' moments loaded first, then used
-                    // (moments 1.73 -> 1.27 ms, FP16 3.08 -> 2.53 ms per flow
-                    // step; groups of 6: 1.34 / 2.64)
-                    constexpr int kG = Q;
-#pragma unroll
-                    for (int i0 = 0; i0 < Q; i0 += kG) {
-                        float4 mg[kG];
-#pragma unroll
-                        for (int u = 0; u < kG; ++u) {
-                            const int i = i0 + u;
-                            if (i >= Q) break;
-                            const int j = L::opp[i];
-                            const bool fl = (i != 0) && nb[j] >= 0;
-                            mg[u] = ldu(b.Min, (uint32_t)(fl ? nb[j] : n));
-                        }
-#pragma unroll
-                        for (int u = 0; u < kG; ++u) {
-                            const int i = i0 + u;
-                            if (i >= Q) break;
-                            const int j = L::opp[i];
-                            const bool fl = (i != 0) && nb[j] >= 0;
-                            f[i] = from_emitter<L, ST>(gather_raw<L, ST, ODD>(b.f, P, nb, n, i), i, fl, mg[u], p, pr);
-                        }
-                    }
-                } else {
-                    pr = plane_ref<ODD>(g, b.rin, b.rout, x);
-                    if (kStage) {
-                        const float sc = ST == kH16 ? p.hs_inv : 1.f;
-                        StageT<ST> raw[Q];
-                        staged_gather<L, ST>(b.f, P, nb, n, stg, base, raw);
-#pragma unroll
-                        for (int i = 0; i < Q; ++i) f[i] = rel_pop<L, ODD>(sc * pop_float<ST>(raw[i]), i, nb, pr);
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < Q; ++i)
-                            f[i] = rel_pop<L, ODD>(gather<L, ST, ODD>(b.f, P, nb, n, i, b.Min, p, pr), i, nb, pr);
-                    }
+    if (LBM && active) {
+        // a boundary node with a fluid interior neighbour is advanced by that neighbour
+        do_flow = !(edge && ((x == 0 && nb.fl[1]) || (x == g.nx - 1 && nb.fl[2])));
+        if (kRefs<ST>) pr = plane_ref<ST == kMomR ? 0 : ODD>(g, b.rin, b.rout, x);
+        if (!kPlain<ST>) {
+            // The emitters' moments in groups whose loads are issued together
+            // (the node's own where the emitter is solid), then used; one at a
+            // time each load waited for its data before the next was issued.
+            // Fused: the node and its faces first, shared with the ions, then
+            // the edge directions in groups of 6 (512^3 electrode: 1.60 ms;
+            // groups of 4 1.66, of 12 1.61 and, with plane references, 2.02
+            // against 1.84); flow only: groups of 10 (1.05 ms; all 18 at once
+            // 1.10, groups of 6 1.09).
+            DevSums<ST> dsums;
+            auto eval = [&](int i, float4 m) {
+                const float gi = emitter_g<L, ST>(i, i != 0 && nb.fl[L::opp[i]], m, p, pr);
+                if constexpr (!kMoments<ST>) {
+                    const float dev = gather_raw<L, ST, ODD>(b.f, P, nb, n, i) * p.hs_inv;
+                    f[i] = fmaf(L::w[i], gi, dev);
+                    add_plain<L>(dsums, i, dev);
                 }
+                return gi;
+            };
+            auto use = [&](int i, float4 m, float4 mo) {  // directions i (odd) and i + 1
+                static_assert(L::opp[1] == 2 && L::opp[Q - 2] == Q - 1, "opposite directions are neighbours");
+                const float gi = eval(i, m);
+                add_pair<L>(sums, i, gi, eval(i + 1, mo));
+            };
+            auto load = [&](int i) { return ldu(b.Min, (uint32_t)(i == 0 ? n : nb.n[L::opp[i]])); };
+            constexpr int kG = NP ? 6 : 10, i1 = NP ? F + 1 : 1;
+            if (NP) {
+                float4 mg[F + 1];
+#pragma unroll
+                for (int i = 0; i <= F; ++i) mg[i] = load(i);
+                keep_order();
+                if (jm) {
+                    auto rho_of = [&](int k, float mx) {  // face k's emitter (k < 0: the node)
+                        if (ST != kMomR) return 1.f + mx;
+                        const float d = k < 0 || k > 1 || !nb.fl[k + 1] ? pr.dIn[1] : pr.dIn[k == 0 ? 0 : 2];
+                        return 1.f + (pr.rout + d) + mx;
+                    };
+                    const float r = rho_of(-1, mg[0].x);
+                    jP[0] = r * mg[0].y;
+                    jP[1] = r * mg[0].z;
+                    jP[2] = D == 3 ? r * mg[0].w : 0.f;
+#pragma unroll
+                    for (int k = 0; k < F; ++k) {
+                        const float4 m = mg[L::opp[k + 1]];
+                        jn[k] = rho_of(k, m.x) * (k < 2 ? m.y : (k < 4 ? m.z : m.w));
+                    }
+                } else if (!kEarlyJ) {
+                    jP[0] = ldu(b.jin, (uint32_t)n);
+                    jP[1] = ldu(b.jin + P, (uint32_t)n);
+                    jP[2] = D == 3 ? ldu(b.jin + 2 * (size_t)P, (uint32_t)n) : 0.f;
+#pragma unroll
+                    for (int k = 0; k < F; ++k)
+                        jn[k] = ldu(b.jin + (size_t)(k >> 1) * P, (uint32_t)nb.n[k + 1]);
+                }
+                add_rest<L>(sums, eval(0, mg[0]));
+#pragma unroll
+                for (int i = 1; i < F; i += 2) use(i, mg[i], mg[i + 1]);
+            }
+#pragma unroll
+            for (int i0 = i1; i0 < Q; i0 += kG) {
+                float4 mg[kG];
+#pragma unroll
+                for (int u = 0; u < kG; ++u)
+                    if (i0 + u < Q) mg[u] = load(i0 + u);
+                float4 m0 = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (!NP && i0 == i1) m0 = load(0);
+                keep_order();
+                if (!NP && i0 == i1) add_rest<L>(sums, eval(0, m0));
+#pragma unroll
+                for (int u = 0; u < kG; u += 2)
+                    if (i0 + u < Q) use(i0 + u, mg[u], mg[u + 1]);
+            }
+            dsums.add_to(sums);
+        } else if (do_flow) {
+            if (kStage) {
+                const float sc = ST == kH16 ? p.hs_inv : 1.f;
+                StageT<ST> raw[Q];
+                staged_gather<L, ST>(b.f, P, nb, n, stg, base, raw);
+#pragma unroll
+                for (int i = 0; i < Q; ++i) f[i] = rel_pop<L, ODD>(sc * pop_float<ST>(raw[i]), i, nb, pr);
+            } else {
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    f[i] = rel_pop<L, ODD>(gather<L, ST, ODD>(b.f, P, nb, n, i, b.Min, p, pr), i, nb, pr);
             }
         }
     }
 
     // the ions: face fluxes of the explicit finite-volume update
-    {
-        if (NP && active) {
-            const float cP[2] = {ec[0], ec[1]};
-            float jP[3];
-            const bool jm = !kPlain<ST> && (b.flags & kJFromM);
-            if (jm) {
-                const float4 m = have_m ? mown : ldu(b.Min, (uint32_t)n);
-                const float r = ST == kMomR ? 1.f + (pr.rout + pr.dIn[1]) + m.x : 1.f + m.x;
-                jP[0] = r * m.y;
-                jP[1] = r * m.z;
-                jP[2] = r * m.w;
-            } else if (kEarlyJ) {
-                jP[0] = ej[0];
-                jP[1] = ej[1];
-                jP[2] = ej[2];
-            } else {
-                jP[0] = ldu(b.jin, (uint32_t)n);
-                jP[1] = ldu(b.jin + P, (uint32_t)n);
-                jP[2] = D == 3 ? ldu(b.jin + 2 * (size_t)P, (uint32_t)n) : 0.f;
-            }
-            const float psiP = p.psi ? ldu(p.psi, (uint32_t)n) : 0.f;
-            // per species: 2/D, and (z D)/2 so that half the drift is hw = u/2 - (z D/2) dpsi
-            const float invD2[2] = {2.f * p.invD[0], 2.f * p.invD[1]};
-            const float hzD[2] = {0.5f * p.z[0] * p.D[0], 0.5f * p.z[1] * p.D[1]};
-            float out[2] = {0.f, 0.f}, fa[2] = {0.f, 0.f}, fi[2] = {0.f, 0.f}, fo[2] = {0.f, 0.f};
+    if (NP && active) {
+        IonFlux fx;
+        bool on[F];  // faces to fluid cells
+        if (g.periodic_x && p.npx != kNpxPeriodic) {  // a periodic lattice whose ions have ends
+            if (!coords) unpack_xyz(g, ldu(g.fluid, (uint32_t)n), x, y, z);
+            end[0] = x == g.nx - 1;
+            end[1] = x == 0;
+        }
+        // the adsorbing faces: not fluid, no end, and not inert
 #pragma unroll
-            for (int k = 0; k < 2 * D; ++k) {
-                const int i = k + 1;
-                const int axis = k >> 1;
-                const int sgi = (k & 1) ? -1 : 1;
-                const float sg = (float)sgi;
-                const bool xb = axis == 0 && (x + sgi < 0 || x + sgi >= g.nx);
-                if (xb && p.npx != kNpxPeriodic) {
-                    if (p.npx == kNpxClosed) continue;
-                    const float dpsi = p.psi ? 0.f : -sg * p.dpsi_dx;
-                    if (sgi < 0) {  // inlet face: ghost at c0, inflow u_in
+        for (int k = 0; k < F; ++k) {
+            const bool e = k < 2 && end[k & 1];
+            fx.ads += nb.fl[k + 1] || e ? 0.f : 1.f;
+            on[k] = nb.fl[k + 1] && !e;
+        }
+        if (inert) {  // rare
+            if (!coords) unpack_xyz(g, ldu(g.fluid, (uint32_t)n), x, y, z);
+            int m[F];
 #pragma unroll
-                        for (int s = 0; s < 2; ++s) {
-                            const float hw = -0.5f * p.u_in - hzD[s] * dpsi;
-                            const float F = sg_flux(p.D[s], invD2[s], hw, cP[s], p.c0);
-                            out[s] += F;
-                            fi[s] -= F;
-                        }
-                    } else {  // outlet face
+            for (int k = 0; k < F; ++k) m[k] = nb_map<L>(g, x, y, z, k + 1, g.periodic_x);
 #pragma unroll
-                        for (int s = 0; s < 2; ++s) {
-                            const float hw = 0.5f * jP[0] - hzD[s] * dpsi;
-                            float F;
-                            if (p.npx == kNpxDirichlet) {
-                                F = sg_flux(p.D[s], invD2[s], hw, cP[s], p.c_out);
-                            } else {  // open: drift carries C_P out, or feed c0 in
-                                const float w = 2.f * hw;
-                                F = fmaxf(w, 0.f) * cP[s] + fminf(w, 0.f) * p.c0;
-                            }
-                            out[s] += F;
-                            fo[s] += F;
-                        }
-                    }
-                    continue;
+            for (int k = 0; k < F; ++k) fx.ads -= m[k] == kInert && !(k < 2 && end[k & 1]) ? 1.f : 0.f;
+        }
+        float psiP = 0.f;
+        if (any) {
+            if (psi) {
+                psiP = ldu(p.psi, (uint32_t)n);
+                if (!kEarlyPsi) {
+#pragma unroll
+                    for (int k = 0; k < F; ++k) psin[k] = ldu(p.psi, (uint32_t)nb.n[k + 1]);
                 }
-                int m = nb[i];
-                const bool early = kEarly && !xb;  // the loaded neighbour (not a periodic re-lookup)
-                if (xb) m = nb_map<L>(g, x, y, z, i, true);  // periodic ions, open flow
-                if (m == kElectrode) {  // adsorbing face, Eq. (6)
-#pragma unroll
-                    for (int s = 0; s < 2; ++s) {
-                        const float F = p.keff[s] * cP[s];
-                        out[s] += F;
-                        fa[s] += F;
-                    }
-                } else if (m >= 0) {
-                    float jN;
-                    if (jm) {
-                        const float4 mm = (have_m && !xb) ? mface[k] : ldu(b.Min, (uint32_t)m);
-                        float r = 1.f + mm.x;
-                        if (ST == kMomR)  // the neighbour's plane (a periodic re-lookup: the other end's)
-                            r = 1.f + (xb ? ldu(b.rin, (uint32_t)(x + sgi < 0 ? g.nx - 1 : 0))
-                                          : pr.rout + pr.dIn[axis == 0 ? (sgi > 0 ? 0 : 2) : 1]) + mm.x;
-                        jN = r * (axis == 0 ? mm.y : (axis == 1 ? mm.z : mm.w));
-                    } else {
-                        jN = (early && kEarlyJ) ? ejn[k] : ldu(b.jin + (size_t)axis * P, (uint32_t)m);
-                    }
-                    // half the face-normal drift: advection by the mean flux of the
-                    // two cells, migration down the potential difference
-                    const float hun = 0.25f * (jP[axis] + jN) * sg;
-                    const bool mig = p.psi || axis == 0;  // the ramp has no y/z gradient
-                    const float dpsi = p.psi ? (kEarlyPsi && early ? epsi[k] : ldu(p.psi, (uint32_t)m)) - psiP
-                                             : -sg * p.dpsi_dx;
-#pragma unroll
-                    for (int s = 0; s < 2; ++s) {
-                        const float hw = mig ? hun - hzD[s] * dpsi : hun;
-                        out[s] += sg_flux(p.D[s], invD2[s], hw, cP[s],
-                                          early ? ecn[k][s] : ldu(b.Cin + (size_t)s * P, (uint32_t)m));
-                    }
-                }
-                // inert wall: no flux
             }
-            // forward Euler into value + remainder (see lo_encode)
-            float e0, e1;
-            stu(b.Cout, (uint32_t)n, two_sum(cP[0], lo_decode(__low2half(elo)) - p.dt * out[0], e0));
-            stu(b.Cout + P, (uint32_t)n, two_sum(cP[1], lo_decode(__high2half(elo)) - p.dt * out[1], e1));
-            stu(b.Clout, (uint32_t)n, __halves2half2(lo_encode(e0), lo_encode(e1)));
-            acc[0] = p.dt * fa[0];
-            acc[1] = p.dt * fa[1];
-            acc[2] = p.dt * fi[0];
-            acc[3] = p.dt * fi[1];
-            acc[4] = p.dt * fo[0];
-            acc[5] = p.dt * fo[1];
+            ion_faces_any<L>(p, psi, on, cP, jP, psiP, cn, jn, psin, fx);
+        } else if (!ion_faces<L>(p, on, cP, jP, cn, jn, fx)) {  // rare
+            if (!coords) unpack_xyz(g, ldu(g.fluid, (uint32_t)n), x, y, z);
+            ion_faces_wide<L, ST>(g, p, b, x, y, z, jm, end, cP[0], cP[1], jP[0], jP[1], jP[2], fx);
+        }
+        at_end = end[0] || end[1];
+        if (at_end) {  // (not both: nx >= 4)
+            if (!coords) unpack_xyz(g, ldu(g.fluid, (uint32_t)n), x, y, z);
+            ion_end_face<L, ST>(g, p, b, end[0] ? 1 : -1, x, y, z, jm, psi, cP[0], cP[1], jP[0], psiP, fx);
+        }
+        const float fa[2] = {fx.ads * (p.keff[0] * cP[0]), fx.ads * (p.keff[1] * cP[1])};
+        // forward Euler into value + remainder (see lo_encode)
+        float e0, e1;
+        const float c0 = two_sum(cP[0], lo_decode(__low2half(elo)) - p.dt * (fx.out[0] + fa[0]), e0);
+        const float c1 = two_sum(cP[1], lo_decode(__high2half(elo)) - p.dt * (fx.out[1] + fa[1]), e1);
+        stu(b.Cout, (uint32_t)n, make_float2(c0, c1));
+        stu(b.Clout, (uint32_t)n, __halves2half2(lo_encode(e0), lo_encode(e1)));
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            acc[s] = p.dt * fa[s];
+            acc[2 + s] = p.dt * fx.fi[s];
+            acc[4 + s] = p.dt * fx.fo[s];
         }
     }
 
     // the flow: collide and stream (and the residual terms on request)
     if (LBM && do_flow) {
-        lbm_node<L, ST, ODD, NP, kStage>(p, b, P, n, nb, f, pr, res, stg, base,
-                                         !(nee && (x == 0 || x == g.nx - 1)));
-        const bool inl = edge && x == 1 && nb[2] >= 0;
-        const bool outl = edge && x == g.nx - 2 && nb[1] >= 0;
+        if constexpr (kMoments<ST>)
+            moment_node<L>(b, n, sums.d, sums.jx, sums.jy, sums.jz, pr.rout, res);
+        else
+            lbm_node<L, ST, ODD, NP, kStage>(p, b, P, n, nb, f, pr, res, kPlain<ST> ? nullptr : &sums, stg, base,
+                                             !(nee && (x == 0 || x == g.nx - 1)));
+        const bool inl = edge && x == 1 && nb.fl[2];
+        const bool outl = edge && x == g.nx - 2 && nb.fl[1];
         if (inl || outl) {
-            const int bn = inl ? nb[2] : nb[1];
+            // the boundary node's moments are the target equilibrium's: the
+            // extrapolated non-equilibrium part carries none
+            const int bn = inl ? nb.n[2] : nb.n[1];
             const int xb = inl ? 0 : g.nx - 1;
-            int nbb[Q];
-            nbb[0] = bn;
-#pragma unroll
-            for (int i = 1; i < Q; ++i) nbb[i] = nb_map<L>(g, xb, y, z, i, false);  // rare path
-            float fb[Q];
             PlaneRef pb{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
             if (kRefs<ST>) pb = plane_ref<ODD>(g, b.rin, b.rout, xb);
-            nee_populations<L>(p, inl, f, fb, pr.rout, pb.rout);
-            lbm_node<L, ST, ODD, NP, kStage>(p, b, P, bn, nbb, fb, pb, res, stg, base, false);
+            MomSums sb;
+            if constexpr (!kPlain<ST>) sb = nee_moments(p, inl, sums, pr.rout, pb.rout);
+            if constexpr (kMoments<ST>) {
+                moment_node<L>(b, bn, sb.d, sb.jx, sb.jy, sb.jz, pb.rout, res);
+            } else {
+                Nbrs<L> nbb;
+                nbb.n[0] = bn;
+                nbb.fl[0] = true;
+#pragma unroll
+                for (int i = 1; i < Q; ++i) set_nbr<L>(nbb, i, nb_map<L>(g, xb, y, z, i, false), bn);  // rare path
+                float fb[Q];
+                nee_populations<L>(p, inl, f, fb, pr.rout, pb.rout);
+                lbm_node<L, ST, ODD, NP, kStage>(p, b, P, bn, nbb, fb, pb, res, kPlain<ST> ? nullptr : &sb, stg, base,
+                                                 false);
+            }
         }
     }
     if (kStage) {
@@ -566,14 +738,13 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 const int r = L::opp[q];
-                const bool fl = q != 0 && nb[r] >= 0;
-                const int c = fl ? nb[r] : n;
+                const bool fl = q != 0 && nb.fl[r];
+                const int c = q == 0 ? n : nb.n[r];
                 const int xc = fl ? x - L::ex[q] : x;
                 if ((uint32_t)(c - base) < (uint32_t)kTile && !(nee && (xc == 0 || xc == g.nx - 1)))
                     *pop_at<Q, StageT<ST>>(b.f, q, n) = v[q];
             }
         }
-        if (BATCH) __syncthreads();  // a next tile's loads would reuse the stage
     }
     if (LBM && (b.flags & kResid)) {
         double s[2];
@@ -585,17 +756,18 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
         __syncthreads();
     }
 
-    if (NP) tile_accumulate<6>(acc, sm, b.acc + (size_t)tile * 8);
+    if (NP) tile_accumulate(acc, at_end, sm, b.acc + (size_t)tile * 8);
 }
 
-template <class L, int ST, int ODD, int LBM, int NP, int STG>
+template <class L, int ST, int ODD, int LBM, int NP, int STG, int PSI>
 __global__ __launch_bounds__(kTile) void step_kernel(Grid g, Phys p, Bufs b)
 {
-    __shared__ double sm[(kTile / 64) * 6];
+    __shared__ double sm[kTileSums];
     __shared__ StageT<ST> stage[STG ? kStageElems<L> : 1];
     extern __shared__ double lds_pad[];  // sized at launch: occupancy cap only
     (void)lds_pad;
-    step_tile<L, ST, ODD, LBM, NP, 0, STG>(g, p, b, block_tile(g), sm, stage);
+    if (NP) tile_sums_init(sm);
+    step_tile<L, ST, ODD, LBM, NP, PSI, STG>(g, p, b, block_tile(g), sm, stage);
 }
 
 // A batch member's descriptor is read from memory, and a pointer read from
@@ -615,6 +787,7 @@ __device__ __forceinline__ void load_inst(const BatchInst *inst, int k, Grid &g,
     g.map = c.g.map;
     g.sched = c.g.sched;
     g.nbr = c.g.nbr;
+    g.rows = c.g.rows;
     p.psi = c.p.psi;
     b.f = c.b.f;
     b.f2 = c.b.f2;
@@ -643,9 +816,10 @@ template <class L, int ST, int ODD, int LBM, int NP>
 __global__ __launch_bounds__(kTile) void batch_kernel(const BatchInst *__restrict__ inst,
                                                       const int2 *__restrict__ tiles, int ntiles)
 {
-    __shared__ double sm[(kTile / 64) * 6];
+    __shared__ double sm[kTileSums];
     extern __shared__ double lds_pad[];
     (void)lds_pad;
+    if (NP) tile_sums_init(sm);
     // workgroups are dealt round-robin over the 8 XCDs: each XCD takes one
     // contiguous eighth of the list, so neighbouring tiles share its L2
     const int G = (int)gridDim.x, w = (int)blockIdx.x;
@@ -663,7 +837,8 @@ __global__ __launch_bounds__(kTile) void batch_kernel(const BatchInst *__restric
         Phys p;
         Bufs b;
         load_inst(inst, e.x, g, p, b);
-        step_tile<L, ST, ODD, LBM, NP, 1>(g, p, b, e.y, sm, nullptr);  // not staged
+        step_tile<L, ST, ODD, LBM, NP, kPsiAny>(g, p, b, e.y, sm, nullptr);  // not staged
+        if (NP && q + stride < hi) __syncthreads();  // the next tile reuses the sums
     }
 }
 
@@ -699,17 +874,28 @@ void launch_batch_t(int cls, const BatchInst *inst, const int2 *tiles, int ntile
     }
 }
 
-template <class L, int ST, int ODD, int LBM, int NP>
-void launch_t(const Grid &g, const Phys &p, const Bufs &b, hipStream_t s)
+template <class L, int ST, int ODD, int LBM, int NP, int PSI>
+void launch_psi(const Grid &g, const Phys &p, const Bufs &b, hipStream_t s)
 {
     const unsigned T = (unsigned)(g.P / kTile);
     if constexpr (kStageOdd<L, ST, ODD, LBM, NP>) {
         if (g.stage_odd) {
-            step_kernel<L, ST, ODD, LBM, NP, 1><<<T, kTile, cap_lds<L, ST, 1>(g.lds_pad), s>>>(g, p, b);
+            step_kernel<L, ST, ODD, LBM, NP, 1, PSI><<<T, kTile, cap_lds<L, ST, 1>(g.lds_pad), s>>>(g, p, b);
             return;
         }
     }
-    step_kernel<L, ST, ODD, LBM, NP, 0><<<T, kTile, (size_t)g.lds_pad, s>>>(g, p, b);
+    step_kernel<L, ST, ODD, LBM, NP, 0, PSI><<<T, kTile, (size_t)g.lds_pad, s>>>(g, p, b);
+}
+
+// A kernel of its own for ions in a potential field or a steep ramp, whose code
+// would cost the others registers.
+template <class L, int ST, int ODD, int LBM, int NP>
+void launch_t(const Grid &g, const Phys &p, const Bufs &b, hipStream_t s)
+{
+    if (NP && (p.psi || p.steep))
+        launch_psi<L, ST, ODD, LBM, NP, NP>(g, p, b, s);
+    else
+        launch_psi<L, ST, ODD, LBM, NP, 0>(g, p, b, s);
 }
 
 template <class L, int ST, int ODD>

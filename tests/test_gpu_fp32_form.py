@@ -1,6 +1,8 @@
-"""FP32 instances at tau = 1 without a body force are held as their moments
-(relative to the plane references); the population form stays for every other
-one and for snapshots that hold populations. Both against the FP64 oracle and
+"""The forms a state is held in, and the kernels each takes: FP32 instances at
+tau = 1 without a body force as moments (relative to the plane references), FP32
+populations elsewhere and for snapshots that hold populations; neighbours
+through the lattice's rows, with inert solids, ragged bricks and a wrap; ion
+drifts inside and beyond the flux series' range. Against the FP64 oracle and
 against each other."""
 import numpy as np
 import pytest
@@ -71,3 +73,95 @@ def test_fused_ions_after_renewed_references(npx):
     s.np_step(11)  # frozen: the flux of the moments
     assert o.np_steps(11) == 0
     assert np.abs(s.concentration() - o.conc()).max() <= 1e-4
+
+
+def test_snapshot_with_the_species_in_planes():
+    # a snapshot written when the two species were two planes (bit 4 clear)
+    g, p = case()
+    s = Solver(g, p)
+    s.np_step(7)
+    want = s.concentration()
+    blob = bytearray(s.snapshot())
+    P_ = (s.n_fluid + 255) // 256 * 256
+    at = 72 + (19 * 4 + 2 * 3 * 4 + 4 * 4) * P_  # behind the populations, the flux pair and the previous velocity
+    for _ in range(2):
+        pairs = np.frombuffer(blob, np.float32, 2 * P_, at).reshape(P_, 2)
+        blob[at:at + 8 * P_] = np.ascontiguousarray(pairs.T).tobytes()
+        at += 8 * P_
+    blob[RSTATE] &= ~16 & 0xFF
+    t = Solver(g, p)
+    t.restore(bytes(blob))
+    assert np.array_equal(t.concentration(), want)
+    s.np_step(3)
+    t.np_step(3)
+    assert np.array_equal(t.concentration(), s.concentration())
+
+
+@pytest.mark.parametrize("streaming", [L.STREAM_AA, L.STREAM_PULL], ids=["aa", "pull"])
+@pytest.mark.parametrize("precision", [L.FP32, L.FP16, L.FP16_DEV], ids=["fp32", "fp16", "fp16dev"])
+def test_population_batches_equal_members_alone(precision, streaming):
+    # tau = 0.8: the batched kernels of the population forms
+    specs = []
+    for n, seed in ((24, 3), (33, 4)):
+        g = Geometry(dim=3, nx=n, ny=n - 5, nz=n - 3, kind=L.SPHERES, porosity=0.6, r_min=3.0, r_max=5.0, seed=seed)
+        specs.append((g, Params(u_in=1e-3, dpsi_vt=10.0, tau=0.8, precision=precision, streaming=streaming)))
+    alone, both = [Solver(*sp) for sp in specs], [Solver(*sp) for sp in specs]
+    b = Batch(both)
+    for n, mode in ((9, L.MODE_FLOW), (8, L.MODE_FUSED), (5, L.MODE_IONS)):
+        b.advance(n, mode)
+        for s in alone:
+            s.flow_steps(n) if mode == L.MODE_FLOW else s.np_step(n, fused=mode == L.MODE_FUSED)
+    b.close()
+    for s, t in zip(alone, both):
+        assert np.array_equal(s.velocity(), t.velocity()) and np.array_equal(s.concentration(), t.concentration())
+        assert np.array_equal(s.adsorbed_total(), t.adsorbed_total())
+
+
+def labels(nz, ny, nx, seed, inert):
+    """Random solid voxels (0.35 of them), a share of which is inert; x ends open."""
+    r = np.random.default_rng(seed)
+    lab = (r.random((nz, ny, nx)) < 0.35).astype(np.uint8)
+    lab[(lab == 1) & (r.random(lab.shape) < inert)] = 2
+    lab[:, :, :2] = lab[:, :, -2:] = 0
+    return lab
+
+
+@pytest.mark.parametrize("nbr_list", [0, 1])
+@pytest.mark.parametrize("shape", [(17, 15, 18), (16, 33, 47), (1, 20, 33), (5, 3, 16)])
+@pytest.mark.parametrize("drive", [L.INLET_OUTLET, L.BODY_FORCE], ids=["inout", "force"])
+def test_rows_on_ragged_lattices_with_inert_solids(shape, drive, nbr_list):
+    nz, ny, nx = shape
+    g = Geometry(dim=2 if nz == 1 else 3, nx=nx, ny=ny, nz=nz, kind=L.USER_LABELS, user_labels=labels(*shape, 5, 0.4))
+    pk = dict(drive=drive, body_force=(1e-5, 0.0, 0.0), u_in=0.0, Ka=2e-3) if drive == L.BODY_FORCE else dict(u_in=1e-3)
+    for npx in (L.NPX_INLET_OUTLET, L.NPX_PERIODIC, L.NPX_CLOSED):
+        p = Params(dpsi_vt=4.0, np_x_bc=npx, **pk)
+        s, o = Solver(g, p), oracle_solver(g, p)
+        s.set_tuning(nbr_list=nbr_list)
+        s.flow_steps(21)
+        o.flow_steps(21)
+        for fused in (True, False):
+            s.np_step(12, fused=fused)
+            assert o.np_steps(12, fused=fused) == 0
+        assert rel_l2(s.velocity(), o.velocity()) <= 1e-5
+        assert np.abs(s.concentration() - o.conc()).max() <= 1e-5
+        a, ao = s.adsorbed_total(), o.adsorbed_total()
+        assert np.all(np.abs(a - ao) <= 1e-5 * np.abs(ao))
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("dpsi", [0.5, 0.74, 0.9, 3.0])
+def test_ion_drift_in_and_beyond_the_series_range(dpsi, fused):
+    # the ramp per cell (|Pe| of the x faces): in the series' range, near its
+    # end with a flow that takes some faces beyond it, and steep
+    n = 24
+    g = Geometry(dim=3, nx=n, ny=20, nz=18, kind=L.SPHERES, porosity=0.6, r_min=3.0, r_max=5.0, seed=2)
+    p = Params(u_in=0.02, dpsi_vt=dpsi * n, D=(0.04, 0.05))
+    s, o = Solver(g, p), oracle_solver(g, p)
+    s.flow_steps(60)
+    o.flow_steps(60)
+    s.np_step(25, fused=fused)
+    assert o.np_steps(25, fused=fused) == 0
+    assert np.abs(s.concentration() - o.conc()).max() <= 1e-5
+    m = s.mass_balance()  # solute + adsorbed + out - in is kept (FP32 fluxes, 25 steps)
+    m0 = s.n_fluid * p.c0
+    assert np.all(np.abs(m[:, 0] + m[:, 1] + m[:, 3] - m[:, 2] - m0) <= 1e-6 * m0)
