@@ -6,6 +6,7 @@
 #include "cdi_internal.h"
 #include "diag_internal.h"
 #include "geometry_internal.h"
+#include "host_copy_internal.h"
 #include "np_solve_internal.h"
 #include "geomgen.h"
 #include "pot_internal.h"
@@ -572,8 +573,7 @@ int occupancy_pad(int k, int *pad)
 
 int d2h(cdi_solver *s, void *dst, const void *src, uint64_t bytes)
 {
-    HIPCHK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
+    HIPCHK(copy_to_host(dst, src, bytes, s->stream));
     return CDI_OK;
 }
 
@@ -589,8 +589,7 @@ int h2d(cdi_solver *s, void *dst, const void *src, uint64_t bytes)
 int planes_d2h(cdi_solver *s, float *host, const float *dev, int d)
 {
     HIPCHK(launch_permute(dev, s->node.xfer, s->vox.lex2int, (int)s->nf, s->P, d, 1, s->stream));
-    HIPCHK(hipMemcpyAsync(host, s->node.xfer, 4ull * s->nf * d, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
+    HIPCHK(copy_to_host(host, s->node.xfer, 4ull * s->nf * d, s->stream));
     return CDI_OK;
 }
 
@@ -970,6 +969,7 @@ int cdi_flow_init(const cdi_geometry *geom, const cdi_params *params, void *vox_
         delete s;
         return err;
     }
+    staging_user_added();
     *out = s;
     g_err[0] = 0;
     return CDI_OK;
@@ -977,6 +977,7 @@ int cdi_flow_init(const cdi_geometry *geom, const cdi_params *params, void *vox_
 
 int cdi_destroy(cdi_solver *s)
 {
+    if (s) staging_user_removed();
     delete s;
     return CDI_OK;
 }
