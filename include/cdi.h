@@ -403,10 +403,11 @@ int cdi_batch_autotune(cdi_batch *b, int32_t steps, const int32_t *modes, int32_
  * x-end face is Dirichlet (value psi_x), field-free, or periodic (both ends).
  * The symmetric positive definite system is solved on the GPU by mixed-
  * precision iterative refinement: each round forms the FP64 residual of the
- * FP64 iterate and solves for the correction by Jacobi-preconditioned
- * conjugate gradients on FP32 vectors (sums in FP64), until the FP64
- * residual meets tol; a round that gains less than 4x hands over to the same
- * CG on FP64 vectors (fp64 = 1: that CG alone). The result (stored as FP32) becomes the potential of
+ * FP64 iterate and solves for the correction by conjugate gradients on FP32
+ * vectors (sums in FP64; preconditioned by Chebyshev sweeps within blocks of
+ * 1024 nodes), until the FP64 residual meets tol; a round that gains less than
+ * 4x hands over to Jacobi-preconditioned CG on FP64 vectors (fp64 = 1: that CG
+ * alone). The result (stored as FP32) becomes the potential of
  * every later ion step. */
 enum { CDI_PSIX_DIRICHLET = 0, CDI_PSIX_NEUMANN = 1, CDI_PSIX_PERIODIC = 2 };
 
@@ -430,7 +431,7 @@ typedef struct {
     int32_t fp64_iterations; /* of the iterations, those on FP64 vectors */
 } cdi_potential_result;
 
-/* Device workspace of the solve (5 FP64 and 5 FP32 vectors and a byte per node, plus
+/* Device workspace of the solve (5 FP64 and 4 FP32 vectors and a byte per node, plus
  * per-workgroup sums); needed only during the call. The solve reads face
  * neighbours from the solver's neighbour list when the potential's x ends
  * are periodic exactly when the lattice's are, else through the voxel map;

@@ -1205,7 +1205,7 @@ namespace {
 
 struct PotLayout {
     double *x, *r, *p, *p2, *q, *part, *state;
-    float *xf, *rf, *pf, *pf2, *qf;
+    float *xf, *rf, *pf, *qf;
     uint8_t *dg;
     uint64_t bytes;
 };
@@ -1222,7 +1222,6 @@ PotLayout pot_layout(void *ws, int P)
     L.xf = c.take<float>(4ull * P);
     L.rf = c.take<float>(4ull * P);
     L.pf = c.take<float>(4ull * P);
-    L.pf2 = c.take<float>(4ull * P);
     L.qf = c.take<float>(4ull * P);
     L.dg = c.take<uint8_t>((uint64_t)P);
     L.part = c.take<double>(8ull * pot_part_doubles());
@@ -1278,7 +1277,7 @@ int solve_potential(cdi_solver *s, const cdi_potential *pc, void *ws, uint64_t w
     a.xf = W.xf;
     a.rf = W.rf;
     a.pf = W.pf;
-    a.pf2 = W.pf2;
+    a.zp = (float2 *)W.p2;  // (an FP64 direction buffer: idle while the FP32 rounds run)
     a.qf = W.qf;
     // the neighbour list (built at init, one gather round trip fewer than the
     // map lookup; measured 6% faster per iteration on the 512^3 electrode)

@@ -31,6 +31,13 @@
 // partials, by the parity of k, so no kernel overwrites a value another
 // workgroup of the same kernel may still read. After the stop every later
 // launch returns at once.
+//
+// The FP32 correction solves use a stronger preconditioner than the diagonal
+// (block_solve below) and run
+//   spmv     stop test; p_k = z_k + beta p_{k-1}, q = A p_k, partial p.q; z_k
+//            and p_{k-1} of a node lie side by side, one gather per neighbour
+//   update   x += alpha p_k; r -= alpha q; z = M r; the pair (z, p_k);
+//            partials r.z, r.r
 #include "cdi_internal.h"
 #include "device_common.h"
 #include "pot_internal.h"
@@ -46,27 +53,6 @@ enum { kRz0 = 0, kRz1 = 1, kRr = 2, kPq = 3, kBb = 4, kNd = 5, kRo = 6, kRegions
 
 // nodes per thread (tiles per pass) of the stencil and update kernels
 constexpr int kPotNodes = 2;
-
-// The vectors a CG iteration works on: FP64 (x, r, q, p, p2) or the FP32
-// set of a refinement round's correction (xf, rf, qf, pf, pf2).
-template <class T>
-struct Vecs;
-template <>
-struct Vecs<double> {
-    __device__ static double *x(const PotArgs &a) { return a.x; }
-    __device__ static double *r(const PotArgs &a) { return a.r; }
-    __device__ static double *q(const PotArgs &a) { return a.q; }
-    __device__ static double *p(const PotArgs &a) { return a.p; }
-    __device__ static double *p2(const PotArgs &a) { return a.p2; }
-};
-template <>
-struct Vecs<float> {
-    __device__ static float *x(const PotArgs &a) { return a.xf; }
-    __device__ static float *r(const PotArgs &a) { return a.rf; }
-    __device__ static float *q(const PotArgs &a) { return a.qf; }
-    __device__ static float *p(const PotArgs &a) { return a.pf; }
-    __device__ static float *p2(const PotArgs &a) { return a.pf2; }
-};
 
 // Whether the solve has stopped, read once per workgroup so that all its
 // waves take the same branch (a stop may be recorded by workgroup 0 of the
@@ -150,17 +136,75 @@ __device__ inline double new_dir(double r, int d, double p, double beta)
     return z + beta * p;
 }
 
-// The FP32 correction solves precondition with the hardware FP32 reciprocal
-// of the diagonal (one instruction instead of an FP64 division; the
-// preconditioner is diag(inv_diag_f(d))^-1, the same in every kernel that
-// applies it, so CG stays consistent) and form the direction in FP32, the
-// precision it is stored in: every copy of a node's direction, its own and
-// its neighbours', is the same FP32 number, the one stored.
+// Reciprocal of the diagonal for the FP32 correction solves (the hardware's,
+// the same in every kernel; 0 for a cell without faces).
 __device__ inline float inv_diag_f(int d) { return d > 0 ? __builtin_amdgcn_rcpf((float)d) : 0.f; }
 
-__device__ inline float new_dir_f(float r, int d, float p, float beta)
+// The preconditioner of the FP32 correction solves. M is block diagonal over
+// blocks of kBlockNodes consecutive nodes (about 16 x 16 x 10 voxels of a brick
+// at porosity 0.4); in a block it is a fixed polynomial in the block of A: z =
+// M r is the kChebSteps-th iterate of the Chebyshev iteration for D^-1 A_b z =
+// D^-1 r on the interval [kChebLow, 2] (D the diagonal), from z = 0. Symmetric,
+// and positive definite: on (0, 2), which holds the spectrum, the polynomial is
+// positive. The electrode's Dirichlet faces screen the potential over a few
+// voxels, so the coupling between blocks matters little: CG takes 0.40 of the
+// diagonal's iterations (112 -> 45 on a 96^3 electrode at porosity 0.4, 176 ->
+// 70 at 0.65; blocks of 256 nodes: 62 and 106, of 2048: 42 and 65; four steps
+// on [0.2, 2]: 50 and 80). The sweeps run on the block in LDS: 5 sweeps cost
+// less than a tenth of the iteration's memory time.
+constexpr int kBlockTiles = 4, kBlockNodes = kBlockTiles * kTile;
+constexpr int kChebSteps = 6;
+constexpr double kChebLow = 0.1;
+
+struct ChebCoef {
+    float first, d[kChebSteps], r[kChebSteps];
+};
+constexpr ChebCoef cheb_coef()
 {
-    return __builtin_fmaf(beta, p, __fmul_rn(r, inv_diag_f(d)));
+    ChebCoef c{};
+    const double th = (2.0 + kChebLow) / 2, de = (2.0 - kChebLow) / 2, s = th / de;
+    double rho = 1 / s;
+    c.first = (float)(1 / th);
+    for (int k = 1; k < kChebSteps; ++k) {
+        const double rn = 1 / (2 * s - rho);
+        c.d[k] = (float)(rn * rho);
+        c.r[k] = (float)(2 * rn / de);
+        rho = rn;
+    }
+    return c;
+}
+
+// z = M r for this thread's kBlockTiles nodes of a block: lm their face
+// neighbours' places in the block (kBlockNodes: none, a slot that stays 0),
+// dinv their reciprocal diagonals. zs: two buffers of kBlockNodes + 1.
+template <int F>
+__device__ __forceinline__ void block_solve(const float (&r)[kBlockTiles], const float (&dinv)[kBlockTiles],
+                                            const uint16_t (&lm)[kBlockTiles][F], float (*zs)[kBlockNodes + 1],
+                                            float (&z)[kBlockTiles])
+{
+    constexpr ChebCoef c = cheb_coef();
+    float d[kBlockTiles];
+#pragma unroll
+    for (int j = 0; j < kBlockTiles; ++j) {
+        d[j] = c.first * (r[j] * dinv[j]);
+        z[j] = d[j];
+    }
+#pragma unroll
+    for (int k = 1; k < kChebSteps; ++k) {
+        float *const b = zs[k & 1];
+#pragma unroll
+        for (int j = 0; j < kBlockTiles; ++j) b[j * kTile + threadIdx.x] = z[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kBlockTiles; ++j) {
+            float s = r[j];
+#pragma unroll
+            for (int f = 0; f < F; ++f) s += b[lm[j][f]];
+            d[j] = fmaf(c.r[k], fmaf(dinv[j], s, -z[j]), c.d[k] * d[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < kBlockTiles; ++j) z[j] = dinv[j] > 0.f ? z[j] + d[j] : 0.f;
+    }
 }
 
 // Stop test on |r_k|^2 (the r.r partials of the last axpy); the same
@@ -185,10 +229,10 @@ __device__ inline bool stop_test(const PotArgs &a, int k, double *sm)
 // of its fluid neighbours, which it forms from their r, diagonal and old p.
 // NN nodes per thread (tiles t and t + 1 of the range), all loads issued
 // before any arithmetic.
-template <class L, int NBR, int NN, class T>
+template <class L, int NBR, int NN>
 __global__ __launch_bounds__(kTile) void pot_dirspmv_kernel(PotArgs a, int k)
 {
-    using V = Vecs<T>;
+    using T = double;
     constexpr int F = 2 * L::D;
     __shared__ double sm[kTile / 64];
     __shared__ int stop;
@@ -200,9 +244,9 @@ __global__ __launch_bounds__(kTile) void pot_dirspmv_kernel(PotArgs a, int k)
         beta = region_sum(a.part + (k & 1 ? kRz1 : kRz0) * G, G, sm) /
                region_sum(a.part + (k & 1 ? kRz0 : kRz1) * G, G, sm);
     }
-    const T *pold = k & 1 ? V::p2(a) : V::p(a);
-    T *pnew = k & 1 ? V::p(a) : V::p2(a);
-    const T *rv = V::r(a);
+    const T *pold = k & 1 ? a.p2 : a.p;
+    T *pnew = k & 1 ? a.p : a.p2;
+    const T *rv = a.r;
     int t0, t1;
     tile_range(a.g.P / kTile, t0, t1);
     double pq = 0;
@@ -241,28 +285,14 @@ __global__ __launch_bounds__(kTile) void pot_dirspmv_kernel(PotArgs a, int k)
 #pragma unroll
         for (int j = 0; j < NN; ++j) {
             if (!act[j]) continue;
-            T pt;
-            double q;
-            if constexpr (sizeof(T) == 4) {
-                const float bf = (float)beta;
-                pt = new_dir_f(r0[j], d0[j], p0[j], bf);
-                q = (double)d0[j] * (double)pt;  // A p accumulated in FP64 (it cancels)
+            const double pn = new_dir(r0[j], d0[j], p0[j], beta);
+            double q = d0[j] * pn;
 #pragma unroll
-                for (int f = 0; f < F; ++f)
-                    if (m[j][f] >= 0) q -= (double)new_dir_f(rm[j][f], dm[j][f], pm[j][f], bf);
-            } else {
-                const double pn = new_dir(r0[j], d0[j], p0[j], beta);
-                q = d0[j] * pn;
-#pragma unroll
-                for (int f = 0; f < F; ++f)
-                    if (m[j][f] >= 0) q -= new_dir(rm[j][f], dm[j][f], pm[j][f], beta);
-                pt = pn;
-            }
-            // stored in T; the partial is formed from the stored values
-            const T qt = (T)q;
-            stu(pnew, (uint32_t)n[j], pt);
-            stu(V::q(a), (uint32_t)n[j], qt);
-            pq += (double)pt * (double)qt;
+            for (int f = 0; f < F; ++f)
+                if (m[j][f] >= 0) q -= new_dir(rm[j][f], dm[j][f], pm[j][f], beta);
+            stu(pnew, (uint32_t)n[j], pn);
+            stu(a.q, (uint32_t)n[j], q);
+            pq += pn * q;
         }
     }
     const double s = wg_sum(pq, sm);
@@ -271,10 +301,9 @@ __global__ __launch_bounds__(kTile) void pot_dirspmv_kernel(PotArgs a, int k)
 
 // Iteration k, second half: alpha = rz_k / (p_k . q); x += alpha p_k;
 // r -= alpha q; partials rz_{k+1} (into the other r.z slot) and |r_{k+1}|^2.
-template <class T>
 __global__ __launch_bounds__(kTile) void pot_axpy_kernel(PotArgs a, int k)
 {
-    using V = Vecs<T>;
+    using T = double;
     __shared__ double sm[kTile / 64];
     __shared__ int stop;
     if (stopped(a.state, &stop)) return;
@@ -286,9 +315,9 @@ __global__ __launch_bounds__(kTile) void pot_axpy_kernel(PotArgs a, int k)
         return;
     }
     const double alpha = rz / pq;
-    const T *pk = k & 1 ? V::p(a) : V::p2(a);
-    T *xv = V::x(a), *rv = V::r(a);
-    const T *qv = V::q(a);
+    const T *pk = k & 1 ? a.p : a.p2;
+    T *xv = a.x, *rv = a.r;
+    const T *qv = a.q;
     int t0, t1;
     tile_range(a.g.P / kTile, t0, t1);
     double rz1 = 0, rr = 0;
@@ -313,15 +342,10 @@ __global__ __launch_bounds__(kTile) void pot_axpy_kernel(PotArgs a, int k)
 #pragma unroll
         for (int j = 0; j < kPotNodes; ++j) {
             if (!act[j]) continue;
-            stu(xv, (uint32_t)n[j], (T)(xo[j] + alpha * (double)pv[j]));
-            const T rt = (T)(ro[j] - alpha * (double)qv_[j]);
-            stu(rv, (uint32_t)n[j], rt);
-            const double rn = rt;
-            double zn;
-            if constexpr (sizeof(T) == 4)
-                zn = __fmul_rn((float)rt, inv_diag_f(dv[j]));  // the z the stencil kernel forms
-            else
-                zn = dv[j] > 0 ? rn / dv[j] : 0.0;
+            stu(xv, (uint32_t)n[j], xo[j] + alpha * pv[j]);
+            const double rn = ro[j] - alpha * qv_[j];
+            stu(rv, (uint32_t)n[j], rn);
+            const double zn = dv[j] > 0 ? rn / dv[j] : 0.0;
             rz1 += rn * zn;
             rr += rn * rn;
         }
@@ -330,6 +354,160 @@ __global__ __launch_bounds__(kTile) void pot_axpy_kernel(PotArgs a, int k)
     if (threadIdx.x == 0) {
         a.part[(k & 1 ? kRz0 : kRz1) * G + blockIdx.x] = s_rz;
         a.part[kRr * G + blockIdx.x] = s_rr;
+    }
+}
+
+// FP32 correction, iteration k, first half: stop test on r_k; beta as above;
+// p_k = z_k + beta p_{k-1} for the node and, from their pairs, its neighbours;
+// q = A p_k (accumulated in FP64: it cancels); partial p_k . q. Every copy of a
+// node's direction is the FP32 number stored. Bound by the number of gathers:
+// the pairs make it 6 per node where r, the diagonal and the old p took 18.
+template <class L, int NBR, int NN>
+__global__ __launch_bounds__(kTile) void pot_spmv32_kernel(PotArgs a, int k)
+{
+    constexpr int F = 2 * L::D;
+    __shared__ double sm[kTile / 64];
+    __shared__ int stop;
+    if (stopped(a.state, &stop)) return;
+    const int G = gridDim.x;
+    float beta = 0.f;
+    if (k > 0) {
+        if (stop_test(a, k, sm)) return;
+        beta = (float)(region_sum(a.part + (k & 1 ? kRz1 : kRz0) * G, G, sm) /
+                       region_sum(a.part + (k & 1 ? kRz0 : kRz1) * G, G, sm));
+    }
+    const float2 *zp = a.zp;
+    int t0, t1;
+    tile_range(a.g.P / kTile, t0, t1);
+    double pq = 0;
+    for (int t = t0; t < t1; t += NN) {
+        int n[NN], m[NN][F];
+        bool act[NN];
+#pragma unroll
+        for (int j = 0; j < NN; ++j) {
+            n[j] = (t + j) * kTile + threadIdx.x;
+            act[j] = t + j < t1 && n[j] < a.g.n_f;
+            if (act[j])
+                face_maps<L, NBR>(a, n[j], m[j]);
+            else
+#pragma unroll
+                for (int f = 0; f < F; ++f) m[j][f] = kInert;
+        }
+        // every load unconditional (index 0 where there is no node or no fluid
+        // neighbour; the value is not used there)
+        float2 v0[NN], vm[NN][F];
+        int d0[NN];
+#pragma unroll
+        for (int j = 0; j < NN; ++j) {
+            const uint32_t q0 = act[j] ? (uint32_t)n[j] : 0u;
+            v0[j] = ldu(zp, q0);
+            d0[j] = act[j] ? a.dg[q0] : 0;
+#pragma unroll
+            for (int f = 0; f < F; ++f) vm[j][f] = ldu(zp, m[j][f] >= 0 ? (uint32_t)m[j][f] : 0u);
+        }
+        keep_order();
+#pragma unroll
+        for (int j = 0; j < NN; ++j) {
+            if (!act[j]) continue;
+            const float pt = fmaf(beta, v0[j].y, v0[j].x);
+            double q = (double)d0[j] * (double)pt;
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                if (m[j][f] >= 0) q -= (double)fmaf(beta, vm[j][f].y, vm[j][f].x);
+            const float qt = (float)q;  // the partial is formed from the stored values
+            stu(a.pf, (uint32_t)n[j], pt);
+            stu(a.qf, (uint32_t)n[j], qt);
+            pq += (double)pt * (double)qt;
+        }
+    }
+    const double s = wg_sum(pq, sm);
+    if (threadIdx.x == 0) a.part[kPq * G + blockIdx.x] = s;
+}
+
+// FP32 correction, iteration k, second half (START: before iteration 0, z and
+// the pairs of the start's r): alpha = rz_k / (p_k . q); x += alpha p_k; r -=
+// alpha q; z = M r (block_solve); partials rz_{k+1} and |r_{k+1}|^2.
+template <class L, int NBR, int START>
+__global__ __launch_bounds__(kTile) void pot_update32_kernel(PotArgs a, int k)
+{
+    constexpr int F = 2 * L::D, NB = kBlockTiles;
+    __shared__ double sm[kTile / 64];
+    __shared__ int stop;
+    __shared__ float zs[2][kBlockNodes + 1];
+    if (stopped(a.state, &stop)) return;
+    const int G = gridDim.x;
+    double alpha = 0;
+    if (!START) {
+        const double rz = region_sum(a.part + (k & 1 ? kRz1 : kRz0) * G, G, sm);
+        const double pq = region_sum(a.part + kPq * G, G, sm);
+        if (!(pq > 0.0) || !isfinite(rz / pq)) {  // breakdown: A p has no positive energy
+            if (blockIdx.x == 0 && threadIdx.x == 0) a.state[kStDone] = kDoneBreakdown;
+            return;
+        }
+        alpha = rz / pq;
+    }
+    if (threadIdx.x < 2) zs[threadIdx.x][kBlockNodes] = 0.f;  // (ordered before use by the sweep's barrier)
+    int b0, b1;
+    tile_range((a.g.P + kBlockNodes - 1) / kBlockNodes, b0, b1);
+    double rz1 = 0, rr = 0;
+    for (int blk = b0; blk < b1; ++blk) {
+        const int base = blk * kBlockNodes;
+        int m[NB][F], dv[NB];
+        float pv[NB], qv[NB], xo[NB], r[NB], dinv[NB], z[NB];
+        uint16_t lm[NB][F];
+        bool act[NB];
+        __syncthreads();  // the sweeps of the block before may still read zs
+        // all loads issued before any store (index 0 where there is no node)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int n = base + j * kTile + (int)threadIdx.x;
+            act[j] = n < a.g.n_f;
+            if (act[j])
+                face_maps<L, NBR>(a, n, m[j]);
+            else
+#pragma unroll
+                for (int f = 0; f < F; ++f) m[j][f] = kInert;
+            const uint32_t q = act[j] ? (uint32_t)n : 0u;
+            if (!START) {
+                pv[j] = ldu(a.pf, q);
+                qv[j] = ldu(a.qf, q);
+                xo[j] = ldu(a.xf, q);
+            }
+            r[j] = ldu(a.rf, q);
+            dv[j] = a.dg[q];
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const uint32_t n = (uint32_t)(base + j * kTile + (int)threadIdx.x);
+            if (!START) {
+                const float xn = (float)(xo[j] + alpha * (double)pv[j]);
+                r[j] = (float)(r[j] - alpha * (double)qv[j]);
+                if (act[j]) {
+                    stu(a.xf, n, xn);
+                    stu(a.rf, n, r[j]);
+                }
+            }
+            r[j] = act[j] ? r[j] : 0.f;
+            dinv[j] = act[j] ? inv_diag_f(dv[j]) : 0.f;
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const uint32_t l = (uint32_t)(m[j][f] - base);  // (beyond the block for negative values too)
+                lm[j][f] = (uint16_t)(m[j][f] >= 0 && l < (uint32_t)kBlockNodes ? l : kBlockNodes);
+            }
+        }
+        block_solve<F>(r, dinv, lm, zs, z);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            if (!act[j]) continue;
+            stu(a.zp, (uint32_t)(base + j * kTile + (int)threadIdx.x), make_float2(z[j], START ? 0.f : pv[j]));
+            rz1 += (double)r[j] * (double)z[j];
+            rr += (double)r[j] * (double)r[j];
+        }
+    }
+    const double s_rz = wg_sum(rz1, sm), s_rr = wg_sum(rr, sm);
+    if (threadIdx.x == 0) {
+        a.part[(START || (k & 1) ? kRz0 : kRz1) * G + blockIdx.x] = s_rz;
+        if (!START) a.part[kRr * G + blockIdx.x] = s_rr;
     }
 }
 
@@ -366,9 +544,9 @@ __global__ __launch_bounds__(kTile) void pot_state_kernel(PotArgs a, int G, doub
 }
 
 // Refinement round: the FP64 residual r = b - A x of the current x, its
-// partial |r|^2 (kRo), and the start of an FP32 correction solve A d = r:
-// rf = r, xf = 0, p = z = rf inv_diag_f(diag), partial rf . z (kRz0). F64: instead the
-// start of FP64 CG iterations on x itself (r, p = z in FP64). Faces from the
+// partial |r|^2 (kRo), and the start of an FP32 correction solve A d = r: rf =
+// r, xf = 0 (its z and partial r . z: pot_update32_kernel's START). F64: instead
+// the start of FP64 CG iterations on x itself (r, p = z in FP64). Faces from the
 // neighbour list where there is one (NBR), the diagonal from the set-up.
 template <class L, int F64, int NBR>
 __global__ __launch_bounds__(kTile) void pot_refine_kernel(PotArgs a)
@@ -380,7 +558,7 @@ __global__ __launch_bounds__(kTile) void pot_refine_kernel(PotArgs a)
     double rz = 0, ro = 0;
     for (int t = t0; t < t1; ++t) {
         const int n = t * kTile + threadIdx.x;
-        float rf = 0.f, zf = 0.f;
+        float rf = 0.f;
         if (n < a.g.n_f) {
             int m[2 * L::D];
             face_maps<L, NBR>(a, n, m);
@@ -409,8 +587,6 @@ __global__ __launch_bounds__(kTile) void pot_refine_kernel(PotArgs a)
                 rz += r * zd;
             } else {
                 rf = (float)r;
-                zf = __fmul_rn(rf, inv_diag_f(diag));  // the z the stencil kernel forms
-                rz += (double)rf * (double)zf;
             }
         } else if (F64) {
             stu(a.r, (uint32_t)n, 0.0);
@@ -419,13 +595,12 @@ __global__ __launch_bounds__(kTile) void pot_refine_kernel(PotArgs a)
         if (!F64) {
             stu(a.rf, (uint32_t)n, rf);
             stu(a.xf, (uint32_t)n, 0.f);
-            stu(a.pf, (uint32_t)n, zf);
         }
     }
     const double s_rz = wg_sum(rz, sm), s_ro = wg_sum(ro, sm);
     if (threadIdx.x == 0) {
         const int G = gridDim.x;
-        a.part[kRz0 * G + blockIdx.x] = s_rz;
+        if (F64) a.part[kRz0 * G + blockIdx.x] = s_rz;
         a.part[kRo * G + blockIdx.x] = s_ro;
     }
 }
@@ -479,10 +654,10 @@ hipError_t pot_workgroups(int dim, int ntiles, bool nbr, int *G)
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    const void *k = dim == 2 ? (nbr ? (const void *)pot_dirspmv_kernel<D2Q9, 1, kPotNodes, double>
-                                    : (const void *)pot_dirspmv_kernel<D2Q9, 0, kPotNodes, double>)
-                             : (nbr ? (const void *)pot_dirspmv_kernel<D3Q19, 1, kPotNodes, double>
-                                    : (const void *)pot_dirspmv_kernel<D3Q19, 0, kPotNodes, double>);
+    const void *k = dim == 2 ? (nbr ? (const void *)pot_dirspmv_kernel<D2Q9, 1, kPotNodes>
+                                    : (const void *)pot_dirspmv_kernel<D2Q9, 0, kPotNodes>)
+                             : (nbr ? (const void *)pot_dirspmv_kernel<D3Q19, 1, kPotNodes>
+                                    : (const void *)pot_dirspmv_kernel<D3Q19, 0, kPotNodes>);
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kTile, 0);
     if (e != hipSuccess) return e;
     // at most 4 per CU: with more, one tile step of all resident workgroups
@@ -506,23 +681,31 @@ hipError_t launch_pot_setup(int dim, const PotArgs &a, int G, double tol, hipStr
     return hipGetLastError();
 }
 
-template <class L, class T>
-void pot_iter_l(const PotArgs &a, int G, int k, hipStream_t s)
+template <class L, int NBR>
+void pot_iter_l(const PotArgs &a, int G, int k, bool f32, hipStream_t s)
 {
-    if (a.nbr)
-        pot_dirspmv_kernel<L, 1, kPotNodes, T><<<G, kTile, 0, s>>>(a, k);
-    else
-        pot_dirspmv_kernel<L, 0, kPotNodes, T><<<G, kTile, 0, s>>>(a, k);
-    pot_axpy_kernel<T><<<G, kTile, 0, s>>>(a, k);
+    if (f32) {
+        pot_spmv32_kernel<L, NBR, kPotNodes><<<G, kTile, 0, s>>>(a, k);
+        pot_update32_kernel<L, NBR, 0><<<G, kTile, 0, s>>>(a, k);
+    } else {
+        pot_dirspmv_kernel<L, NBR, kPotNodes><<<G, kTile, 0, s>>>(a, k);
+        pot_axpy_kernel<<<G, kTile, 0, s>>>(a, k);
+    }
 }
 
 hipError_t launch_pot_iter(int dim, const PotArgs &a, int G, int k, bool f32, hipStream_t s)
 {
     if (dim == 2)
-        f32 ? pot_iter_l<D2Q9, float>(a, G, k, s) : pot_iter_l<D2Q9, double>(a, G, k, s);
+        a.nbr ? pot_iter_l<D2Q9, 1>(a, G, k, f32, s) : pot_iter_l<D2Q9, 0>(a, G, k, f32, s);
     else
-        f32 ? pot_iter_l<D3Q19, float>(a, G, k, s) : pot_iter_l<D3Q19, double>(a, G, k, s);
+        a.nbr ? pot_iter_l<D3Q19, 1>(a, G, k, f32, s) : pot_iter_l<D3Q19, 0>(a, G, k, f32, s);
     return hipGetLastError();
+}
+
+template <class L>
+void start32_l(const PotArgs &a, int G, hipStream_t s)
+{
+    a.nbr ? pot_update32_kernel<L, 1, 1><<<G, kTile, 0, s>>>(a, 0) : pot_update32_kernel<L, 0, 1><<<G, kTile, 0, s>>>(a, 0);
 }
 
 template <class L>
@@ -541,6 +724,7 @@ hipError_t launch_pot_refine(int dim, const PotArgs &a, int G, double tol, doubl
     else
         refine_l<D3Q19>(a, G, f64, s);
     pot_refine_state_kernel<<<1, kTile, 0, s>>>(a, G, tol, tol_min);
+    if (!f64) dim == 2 ? start32_l<D2Q9>(a, G, s) : start32_l<D3Q19>(a, G, s);
     return hipGetLastError();
 }
 

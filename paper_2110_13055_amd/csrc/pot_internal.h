@@ -36,7 +36,8 @@ struct PotArgs {
     double *x, *r, *q;   // CG vectors, P each
     double *p, *p2;      // search direction, alternating between two buffers
     float *xf, *rf, *qf; // the FP32 vectors of a refinement round's correction solve
-    float *pf, *pf2;
+    float *pf;
+    float2 *zp;          // (z, old direction) of each node, for the gathers
     const int *nbr;      // face neighbours (planes 0 .. 2D-1 of the node list) or nullptr
     uint8_t *dg;         // diagonal of A per node (0 .. 12)
     double *part;        // per-workgroup partial sums (pot_part_doubles)
