@@ -1463,8 +1463,9 @@ int cdi_copy_potential(cdi_solver *s, float *psi)
 namespace {
 
 struct NpsLayout {
-    double *x, *r, *rh, *pv, *v, *sv, *t, *part, *state;
-    float *dg;
+    double2 *x, *r, *rh, *pv, *v, *t;
+    float2 *ph, *sh, *di;
+    double *part, *state;
     uint64_t bytes;
 };
 
@@ -1472,14 +1473,15 @@ NpsLayout nps_layout(void *ws, int P)
 {
     Carver c(ws);
     NpsLayout L;
-    L.x = c.take<double>(16ull * P);
-    L.r = c.take<double>(16ull * P);
-    L.rh = c.take<double>(16ull * P);
-    L.pv = c.take<double>(16ull * P);
-    L.v = c.take<double>(16ull * P);
-    L.sv = c.take<double>(16ull * P);
-    L.t = c.take<double>(16ull * P);
-    L.dg = c.take<float>(8ull * P);
+    L.x = c.take<double2>(16ull * P);
+    L.r = c.take<double2>(16ull * P);
+    L.rh = c.take<double2>(16ull * P);
+    L.pv = c.take<double2>(16ull * P);
+    L.v = c.take<double2>(16ull * P);
+    L.t = c.take<double2>(16ull * P);
+    L.ph = c.take<float2>(8ull * P);
+    L.sh = c.take<float2>(8ull * P);
+    L.di = c.take<float2>(8ull * P);
     L.part = c.take<double>(8ull * nps_part_doubles());
     L.state = c.take<double>(8ull * kNsSlots);
     L.bytes = c.off;
@@ -1509,22 +1511,22 @@ int np_solve(cdi_solver *s, double idt, double tol, int32_t max_iter, void *ws, 
     a.rh = W.rh;
     a.pv = W.pv;
     a.v = W.v;
-    a.sv = W.sv;
     a.t = W.t;
-    a.dg = W.dg;
+    a.ph = W.ph;
+    a.sh = W.sh;
+    a.di = W.di;
     a.part = W.part;
     a.state = W.state;
-    int G = 0;
-    HIPCHK(nps_workgroups(s->dim, s->ntiles, &G));
-    HIPCHK(launch_nps_setup(s->dim, a, G, tol, s->stream));
+    HIPCHK(nps_workgroups(s->dim, s->ntiles, &a.G, a.Gd));
+    HIPCHK(launch_nps_setup(s->dim, a, tol, s->stream));
     double st[kNsSlots];
     if ((rc = d2h(s, st, W.state, sizeof st)) != CDI_OK) return rc;
     int k = 0;
     while (st[kNsDone] == 0 && k < max_iter) {
         const int n = std::min(32, max_iter - k);
-        for (int q = k; q < k + n; ++q) HIPCHK(launch_nps_iter(s->dim, a, G, q, s->stream));
+        for (int q = k; q < k + n; ++q) HIPCHK(launch_nps_iter(s->dim, a, q, s->stream));
         k += n;
-        HIPCHK(launch_nps_check(a, G, k, s->stream));
+        HIPCHK(launch_nps_check(a, k, s->stream));
         if ((rc = d2h(s, st, W.state, sizeof st)) != CDI_OK) return rc;
     }
     *iters = (int)std::max(st[kNsIters], st[kNsIters + 1]);

@@ -10,25 +10,29 @@
 // coefficients are evaluated in FP32 exactly as the explicit step does; the
 // operator is applied in FP64. For species s the outflow is A_s C - b_s; a
 // backward-Euler step solves (I/dt + A_s) C' = C/dt + b_s and the steady
-// state A_s C = b_s, both by BiCGSTAB (van der Vorst 1992) with the diagonal
-// as right preconditioner, both species in the same kernels with their own
-// scalars. Persistent workgroups and fixed-order partial sums as in pot.hip:
-// every workgroup derives the same scalars, and the iterate does not depend
-// on timing or on how often the host checks.
+// state A_s C = b_s, both by BiCGSTAB (van der Vorst 1992) with right
+// preconditioning (block_solve below), both species in the same kernels with
+// their own scalars, side by side in memory: one load brings a node's pair.
+// Persistent workgroups and fixed-order partial sums as in pot.hip: every
+// workgroup derives the same scalars, and the iterate does not depend on
+// timing or on how often the host checks.
 //
-// Iteration k (species s, K = diag). The directions are stored
-// preconditioned, p^ = K^-1 p and s^ = K^-1 s, so that the operator gathers
-// no diagonals (measured on the 512^3 electrode, together with issuing every
-// load of a node before its per-face branches: 7.33 -> 5.89 ms per iteration):
+// Iteration k (species s, M the preconditioner). The vectors are FP64; the
+// preconditioned directions p^ = M p and s^ = M s are FP32 numbers, the same
+// ones where A is applied and where x is updated, so that their rounding
+// changes M and not the balance of x and r. s replaces r.
 //   dir     stop test on |r_k|; beta = (rho_k / rho_{k-1}) (alpha / omega);
-//           p^ = K^-1 (r - beta omega v) + beta p^
+//           p = r + beta (p - omega v); p^ = M p
 //   apply   v = A p^; partial rhat . v
-//   sdir    alpha = rho_k / (rhat . v); s^ = K^-1 (r - alpha v)
-//   apply   t = A s^; partials t . s (s = K s^), t . t
+//   sdir    alpha = rho_k / (rhat . v); s = r - alpha v; s^ = M s
+//   apply   t = A s^; partials t . s, t . t
 //   update  omega = (t . s) / (t . t); x += alpha p^ + omega s^;
-//           r = K s^ - omega t; partials rho_{k+1} = rhat . r, |r|^2
+//           r = s - omega t; partials rho_{k+1} = rhat . r, |r|^2
 // A species whose residual met the tolerance is frozen (its partials stop
-// changing, so every later test repeats the decision).
+// changing, so every later test repeats the decision; its scalars are zero,
+// which keeps its x and r).
+#include <algorithm>
+
 #include "cdi_internal.h"
 #include "device_common.h"
 #include "np_solve_internal.h"
@@ -41,9 +45,10 @@ namespace {
 // Partial-sum regions, 2 species x G doubles each.
 enum { kRv = 0, kTs = 1, kTt = 2, kRho0 = 3, kRho1 = 4, kRr = 5, kBb = 6, kRegions = 7 };
 
-__device__ inline double *reg(const NpsArgs &a, int r, int s) { return a.part + ((size_t)r * 2 + s) * gridDim.x; }
+__device__ inline double *reg(const NpsArgs &a, int r, int s) { return a.part + ((size_t)r * 2 + s) * a.G; }
 
-__device__ __forceinline__ double of_species(float2 c, int s) { return s ? c.y : c.x; }
+__device__ __forceinline__ float of_species(float2 c, int s) { return s ? c.y : c.x; }
+__device__ __forceinline__ double of_species(double2 c, int s) { return s ? c.y : c.x; }
 
 // alpha, beta of a face from the half drift hw (the explicit step's Bs).
 __device__ inline void sg_coef(float D, float invD2, float hw, float &al, float &be)
@@ -76,17 +81,14 @@ struct NpNode {
     float diag[2];
 };
 
+// Its neighbours, from the list when the instance has one built with the ions'
+// x periodicity (read with the node's data), else through the coordinates and
+// the map.
 template <class L>
-__device__ inline void np_node(const Grid &g, const Phys &p, const float *j, int n, NpNode<L> &c)
+__device__ __forceinline__ void np_faces(const Grid &g, const Phys &p, int n, NpNode<L> &c)
 {
     constexpr int D = L::D;
     const int P = g.P;
-    // every load is issued before the per-face branches (a load inside a
-    // divergent branch waits for its data before the next face starts): the
-    // six neighbours, then the flux (and potential) of each, at the node
-    // itself where the face is not fluid. The neighbours come from the list
-    // when the instance has one built with the ions' x periodicity (read
-    // with the node's data), else through the coordinates and the map.
     if (g.nbr && (p.npx == kNpxPeriodic) == (g.periodic_x != 0)) {
 #pragma unroll
         for (int k = 0; k < 2 * D; ++k) c.m[k] = ldu(g.nbr + (size_t)k * P, (uint32_t)n);
@@ -98,6 +100,17 @@ __device__ inline void np_node(const Grid &g, const Phys &p, const float *j, int
 #pragma unroll
         for (int k = 0; k < 2 * D; ++k) c.m[k] = nb_get<L>(g, ctx, k + 1);
     }
+}
+
+// Its coefficients, after np_faces. Every load is issued before the per-face
+// branches (a load inside a divergent branch waits for its data before the
+// next face starts): the flux (and potential) of each neighbour, at the node
+// itself where the face is not fluid.
+template <class L>
+__device__ __forceinline__ void np_coefs(const Grid &g, const Phys &p, const float *j, int n, NpNode<L> &c)
+{
+    constexpr int D = L::D;
+    const int P = g.P;
     float jP[3], jN[2 * D], psiN[2 * D];
     jP[0] = ldu(j, (uint32_t)n);
     jP[1] = ldu(j + P, (uint32_t)n);
@@ -163,45 +176,49 @@ __device__ inline void np_node(const Grid &g, const Phys &p, const float *j, int
 }
 
 template <class L>
+__device__ inline void np_node(const Grid &g, const Phys &p, const float *j, int n, NpNode<L> &c)
+{
+    np_faces<L>(g, p, n, c);
+    np_coefs<L>(g, p, j, n, c);
+}
+
+template <class L>
 __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
 {
     __shared__ double sm[kTile / 64];
     int t0, t1;
     tile_range(a.g.P / kTile, t0, t1);
-    const int P = a.g.P;
     double bb[2] = {0, 0}, rho[2] = {0, 0}, rr[2] = {0, 0};
     for (int t = t0; t < t1; ++t) {
         const int n = t * kTile + threadIdx.x;
         double xv[2] = {0, 0}, rv[2] = {0, 0};
-        float dv[2] = {1.f, 1.f};
+        float di[2] = {0, 0};
         if (n < a.g.n_f) {
             NpNode<L> c;
             np_node<L>(a.g, a.p, a.j, n, c);
+            float2 cN[2 * L::D];
+#pragma unroll
+            for (int k = 0; k < 2 * L::D; ++k) cN[k] = a.C[c.m[k] >= 0 ? c.m[k] : n];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 xv[s] = of_species(a.C[n], s);
                 double ax = (c.diag[s] + a.idt) * xv[s];
 #pragma unroll
                 for (int k = 0; k < 2 * L::D; ++k)
-                    if (c.m[k] >= 0) ax -= (double)c.be[s][k] * of_species(a.C[c.m[k]], s);
+                    if (c.m[k] >= 0) ax -= (double)c.be[s][k] * (double)of_species(cN[k], s);
                 const double rhs = a.idt * xv[s] + c.b[s];
                 rv[s] = rhs - ax;
-                dv[s] = (float)(c.diag[s] + a.idt);
-                if (!(dv[s] > 0.f)) dv[s] = 1.f;  // a cell with no outflow at all (an isolated closed pocket)
+                const float d = (float)(c.diag[s] + a.idt);
+                di[s] = 1.f / (d > 0.f ? d : 1.f);  // (no outflow at all: an isolated closed pocket)
                 bb[s] += rhs * rhs;
                 rho[s] += rv[s] * rv[s];
                 rr[s] += rv[s] * rv[s];
             }
         }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            stu(a.x, (uint32_t)(s * P + n), xv[s]);
-            stu(a.r, (uint32_t)(s * P + n), rv[s]);
-            stu(a.rh, (uint32_t)(s * P + n), rv[s]);
-            stu(a.pv, (uint32_t)(s * P + n), 0.0);
-            stu(a.v, (uint32_t)(s * P + n), 0.0);
-            stu(a.dg, (uint32_t)(s * P + n), dv[s]);
-        }
+        stu(a.x, (uint32_t)n, make_double2(xv[0], xv[1]));
+        stu(a.r, (uint32_t)n, make_double2(rv[0], rv[1]));
+        stu(a.rh, (uint32_t)n, make_double2(rv[0], rv[1]));
+        stu(a.di, (uint32_t)n, make_float2(di[0], di[1]));
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -218,17 +235,6 @@ __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
     }
 }
 
-// Per-species stop decision from the |r|^2 partials (the same in every workgroup).
-__device__ inline void species_active(const NpsArgs &a, double *sm, bool (&act)[2], double (&rr)[2])
-{
-    const int G = gridDim.x;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        rr[s] = region_sum(reg(a, kRr, s), G, sm);
-        act[s] = !(rr[s] <= a.state[kNsThr + s]);
-    }
-}
-
 __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, double tol)
 {
     __shared__ double sm[kTile / 64];
@@ -240,67 +246,225 @@ __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, doub
             a.state[kNsThr + s] = tol * tol * bb;
             a.state[kNsRr + s] = rr;
             a.state[kNsIters + s] = 0;
+            a.state[kNsScale + s] = rr > 0.0 && isfinite(rr) ? ldexp(1.0, -ilogb(sqrt(rr))) : 1.0;
             a.state[kNsActive + s] = rr <= tol * tol * bb ? 0.0 : 1.0;
         }
     }
     if (threadIdx.x == 0) a.state[kNsDone] = (a.state[kNsActive] == 0 && a.state[kNsActive + 1] == 0) ? 1.0 : 0.0;
 }
 
-// dir: stop test and the new direction.
-__global__ __launch_bounds__(kTile) void nps_dir_kernel(NpsArgs a, int k)
+// The preconditioner: M is block diagonal over blocks of kBlockNodes
+// consecutive nodes (16 x 16 x 7 voxels of a brick at porosity 0.6), in a
+// block the kChebSteps-th iterate of the Chebyshev iteration for D^-1 A_b z =
+// D^-1 r on [kChebLow, 2], from z = 0 (D the diagonal; what leaves a cell
+// enters its neighbours, so that the columns of A D^-1 - I sum to at most 1
+// and the spectrum ends at 2), on FP32 numbers, with r scaled by a power of two
+// per solve (which scales M). The blocks take the cells' own coefficients:
+// BiCGSTAB needs 0.4 of the diagonal's iterations (207 and 249 -> 89 and 91 for
+// the two ions on a 96^3 electrode at porosity 0.6 in the ramp's field, 249 and
+// 263 -> 98 and 101 with an electrode at -20 thermal voltages), where a
+// diffusion-only block does as well in weak fields and fails in steep ones
+// (no convergence at -20). The coefficients are formed again from flux and
+// potential where they are needed, 16 bytes a node instead of 48 for stored
+// ones. The sweeps run on the block in LDS; what bounds the direction kernels
+// is their streams (112 and 96 bytes a node) about as much as their arithmetic.
+// 192^3, 4.2 M nodes, to 1e-10: 141 -> 52 ms, 300 -> 118 iterations of 383 ->
+// 372 us.
+// Nodes per thread of the direction kernels: two. A node's row and its loads
+// take about 45 registers; at four a thread only two workgroups of 256 fit a
+// compute unit (per iteration of 4.2 M nodes, p^ and s^: 124 and 109 us at four,
+// 95 and 72 at two, 108 and 87 at one; capped at 168 or 128 registers the four
+// spill, 148 and 95, 231 and 220).
+constexpr int kDirNodes = 2, kDirThreads = kBlockNodes / kDirNodes;
+
+template <class L>
+struct BlockRows {
+    float be[kDirNodes][2][2 * L::D];   // off the diagonal, 0 outside the block
+    uint16_t lm[kDirNodes][2 * L::D];   // the neighbours' places in the block (the node's own where be = 0)
+    float dinv[kDirNodes][2];
+};
+
+// The rows of this thread's nodes (zero beyond the lattice): only the
+// coefficients of neighbours in the block, straight through.
+template <class L>
+__device__ __forceinline__ void block_rows(const NpsArgs &a, int base, BlockRows<L> &b)
 {
-    __shared__ double sm[kTile / 64];
-    __shared__ int stop;
-    if (stopped_at(a.state, kNsDone, &stop)) return;
-    const int G = gridDim.x;
-    bool act[2];
-    double rr[2];
-    species_active(a, sm, act, rr);
-    double beta[2] = {0, 0}, omega[2] = {1, 1};
-    bool bad = false;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const double rho_new = region_sum(reg(a, k & 1 ? kRho1 : kRho0, s), G, sm);
-        const double rho_old = region_sum(reg(a, k & 1 ? kRho0 : kRho1, s), G, sm);
-        const double rv = region_sum(reg(a, kRv, s), G, sm);
-        const double ts = region_sum(reg(a, kTs, s), G, sm), tt = region_sum(reg(a, kTt, s), G, sm);
-        if (k == 0) continue;  // p = r
-        const double alpha = rho_old / rv;
-        omega[s] = ts / tt;
-        beta[s] = (rho_new / rho_old) * (alpha / omega[s]);
-        if (act[s] && !(isfinite(beta[s]) && isfinite(rr[s]))) bad = true;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        for (int s = 0; s < 2; ++s) {
-            a.state[kNsActive + s] = act[s] ? 1.0 : 0.0;
-            a.state[kNsRr + s] = rr[s];
-            if (act[s]) a.state[kNsIters + s] = k;
-        }
-        if (bad) a.state[kNsDone] = 2.0;
-        else if (!act[0] && !act[1]) a.state[kNsDone] = 1.0;
-    }
-    if (bad || (!act[0] && !act[1])) return;
-    int t0, t1;
-    tile_range(a.g.P / kTile, t0, t1);
+    constexpr int F = 2 * L::D;
+    const Phys &p = a.p;
     const int P = a.g.P;
-    for (int t = t0; t < t1; ++t) {
-        const int n = t * kTile + threadIdx.x;
-        if (n >= a.g.n_f) continue;
+    const float invD2[2] = {2.f * p.invD[0], 2.f * p.invD[1]};
+    const float hzD[2] = {0.5f * p.z[0] * p.D[0], 0.5f * p.z[1] * p.D[1]};
+    NpNode<L> c[kDirNodes];
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (!act[s]) continue;
-            const uint32_t q = (uint32_t)(s * P + n);
-            const double d = (double)ldu(a.dg, q);
-            const double pn = k == 0 ? ldu(a.r, q) / d
-                                     : (ldu(a.r, q) - beta[s] * omega[s] * ldu(a.v, q)) / d + beta[s] * ldu(a.pv, q);
-            stu(a.pv, q, pn);
+    for (int j = 0; j < kDirNodes; ++j) {
+        const int n = base + j * kDirThreads + (int)threadIdx.x;
+        np_faces<L>(a.g, p, n < a.g.n_f ? n : a.g.n_f - 1, c[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < kDirNodes; ++j) {
+        const int own = j * kDirThreads + (int)threadIdx.x;
+        const bool on = base + own < a.g.n_f;
+        const uint32_t n = on ? (uint32_t)(base + own) : 0u;
+        bool in[F];
+        float jP[L::D], jN[F], psiN[F];
+#pragma unroll
+        for (int d = 0; d < L::D; ++d) jP[d] = ldu(a.j + (size_t)d * P, n);
+        const float psiP = p.psi ? ldu(p.psi, n) : 0.f;
+        const float2 di = ldu(a.di, n);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            const uint32_t l = (uint32_t)(c[j].m[f] - base);  // (beyond the block for negative values too)
+            in[f] = on && c[j].m[f] >= 0 && l < (uint32_t)kBlockNodes;
+            b.lm[j][f] = (uint16_t)(in[f] ? l : (uint32_t)own);
+            const uint32_t q = in[f] ? (uint32_t)c[j].m[f] : n;
+            jN[f] = ldu(a.j + (size_t)(f >> 1) * P, q);
+            psiN[f] = p.psi ? ldu(p.psi, q) : 0.f;
+        }
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            const float sg = (f & 1) ? -1.f : 1.f;
+            const float hun = 0.25f * (jP[f >> 1] + jN[f]) * sg;
+            const float dpsi = p.psi ? psiN[f] - psiP : (f >> 1) == 0 ? -sg * p.dpsi_dx : 0.f;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                float al, be;
+                sg_coef(p.D[s], invD2[s], hun - hzD[s] * dpsi, al, be);
+                b.be[j][s][f] = in[f] ? be : 0.f;
+            }
+        }
+        b.dinv[j][0] = on ? di.x : 0.f;
+        b.dinv[j][1] = on ? di.y : 0.f;
+    }
+}
+
+// z = M r of this thread's nodes. zs: two buffers of a block.
+template <class L>
+__device__ __forceinline__ void block_solve(const float (&r)[kDirNodes][2], const BlockRows<L> &b,
+                                            float2 (*zs)[kBlockNodes], float (&z)[kDirNodes][2])
+{
+    constexpr ChebCoef c = cheb_coef();
+    float d[kDirNodes][2];
+#pragma unroll
+    for (int j = 0; j < kDirNodes; ++j)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) z[j][s] = d[j][s] = c.first * (r[j][s] * b.dinv[j][s]);
+#pragma unroll
+    for (int k = 1; k < kChebSteps; ++k) {
+        float2 *const q = zs[k & 1];
+#pragma unroll
+        for (int j = 0; j < kDirNodes; ++j) q[j * kDirThreads + threadIdx.x] = make_float2(z[j][0], z[j][1]);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kDirNodes; ++j) {
+            float y[2] = {r[j][0], r[j][1]};
+#pragma unroll
+            for (int f = 0; f < 2 * L::D; ++f) {
+                const float2 v = q[b.lm[j][f]];
+                y[0] = fmaf(b.be[j][0][f], v.x, y[0]);
+                y[1] = fmaf(b.be[j][1][f], v.y, y[1]);
+            }
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                d[j][s] = fmaf(c.r[k], fmaf(b.dinv[j][s], y[s], -z[j][s]), c.d[k] * d[j][s]);
+                z[j][s] += d[j][s];
+            }
+            keep_order();  // one node's gathers at a time (all at once take 48 more registers)
         }
     }
 }
 
-// y = (idt I + A) in for the active species (in = p^ or s^, already
-// preconditioned), with partials: WHICH 0 (y = v): rhat . v; WHICH 1 (y = t):
-// t . s with s = K s^, t . t.
+// The two halves of an iteration that make a direction. WHICH 0 (dir): the
+// stop test, p and p^ = M p; WHICH 1 (sdir): s = r - alpha v and s^ = M s.
+template <class L, int WHICH>
+__global__ __launch_bounds__(kDirThreads) void nps_dir_kernel(NpsArgs a, int k)
+{
+    __shared__ double sm[12 * (kDirThreads / 64)];
+    __shared__ int stop;
+    __shared__ float2 zs[2][kBlockNodes];
+    if (stopped_at(a.state, kNsDone, &stop)) return;
+    const int G = a.G;
+    const int now = k & 1 ? kRho1 : kRho0, old = k & 1 ? kRho0 : kRho1;
+    bool act[2];
+    double beta[2] = {0, 0}, omega[2] = {0, 0}, alpha[2] = {0, 0};
+    if (WHICH == 0) {
+        const double *const regions[12] = {reg(a, kRr, 0),  reg(a, kRr, 1),  reg(a, now, 0), reg(a, now, 1),
+                                           reg(a, old, 0),  reg(a, old, 1),  reg(a, kRv, 0), reg(a, kRv, 1),
+                                           reg(a, kTs, 0),  reg(a, kTs, 1),  reg(a, kTt, 0), reg(a, kTt, 1)};
+        double t[12];
+        region_sums(regions, G, sm, t);
+        bool bad = false;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            act[s] = !(t[s] <= a.state[kNsThr + s]);
+            if (k == 0 || !act[s]) continue;  // p = r
+            const double om = t[8 + s] / t[10 + s];
+            const double be = (t[2 + s] / t[4 + s]) * ((t[4 + s] / t[6 + s]) / om);
+            if (!(isfinite(be) && isfinite(t[s]))) bad = true;
+            omega[s] = om;
+            beta[s] = be;
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            for (int s = 0; s < 2; ++s) {
+                a.state[kNsActive + s] = act[s] ? 1.0 : 0.0;
+                a.state[kNsRr + s] = t[s];
+                if (act[s]) a.state[kNsIters + s] = k;
+            }
+            if (bad) a.state[kNsDone] = 2.0;
+            else if (!act[0] && !act[1]) a.state[kNsDone] = 1.0;
+        }
+        if (bad || (!act[0] && !act[1])) return;
+    } else {
+        const double *const regions[4] = {reg(a, now, 0), reg(a, now, 1), reg(a, kRv, 0), reg(a, kRv, 1)};
+        double t[4];
+        region_sums(regions, G, sm, t);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            if (a.state[kNsActive + s] != 0.0) alpha[s] = t[s] / t[2 + s];
+    }
+    const double scale[2] = {a.state[kNsScale], a.state[kNsScale + 1]};
+    int b0, b1;
+    tile_range((a.g.P + kBlockNodes - 1) / kBlockNodes, b0, b1);
+    for (int blk = b0; blk < b1; ++blk) {
+        const int base = blk * kBlockNodes;
+        BlockRows<L> rows;
+        block_rows<L>(a, base, rows);
+        float rf[kDirNodes][2], z[kDirNodes][2];
+#pragma unroll
+        for (int j = 0; j < kDirNodes; ++j) {
+            const int n = base + j * kDirThreads + (int)threadIdx.x;
+            double2 w = make_double2(0, 0);
+            if (n < a.g.n_f) {
+                w = ldu(a.r, (uint32_t)n);
+                if (WHICH == 0) {
+                    if (k > 0) {
+                        const double2 v = ldu(a.v, (uint32_t)n), p = ldu(a.pv, (uint32_t)n);
+                        w.x += beta[0] * (p.x - omega[0] * v.x);
+                        w.y += beta[1] * (p.y - omega[1] * v.y);
+                    }
+                    stu(a.pv, (uint32_t)n, w);
+                } else {
+                    const double2 v = ldu(a.v, (uint32_t)n);
+                    w.x -= alpha[0] * v.x;
+                    w.y -= alpha[1] * v.y;
+                    stu(a.r, (uint32_t)n, w);
+                }
+            }
+            rf[j][0] = (float)(w.x * scale[0]);
+            rf[j][1] = (float)(w.y * scale[1]);
+        }
+        keep_order();
+        __syncthreads();  // the sweeps of the block before may still read zs
+        block_solve<L>(rf, rows, zs, z);
+#pragma unroll
+        for (int j = 0; j < kDirNodes; ++j) {
+            const int n = base + j * kDirThreads + (int)threadIdx.x;
+            if (n < a.g.n_f) stu(WHICH == 0 ? a.ph : a.sh, (uint32_t)n, make_float2(z[j][0], z[j][1]));
+        }
+    }
+}
+
+// y = (idt I + A) in (in = p^ or s^), with partials: WHICH 0 (y = v): rhat . v;
+// WHICH 1 (y = t): t . s, t . t.
 template <class L, int WHICH>
 __global__ __launch_bounds__(kTile) void nps_apply_kernel(NpsArgs a)
 {
@@ -308,47 +472,37 @@ __global__ __launch_bounds__(kTile) void nps_apply_kernel(NpsArgs a)
     __shared__ int stop;
     if (stopped_at(a.state, kNsDone, &stop)) return;
     const bool act[2] = {a.state[kNsActive] != 0.0, a.state[kNsActive + 1] != 0.0};
-    const double *in = WHICH == 0 ? a.pv : a.sv;
-    double *out = WHICH == 0 ? a.v : a.t;
+    const float2 *in = WHICH == 0 ? a.ph : a.sh;
+    double2 *out = WHICH == 0 ? a.v : a.t;
     int t0, t1;
     tile_range(a.g.P / kTile, t0, t1);
-    const int P = a.g.P;
     double d0[2] = {0, 0}, d1[2] = {0, 0};
     for (int t = t0; t < t1; ++t) {
         const int n = t * kTile + threadIdx.x;
         if (n >= a.g.n_f) continue;
         NpNode<L> c;
-        np_node<L>(a.g, a.p, a.j, n, c);
-        // both species' neighbour values (stored preconditioned), all
-        // gathered before any is used (the node's own where the face is not
-        // fluid; not applied there)
-        double vN[2][2 * L::D], vP[2];
+        np_faces<L>(a.g, a.p, n, c);
+        // the neighbours' pairs, all gathered before any is used (the node's
+        // own where the face is not fluid; not applied there)
+        float2 vN[2 * L::D];
+#pragma unroll
+        for (int f = 0; f < 2 * L::D; ++f) vN[f] = ldu(in, (uint32_t)(c.m[f] >= 0 ? c.m[f] : n));
+        const float2 vP = ldu(in, (uint32_t)n);
+        const double2 w = ldu(WHICH == 0 ? a.rh : a.r, (uint32_t)n);
+        np_coefs<L>(a.g, a.p, a.j, n, c);
+        double y[2];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
+            y[s] = ((double)c.diag[s] + a.idt) * (double)of_species(vP, s);
 #pragma unroll
             for (int f = 0; f < 2 * L::D; ++f)
-                vN[s][f] = ldu(in, (uint32_t)(s * P + (c.m[f] >= 0 ? c.m[f] : n)));
-            vP[s] = ldu(in, (uint32_t)(s * P + n));
+                if (c.m[f] >= 0) y[s] -= (double)c.be[s][f] * (double)of_species(vN[f], s);
+            d0[s] += y[s] * of_species(w, s);
+            if (WHICH == 1) d1[s] += y[s] * y[s];
         }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (!act[s]) continue;
-            const uint32_t q = (uint32_t)(s * P + n);
-            const double yP = vP[s];
-            double y = ((double)c.diag[s] + a.idt) * yP;
-#pragma unroll
-            for (int f = 0; f < 2 * L::D; ++f)
-                if (c.m[f] >= 0) y -= (double)c.be[s][f] * vN[s][f];
-            stu(out, q, y);
-            if (WHICH == 0) {
-                d0[s] += ldu(a.rh, q) * y;
-            } else {
-                d0[s] += y * (yP * (double)ldu(a.dg, q));
-                d1[s] += y * y;
-            }
-        }
+        stu(out, (uint32_t)n, make_double2(y[0], y[1]));
     }
-    const int G = gridDim.x;
+    const int G = a.G;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         if (!act[s]) continue;  // a frozen species keeps its last partials
@@ -365,65 +519,44 @@ __global__ __launch_bounds__(kTile) void nps_apply_kernel(NpsArgs a)
     }
 }
 
-// s^ = K^-1 (r - alpha v)
-__global__ __launch_bounds__(kTile) void nps_sdir_kernel(NpsArgs a, int k)
-{
-    __shared__ double sm[kTile / 64];
-    __shared__ int stop;
-    if (stopped_at(a.state, kNsDone, &stop)) return;
-    const bool act[2] = {a.state[kNsActive] != 0.0, a.state[kNsActive + 1] != 0.0};
-    const int G = gridDim.x;
-    double alpha[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-        alpha[s] = region_sum(reg(a, k & 1 ? kRho1 : kRho0, s), G, sm) / region_sum(reg(a, kRv, s), G, sm);
-    int t0, t1;
-    tile_range(a.g.P / kTile, t0, t1);
-    const int P = a.g.P;
-    for (int t = t0; t < t1; ++t) {
-        const int n = t * kTile + threadIdx.x;
-        if (n >= a.g.n_f) continue;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (!act[s]) continue;
-            const uint32_t q = (uint32_t)(s * P + n);
-            stu(a.sv, q, (ldu(a.r, q) - alpha[s] * ldu(a.v, q)) / (double)ldu(a.dg, q));
-        }
-    }
-}
-
-// x += alpha p^ + omega s^; r = K s^ - omega t; partials rho_{k+1}, |r|^2
+// x += alpha p^ + omega s^; r = s - omega t; partials rho_{k+1}, |r|^2. Bound
+// by its streams (112 bytes a node).
 __global__ __launch_bounds__(kTile) void nps_update_kernel(NpsArgs a, int k)
 {
-    __shared__ double sm[kTile / 64];
+    __shared__ double sm[8 * (kTile / 64)];
     __shared__ int stop;
     if (stopped_at(a.state, kNsDone, &stop)) return;
     const bool act[2] = {a.state[kNsActive] != 0.0, a.state[kNsActive + 1] != 0.0};
-    const int G = gridDim.x;
-    double alpha[2], omega[2];
+    const int G = a.G, now = k & 1 ? kRho1 : kRho0;
+    const double *const regions[8] = {reg(a, now, 0), reg(a, now, 1), reg(a, kRv, 0), reg(a, kRv, 1),
+                                      reg(a, kTs, 0), reg(a, kTs, 1), reg(a, kTt, 0), reg(a, kTt, 1)};
+    double t8[8], alpha[2], omega[2];
+    region_sums(regions, G, sm, t8);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-        alpha[s] = region_sum(reg(a, k & 1 ? kRho1 : kRho0, s), G, sm) / region_sum(reg(a, kRv, s), G, sm);
-        omega[s] = region_sum(reg(a, kTs, s), G, sm) / region_sum(reg(a, kTt, s), G, sm);
+        alpha[s] = act[s] ? t8[s] / t8[2 + s] : 0.0;
+        omega[s] = act[s] ? t8[4 + s] / t8[6 + s] : 0.0;
     }
     int t0, t1;
     tile_range(a.g.P / kTile, t0, t1);
-    const int P = a.g.P;
     double rho[2] = {0, 0}, rr[2] = {0, 0};
     for (int t = t0; t < t1; ++t) {
         const int n = t * kTile + threadIdx.x;
         if (n >= a.g.n_f) continue;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (!act[s]) continue;
-            const uint32_t q = (uint32_t)(s * P + n);
-            const double sh = ldu(a.sv, q);
-            stu(a.x, q, ldu(a.x, q) + alpha[s] * ldu(a.pv, q) + omega[s] * sh);
-            const double rn = sh * (double)ldu(a.dg, q) - omega[s] * ldu(a.t, q);
-            stu(a.r, q, rn);
-            rho[s] += ldu(a.rh, q) * rn;
-            rr[s] += rn * rn;
-        }
+        const uint32_t q = (uint32_t)n;
+        const float2 ph = ldu(a.ph, q), sh = ldu(a.sh, q);
+        double2 x = ldu(a.x, q), r = ldu(a.r, q);
+        const double2 tv = ldu(a.t, q), rh = ldu(a.rh, q);
+        x.x += alpha[0] * (double)ph.x + omega[0] * (double)sh.x;
+        x.y += alpha[1] * (double)ph.y + omega[1] * (double)sh.y;
+        r.x -= omega[0] * tv.x;
+        r.y -= omega[1] * tv.y;
+        stu(a.x, q, x);
+        stu(a.r, q, r);
+        rho[0] += rh.x * r.x;
+        rho[1] += rh.y * r.y;
+        rr[0] += r.x * r.x;
+        rr[1] += r.y * r.y;
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -455,13 +588,14 @@ __global__ __launch_bounds__(kTile) void nps_check_kernel(NpsArgs a, int k, int 
 }
 
 // The FP64 solution as FP32 concentrations with their remainders.
-__global__ __launch_bounds__(kTile) void nps_store_kernel(const double *x, float2 *C, __half2 *Clo, int P, int n_f)
+__global__ __launch_bounds__(kTile) void nps_store_kernel(const double2 *x, float2 *C, __half2 *Clo, int n_f)
 {
     const int n = blockIdx.x * kTile + threadIdx.x;
     if (n >= n_f) return;
-    const float c0 = (float)x[n], c1 = (float)x[P + n];
-    C[n] = make_float2(c0, c1);
-    Clo[n] = __halves2half2(lo_encode((float)(x[n] - c0)), lo_encode((float)(x[P + n] - c1)));
+    const double2 v = x[n];
+    const float2 c = make_float2((float)v.x, (float)v.y);
+    C[n] = c;
+    Clo[n] = __halves2half2(lo_encode((float)(v.x - c.x)), lo_encode((float)(v.y - c.y)));
 }
 
 // Rates of adsorption, inflow and outflow of C (per tile, FP64).
@@ -479,7 +613,7 @@ __global__ __launch_bounds__(kTile) void nps_rates_kernel(Grid g, Phys p, const 
         np_node<L>(g, p, j, n, c);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const double cp = of_species(C[n], s);
+            const double cp = (double)of_species(C[n], s);
 #pragma unroll
             for (int f = 0; f < 2 * L::D; ++f) {
                 const int m = c.m[f];
@@ -511,7 +645,7 @@ __global__ __launch_bounds__(kTile) void nps_rates_kernel(Grid g, Phys p, const 
 
 uint64_t nps_part_doubles() { return (uint64_t)kRegions * 2 * kNpsMaxWorkgroups; }
 
-hipError_t nps_workgroups(int dim, int ntiles, int *G)
+hipError_t nps_workgroups(int dim, int ntiles, int *G, int *Gd)
 {
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -527,45 +661,58 @@ hipError_t nps_workgroups(int dim, int ntiles, int *G)
     long long g = (long long)cus * (per_cu > 0 ? per_cu : 1);
     g = g < kNpsMaxWorkgroups ? g : kNpsMaxWorkgroups;
     *G = (int)(ntiles < g ? ntiles : g);
-    return hipSuccess;
+    // the direction kernels: as many workgroups as are resident together, none
+    // left over for a second wave
+    int fit = 0;
+    e = hipSuccess;
+    for (int w = 0; w < 2 && e == hipSuccess; ++w) {
+        const void *const d[2][2] = {{(const void *)nps_dir_kernel<D2Q9, 0>, (const void *)nps_dir_kernel<D2Q9, 1>},
+                                     {(const void *)nps_dir_kernel<D3Q19, 0>, (const void *)nps_dir_kernel<D3Q19, 1>}};
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, d[dim == 3][w], kDirThreads, 0);
+        const long long most = (long long)cus * std::min(std::max(fit, 1), kNpsWorkgroupsPerCU);
+        const long long blocks = ((long long)ntiles + kBlockTiles - 1) / kBlockTiles;
+        Gd[w] = (int)std::min(std::min(blocks, most), (long long)kNpsMaxWorkgroups);
+    }
+    return e;
 }
 
-hipError_t launch_nps_setup(int dim, const NpsArgs &a, int G, double tol, hipStream_t s)
+hipError_t launch_nps_setup(int dim, const NpsArgs &a, double tol, hipStream_t s)
 {
     if (dim == 2)
-        nps_setup_kernel<D2Q9><<<G, kTile, 0, s>>>(a);
+        nps_setup_kernel<D2Q9><<<a.G, kTile, 0, s>>>(a);
     else
-        nps_setup_kernel<D3Q19><<<G, kTile, 0, s>>>(a);
-    nps_state_kernel<<<1, kTile, 0, s>>>(a, G, tol);
+        nps_setup_kernel<D3Q19><<<a.G, kTile, 0, s>>>(a);
+    nps_state_kernel<<<1, kTile, 0, s>>>(a, a.G, tol);
     return hipGetLastError();
 }
 
-hipError_t launch_nps_iter(int dim, const NpsArgs &a, int G, int k, hipStream_t s)
+hipError_t launch_nps_iter(int dim, const NpsArgs &a, int k, hipStream_t s)
 {
-    nps_dir_kernel<<<G, kTile, 0, s>>>(a, k);
-    if (dim == 2)
-        nps_apply_kernel<D2Q9, 0><<<G, kTile, 0, s>>>(a);
-    else
-        nps_apply_kernel<D3Q19, 0><<<G, kTile, 0, s>>>(a);
-    nps_sdir_kernel<<<G, kTile, 0, s>>>(a, k);
-    if (dim == 2)
-        nps_apply_kernel<D2Q9, 1><<<G, kTile, 0, s>>>(a);
-    else
-        nps_apply_kernel<D3Q19, 1><<<G, kTile, 0, s>>>(a);
-    nps_update_kernel<<<G, kTile, 0, s>>>(a, k);
+    if (dim == 2) {
+        nps_dir_kernel<D2Q9, 0><<<a.Gd[0], kDirThreads, 0, s>>>(a, k);
+        nps_apply_kernel<D2Q9, 0><<<a.G, kTile, 0, s>>>(a);
+        nps_dir_kernel<D2Q9, 1><<<a.Gd[1], kDirThreads, 0, s>>>(a, k);
+        nps_apply_kernel<D2Q9, 1><<<a.G, kTile, 0, s>>>(a);
+    } else {
+        nps_dir_kernel<D3Q19, 0><<<a.Gd[0], kDirThreads, 0, s>>>(a, k);
+        nps_apply_kernel<D3Q19, 0><<<a.G, kTile, 0, s>>>(a);
+        nps_dir_kernel<D3Q19, 1><<<a.Gd[1], kDirThreads, 0, s>>>(a, k);
+        nps_apply_kernel<D3Q19, 1><<<a.G, kTile, 0, s>>>(a);
+    }
+    nps_update_kernel<<<a.G, kTile, 0, s>>>(a, k);
     return hipGetLastError();
 }
 
-hipError_t launch_nps_check(const NpsArgs &a, int G, int k, hipStream_t s)
+hipError_t launch_nps_check(const NpsArgs &a, int k, hipStream_t s)
 {
-    nps_check_kernel<<<1, kTile, 0, s>>>(a, k, G);
+    nps_check_kernel<<<1, kTile, 0, s>>>(a, k, a.G);
     return hipGetLastError();
 }
 
 hipError_t launch_nps_store(const NpsArgs &a, float2 *Cout, __half2 *Clo, hipStream_t s)
 {
     const int tiles = a.g.P / kTile;
-    if (tiles > 0) nps_store_kernel<<<tiles, kTile, 0, s>>>(a.x, Cout, Clo, a.g.P, a.g.n_f);
+    if (tiles > 0) nps_store_kernel<<<tiles, kTile, 0, s>>>(a.x, Cout, Clo, a.g.n_f);
     return hipGetLastError();
 }
 

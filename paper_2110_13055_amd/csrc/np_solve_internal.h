@@ -20,7 +20,8 @@ enum {
     kNsBb = 6,      // + s
     kNsThr = 8,     // + s
     kNsDone = 10,   // 0 running, 1 converged, 2 diverged / breakdown
-    kNsSlots = 12
+    kNsScale = 11,  // + s: the power of two that brings |r_0| to 1 to 2
+    kNsSlots = 13
 };
 
 struct NpsArgs {
@@ -28,23 +29,27 @@ struct NpsArgs {
     Phys p;
     const float2 *C;   // concentrations of the state the step starts from
     const float *j;    // frozen advecting mass flux (d planes of P)
+    int G, Gd[2];      // workgroups (nps_workgroups)
     double idt;        // 1 / dt of a backward-Euler step, 0 for the steady state
-    // FP64 vectors, 2 planes (species) of P each
-    double *x, *r, *rh, *pv, *v, *sv, *t;
-    float *dg;         // diagonal of (I/dt + A), 2 planes of P
+    // FP64 vectors of P, both species of a node side by side (r holds s between
+    // the halves of an iteration), and the preconditioned directions
+    double2 *x, *r, *rh, *pv, *v, *t;
+    float2 *ph, *sh;
+    float2 *di;        // reciprocal diagonals of (I/dt + A)
     double *part;      // per-workgroup partial sums (nps_part_doubles)
     double *state;     // kNsSlots doubles
     double *acc;       // the solver's per-tile accumulators (rates pass)
 };
 
 uint64_t nps_part_doubles();
-hipError_t nps_workgroups(int dim, int ntiles, int *G);
-// x = C, r = rhat = C idt + b - A x, diagonal, |rhs|^2, rho_0 and the state.
-hipError_t launch_nps_setup(int dim, const NpsArgs &a, int G, double tol, hipStream_t s);
+// Workgroups of the kernels that leave partial sums, and of the two direction kernels.
+hipError_t nps_workgroups(int dim, int ntiles, int *G, int *Gd);
+// x = C, r = rhat = C idt + b - A x, reciprocal diagonals, |rhs|^2, rho_0 and the state.
+hipError_t launch_nps_setup(int dim, const NpsArgs &a, double tol, hipStream_t s);
 // BiCGSTAB iteration k (direction, A p, s, A s, update); returns at once after the stop.
-hipError_t launch_nps_iter(int dim, const NpsArgs &a, int G, int k, hipStream_t s);
+hipError_t launch_nps_iter(int dim, const NpsArgs &a, int k, hipStream_t s);
 // The stop test before iteration k (one workgroup).
-hipError_t launch_nps_check(const NpsArgs &a, int G, int k, hipStream_t s);
+hipError_t launch_nps_check(const NpsArgs &a, int k, hipStream_t s);
 // C_out = (float) x for the fluid nodes.
 hipError_t launch_nps_store(const NpsArgs &a, float2 *Cout, __half2 *Clo, hipStream_t s);
 // Rates of adsorption, inflow and outflow of the concentrations C (FP64 per

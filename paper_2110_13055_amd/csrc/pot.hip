@@ -152,28 +152,7 @@ __device__ inline float inv_diag_f(int d) { return d > 0 ? __builtin_amdgcn_rcpf
 // 70 at 0.65; blocks of 256 nodes: 62 and 106, of 2048: 42 and 65; four steps
 // on [0.2, 2]: 50 and 80). The sweeps run on the block in LDS: 5 sweeps cost
 // less than a tenth of the iteration's memory time.
-constexpr int kBlockTiles = 4, kBlockNodes = kBlockTiles * kTile;
-constexpr int kChebSteps = 6;
-constexpr double kChebLow = 0.1;
-
-struct ChebCoef {
-    float first, d[kChebSteps], r[kChebSteps];
-};
-constexpr ChebCoef cheb_coef()
-{
-    ChebCoef c{};
-    const double th = (2.0 + kChebLow) / 2, de = (2.0 - kChebLow) / 2, s = th / de;
-    double rho = 1 / s;
-    c.first = (float)(1 / th);
-    for (int k = 1; k < kChebSteps; ++k) {
-        const double rn = 1 / (2 * s - rho);
-        c.d[k] = (float)(rn * rho);
-        c.r[k] = (float)(2 * rn / de);
-        rho = rn;
-    }
-    return c;
-}
-
+//
 // z = M r for this thread's kBlockTiles nodes of a block: lm their face
 // neighbours' places in the block (kBlockNodes: none, a slot that stays 0),
 // dinv their reciprocal diagonals. zs: two buffers of kBlockNodes + 1.

@@ -40,12 +40,63 @@ __device__ inline bool stopped_at(const double *state, int slot, int *flag)
     return *flag != 0;
 }
 
+// Totals of N partial-sum regions (G values each), the same in every workgroup:
+// all loads first, then one pass through LDS. sm: N * waves.
+template <int N>
+__device__ inline void region_sums(const double *const (&part)[N], int G, double *sm, double (&out)[N])
+{
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+#pragma unroll
+    for (int i = 0; i < N; ++i) out[i] = 0;
+    for (int k = threadIdx.x; k < G; k += blockDim.x)
+#pragma unroll
+        for (int i = 0; i < N; ++i) out[i] += part[i][k];
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i) out[i] += __shfl_xor(out[i], off, 64);
+    __syncthreads();  // sm may still be read from a previous call
+    if (lane == 0)
+#pragma unroll
+        for (int i = 0; i < N; ++i) sm[i * waves + wave] = out[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        out[i] = 0;
+        for (int w = 0; w < waves; ++w) out[i] += sm[i * waves + w];
+    }
+}
+
 // Total of a partial-sum region (G values), the same in every workgroup.
 __device__ inline double region_sum(const double *part, int G, double *sm)
 {
     double v = 0;
     for (int k = threadIdx.x; k < G; k += blockDim.x) v += part[k];
     return wg_sum(v, sm);
+}
+
+// Chebyshev sweeps of the solvers' block preconditioners: kChebSteps steps on
+// [kChebLow, 2] (the spectrum of the diagonally scaled matrix ends at 2) over
+// blocks of kBlockNodes consecutive nodes.
+constexpr int kBlockTiles = 4, kBlockNodes = kBlockTiles * kTile;
+constexpr int kChebSteps = 6;
+constexpr double kChebLow = 0.1;
+
+struct ChebCoef {
+    float first, d[kChebSteps], r[kChebSteps];
+};
+constexpr ChebCoef cheb_coef()
+{
+    ChebCoef c{};
+    const double th = (2.0 + kChebLow) / 2, de = (2.0 - kChebLow) / 2, s = th / de;
+    double rho = 1 / s;
+    c.first = (float)(1 / th);
+    for (int k = 1; k < kChebSteps; ++k) {
+        const double rn = 1 / (2 * s - rho);
+        c.d[k] = (float)(rn * rho);
+        c.r[k] = (float)(2 * rn / de);
+        rho = rn;
+    }
+    return c;
 }
 
 }  // namespace cdi
