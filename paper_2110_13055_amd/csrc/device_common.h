@@ -373,18 +373,17 @@ constexpr int kPopBlockLog = 6;
 // apart, so that a node's Q accesses share the first and fold the second
 // into the instructions' offsets)
 template <int Q, class T>
-__device__ __forceinline__ T *pop_at(void *F, int q, int n)
-{
-    T *const node = reinterpret_cast<T *>(F) + (size_t)(uint32_t)(n >> kPopBlockLog) * (Q << kPopBlockLog) +
-                    (n & ((1 << kPopBlockLog) - 1));
-    return node + (q << kPopBlockLog);
-}
-template <int Q, class T>
 __device__ __forceinline__ const T *pop_at(const void *F, int q, int n)
 {
-    const T *const node = reinterpret_cast<const T *>(F) +
-                          (size_t)(uint32_t)(n >> kPopBlockLog) * (Q << kPopBlockLog) + (n & ((1 << kPopBlockLog) - 1));
-    return node + (q << kPopBlockLog);
+    const uint32_t first = (uint32_t)n & ~((1u << kPopBlockLog) - 1);  // of the block
+    const char *const node = reinterpret_cast<const char *>(F) + (uint64_t)(uint32_t)n * sizeof(T) +
+                             (uint64_t)first * (uint32_t)((Q - 1) * sizeof(T));
+    return reinterpret_cast<const T *>(node) + (q << kPopBlockLog);
+}
+template <int Q, class T>
+__device__ __forceinline__ T *pop_at(void *F, int q, int n)
+{
+    return const_cast<T *>(pop_at<Q, T>(const_cast<const void *>(F), q, n));
 }
 
 // Value of direction a or b (one of the two per lane) at node m.

@@ -75,15 +75,56 @@ __device__ __forceinline__ StageT<ST> pop_stored(float v)
     else return v;
 }
 
-// Where incoming population i of node n (odd parity) is stored: plane pl of
-// node nd; in: nd lies in the tile starting at base.
-template <class L>
-__device__ __forceinline__ bool staged_slot(const Nbrs<L> &nb, int n, int i, int base, int &pl, uint32_t &loc)
+// Where the staged odd step finds and leaves its populations: slot i is plane i
+// of the neighbour along e_i, or plane opp(i) of the node itself where that is
+// solid; the population opp(i) arrives in it and the one sent along e_i leaves
+// through it. The slot's place in the stage, the thread's spare element when
+// another tile owns it (never so where the neighbour is solid), is formed once
+// for the three uses below. Formed at each, with the lanes' masks kept in scalar
+// registers that spilled, longer address sums and a source term of a dozen
+// operations per direction, a forced FP32 odd step issued 1500 vector
+// instructions a wave instead of 1130 and took 251 us instead of 234 (5.2 M
+// nodes); the FP16 fused one at 45 M nodes 795 instead of 735.
+template <class L, int ST>
+struct StageSlots {
+    static constexpr uint32_t kBytes = sizeof(StageT<ST>);
+    static constexpr uint32_t kSpare = L::Q * kTile * kBytes;  // from here on: another tile's
+    uint32_t own, two[(L::Q - 1) / 2];                         // byte offsets, those of i and opp(i) in one word
+    __device__ __forceinline__ uint32_t at(int i) const
+    {
+        return i == 0 ? own : (i & 1 ? two[(i - 1) / 2] & 0xffffu : two[(i - 1) / 2] >> 16);
+    }
+    __device__ __forceinline__ bool outside(int i) const { return i != 0 && at(i) >= kSpare; }
+};
+
+template <class L, int ST>
+__device__ __forceinline__ void stage_slots(const Nbrs<L> &nb, int base, StageSlots<L, ST> &s)
 {
-    const int j = L::opp[i];
-    pl = i != 0 && nb.fl[j] ? j : i;
-    loc = (uint32_t)((i == 0 ? n : nb.n[j]) - base);
-    return loc < (uint32_t)kTile;
+    constexpr uint32_t B = StageSlots<L, ST>::kBytes;
+    s.own = threadIdx.x * B;
+    auto slot = [&](int i) {
+        const uint32_t loc = (uint32_t)(nb.n[i] - base);
+        return loc < (uint32_t)kTile ? loc * B + (nb.fl[i] ? i * kTile * B : L::opp[i] * kTile * B)
+                                     : StageSlots<L, ST>::kSpare + s.own;
+    };
+#pragma unroll
+    for (int i = 1; i < L::Q; i += 2) s.two[(i - 1) / 2] = slot(i) | slot(i + 1) << 16;
+}
+
+template <int ST>
+__device__ __forceinline__ LdsT<ST> *stage_at(LdsT<ST> *stage, uint32_t byte)
+{
+    typedef __attribute__((address_space(3))) char lds_char;
+    return (LdsT<ST> *)((lds_char *)stage + byte);
+}
+
+// The slots' lanes are told apart by a comparison where they are needed: kept
+// from one use to the next the masks do not fit the scalar registers.
+template <class L, int ST>
+__device__ __forceinline__ void stage_forget(StageSlots<L, ST> &s)
+{
+#pragma unroll
+    for (int i = 0; i < (L::Q - 1) / 2; ++i) asm volatile("" : "+v"(s.two[i]));
 }
 
 // The stored values behind the Q incoming populations of node n (odd
@@ -91,38 +132,31 @@ __device__ __forceinline__ bool staged_slot(const Nbrs<L> &nb, int n, int i, int
 // the tile (into the same registers, for those lanes only), so that the
 // stage reads are waited for once rather than before every global load.
 template <class L, int ST>
-__device__ __forceinline__ void staged_gather(const void *F, int P, const Nbrs<L> &nb, int n, const LdsT<ST> *stage,
-                                              int base, StageT<ST> (&raw)[L::Q])
+__device__ __forceinline__ void staged_gather(const void *F, const Nbrs<L> &nb, LdsT<ST> *stage,
+                                              const StageSlots<L, ST> &s, StageT<ST> (&raw)[L::Q])
 {
 #pragma unroll
-    for (int i = 0; i < L::Q; ++i) {
-        int pl;
-        uint32_t loc;
-        const bool in = staged_slot<L>(nb, n, i, base, pl, loc);
-        raw[i] = stage[in ? pl * kTile + (int)loc : L::Q * kTile + (int)threadIdx.x];
-    }
+    for (int i = 0; i < L::Q; ++i) raw[i] = *stage_at<ST>(stage, s.at(L::opp[i]));
 #pragma unroll
     for (int i = 1; i < L::Q; ++i) {
-        int pl;
-        uint32_t loc;
-        if (!staged_slot<L>(nb, n, i, base, pl, loc))  // a fluid emitter: plane opp(i) of it
-            raw[i] = *pop_at<L::Q, StageT<ST>>(F, L::opp[i], nb.n[L::opp[i]]);
+        const int j = L::opp[i];
+        if (s.outside(j)) raw[i] = *pop_at<L::Q, StageT<ST>>(F, j, nb.n[j]);
     }
 }
 
 // Store outgoing value v of direction i (odd parity); lds_ok false for the
-// nodes whose slots go through global memory.
+// nodes whose slots go through global memory (what they leave in the stage is
+// not stored back).
 template <class L, int ST>
-__device__ __forceinline__ void staged_scatter(void *F, int P, const Nbrs<L> &nb, int n, int i, float v,
-                                               LdsT<ST> *stage, int base, bool lds_ok)
+__device__ __forceinline__ void staged_scatter(void *F, const Nbrs<L> &nb, int i, float v, LdsT<ST> *stage,
+                                               const StageSlots<L, ST> &s, bool lds_ok)
 {
-    const int j = L::opp[i];
-    const bool own = i == 0 || !nb.fl[i];
-    const int m = i == 0 ? n : nb.n[i];
-    const uint32_t loc = (uint32_t)(m - base);
-    const bool in = lds_ok && loc < (uint32_t)kTile;
-    stage[in ? (own ? j : i) * kTile + (int)loc : L::Q * kTile + (int)threadIdx.x] = pop_stored<ST>(v);
-    if (!in) st_pair<kHalfPop<ST>, L::Q>(F, j, i, m, own, v);
+    const StageT<ST> r = pop_stored<ST>(v);
+    *stage_at<ST>(stage, s.at(i)) = r;
+    if (s.outside(i))
+        *pop_at<L::Q, StageT<ST>>(F, i, nb.n[i]) = r;
+    else if (!lds_ok)  // rare
+        st_pair<kHalfPop<ST>, L::Q>(F, L::opp[i], i, nb.n[i], i == 0 || !nb.fl[i], v);
 }
 
 // Moments, residual terms, collision and the AA store of one node whose
@@ -134,7 +168,7 @@ __device__ __forceinline__ void staged_scatter(void *F, int P, const Nbrs<L> &nb
 template <class L, int ST, int ODD, int NP, bool STAGE = false>
 __device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, const Bufs &b, int P, int n, const Nbrs<L> &nb,
                                 const float (&f)[L::Q], const PlaneRef &pr, double (&res)[2], const MomSums *sums,
-                                LdsT<ST> *stage = nullptr, int base = 0, bool lds_ok = false)
+                                LdsT<ST> *stage = nullptr, const StageSlots<L, ST> *slots = nullptr, bool lds_ok = false)
 {
     constexpr int Q = L::Q, D = L::D;
     float drho, jx, jy, jz;  // drho: rho - 1 - pr.rout
@@ -192,22 +226,29 @@ __device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, co
         for (int i = 0; i < Q; ++i) {
             const float v = sc * stored_pop<L, ODD>(feq_dir<L>(i, eq, ux, uy, uz), i, nb, pr);
             if (STAGE)
-                staged_scatter<L, ST>(b.f, P, nb, n, i, v, stage, base, lds_ok);
+                staged_scatter<L, ST>(b.f, nb, i, v, stage, *slots, lds_ok);
             else
                 scatter<L, ST, ODD>(ODD == kPull ? b.f2 : b.f, P, nb, n, i, v);
         }
         return;
     }
+    // Guo, Zheng & Shi (2002) source term, coef w_i (3 (e_i - u) + 9 (e_i . u)
+    // e_i) . F, as w_i ((e_i . G) (1 + 3 e_i . u) - u . G) with G = 3 coef F: four
+    // operations a direction. Fused steps keep a branch per direction, which
+    // stops the scheduler from spreading all of them over the registers (FP16
+    // fused, 45 M nodes, even and odd: 410 and 735 us against 435 and 726
+    // without it; FP32 flow, forced, 5.2 M nodes: 133 and 234 against 127 and 235)
+    const float fc = 3.f * p.fcoef;
+    const float Gx = fc * p.F[0], Gy = fc * p.F[1], Gz = D == 3 ? fc * p.F[2] : 0.f;
+    const float uG = fmaf(ux, Gx, fmaf(uy, Gy, uz * Gz));
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         const float fe = feq_dir<L>(i, eq, ux, uy, uz);
         float src = 0.f;
-        if (p.forced) {  // Guo, Zheng & Shi (2002) source term
+        if (p.forced) {
             const float eu = lat_dot<L>(i, ux, uy, uz);
-            src = p.fcoef * L::w[i] *
-                  ((3.f * (L::ex[i] - ux) + 9.f * eu * L::ex[i]) * p.F[0] +
-                   (3.f * (L::ey[i] - uy) + 9.f * eu * L::ey[i]) * p.F[1] +
-                   (3.f * (L::ez[i] - uz) + 9.f * eu * L::ez[i]) * p.F[2]);
+            src = L::w[i] * (i == 0 ? -uG : fmaf(lat_dot<L>(i, Gx, Gy, Gz), fmaf(3.f, eu, 1.f), -uG));
+            if (NP) asm volatile("" : "+v"(src));
         }
         float out;
         if (ST == kF16)
@@ -215,7 +256,7 @@ __device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, co
         else
             out = sc * stored_pop<L, ODD>(f[i] - om * (f[i] - fe) + src, i, nb, pr);
         if (STAGE)
-            staged_scatter<L, ST>(b.f, P, nb, n, i, out, stage, base, lds_ok);
+            staged_scatter<L, ST>(b.f, nb, i, out, stage, *slots, lds_ok);
         else
             scatter<L, ST, ODD>(ODD == kPull ? b.f2 : b.f, P, nb, n, i, out);
     }
@@ -532,7 +573,11 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
         }
         keep_order();
     }
-    if (kStage) __syncthreads();
+    StageSlots<L, ST> slots;
+    if (kStage) {
+        if (active) stage_slots<L, ST>(nb, base, slots);
+        __syncthreads();
+    }
     const bool nee = g.inout && (b.flags & kNee);
     // fused, with the moment buffers: the ions' flux is in the moments (else,
     // on the first step of a call, in jin)
@@ -624,7 +669,8 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
             if (kStage) {
                 const float sc = ST == kH16 ? p.hs_inv : 1.f;
                 StageT<ST> raw[Q];
-                staged_gather<L, ST>(b.f, P, nb, n, stg, base, raw);
+                staged_gather<L, ST>(b.f, nb, stg, slots, raw);
+                stage_forget(slots);
 #pragma unroll
                 for (int i = 0; i < Q; ++i) f[i] = rel_pop<L, ODD>(sc * pop_float<ST>(raw[i]), i, nb, pr);
             } else {
@@ -698,7 +744,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
         if constexpr (kMoments<ST>)
             moment_node<L>(b, n, sums.d, sums.jx, sums.jy, sums.jz, pr.rout, res);
         else
-            lbm_node<L, ST, ODD, NP, kStage>(p, b, P, n, nb, f, pr, res, kPlain<ST> ? nullptr : &sums, stg, base,
+            lbm_node<L, ST, ODD, NP, kStage>(p, b, P, n, nb, f, pr, res, kPlain<ST> ? nullptr : &sums, stg, &slots,
                                              !(nee && (x == 0 || x == g.nx - 1)));
         const bool inl = edge && x == 1 && nb.fl[2];
         const bool outl = edge && x == g.nx - 2 && nb.fl[1];
@@ -721,8 +767,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
                 for (int i = 1; i < Q; ++i) set_nbr<L>(nbb, i, nb_map<L>(g, xb, y, z, i, false), bn);  // rare path
                 float fb[Q];
                 nee_populations<L>(p, inl, f, fb, pr.rout, pb.rout);
-                lbm_node<L, ST, ODD, NP, kStage>(p, b, P, bn, nbb, fb, pb, res, kPlain<ST> ? nullptr : &sb, stg, base,
-                                                 false);
+                lbm_node<L, ST, ODD, NP>(p, b, P, bn, nbb, fb, pb, res, kPlain<ST> ? nullptr : &sb);
             }
         }
     }
@@ -731,6 +776,8 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
         // tile: node x - e_q for slot q when that voxel is fluid, else the node
         __syncthreads();
         if (active) {
+            stage_forget(slots);
+            const bool end0 = nee && (x == 0 || x == g.nx - 1), endm = nee && x == 1, endp = nee && x == g.nx - 2;
             // all stage reads first, then the stores (one wait for the reads)
             StageT<ST> v[Q];
 #pragma unroll
@@ -739,10 +786,8 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
             for (int q = 0; q < Q; ++q) {
                 const int r = L::opp[q];
                 const bool fl = q != 0 && nb.fl[r];
-                const int c = q == 0 ? n : nb.n[r];
-                const int xc = fl ? x - L::ex[q] : x;
-                if ((uint32_t)(c - base) < (uint32_t)kTile && !(nee && (xc == 0 || xc == g.nx - 1)))
-                    *pop_at<Q, StageT<ST>>(b.f, q, n) = v[q];
+                const bool end = L::ex[q] == 0 || !fl ? end0 : (L::ex[q] > 0 ? endm : endp);  // the reader's plane
+                if (!slots.outside(r) && !end) *pop_at<Q, StageT<ST>>(b.f, q, n) = v[q];
             }
         }
     }
