@@ -134,15 +134,16 @@ def hbm_probe(mib: int = 2048, reps: int = 5):
 def potential_rates(coupled_steps: int = 10):
     """The potential (Poisson, Eq. 4-5) on the bench electrode. Static solve:
     Laplace with the electrode at -20 thermal voltages, the inlet face at 0
-    and a field-free outlet, Jacobi-PCG from zero to a relative residual of
-    1e-8. Coupled: fused LBM + ion steps with the potential re-solved from the
+    and a field-free outlet, preconditioned CG from zero to a relative residual
+    of 1e-8. Coupled: fused LBM + ion steps with the potential re-solved from the
     current charge (electrode at -4, kappa2 = 0.5, warm start, 1e-6) before
     every step.
     Algorithmic bytes of one CG iteration per fluid node (the iterations of
     the mixed-precision refinement run on FP32 vectors): the stencil kernel
-    reads r, the old direction, the diagonal byte and the six face-neighbour
+    reads z and the old direction, the diagonal byte and the six face-neighbour
     indices and writes the new direction and q = A p (41 B); the update
-    kernel reads x, r, p, q and the diagonal byte and writes x, r (25 B). The
+    kernel reads x, r, p, q, the diagonal byte and the indices (for the block
+    preconditioner's sweeps) and writes x, r, z and the direction (57 B). The
     refinement rounds' FP64 residuals (two or three per solve) are inside the
     timed solve but not in this per-iteration count."""
     import torch
@@ -150,7 +151,7 @@ def potential_rates(coupled_steps: int = 10):
     g, p, _ = P.preset(WORKLOAD)
     s = P.Solver(g, p)
     nf = s.n_fluid
-    per_iter = (4 + 4 + 1 + 24 + 4 + 4) + (16 + 1 + 8)
+    per_iter = (8 + 1 + 24 + 4 + 4) + (16 + 1 + 24 + 16)
     out = {"n_fluid": nf, "algorithmic_bytes_per_node_iter": round(per_iter, 1)}
     pot = P.Potential(psi_electrode=-20.0, x_bc=(P.PSIX_DIRICHLET, P.PSIX_NEUMANN), tol=1e-8,
                       warm_start=False, check_every=16)
@@ -188,12 +189,13 @@ def potential_rates(coupled_steps: int = 10):
     except P.CdiError as exc:
         out["coupled_pnp"] = {"error": str(exc)}
     # the steady ion state on this flow and potential (implicit scheme),
-    # BiCGSTAB to 1e-8; per iteration both species (directions stored
-    # preconditioned): direction 72 B (r, v, p^, diagonal; p^ written), two
-    # operator applications 78 + 70 B (own vectors, neighbour indices, flux
-    # and potential; the second also the diagonal), s^ 56 B, update 120 B per
-    # fluid node
-    per_it_np = 72 + 78 + 56 + 70 + 120
+    # BiCGSTAB to 1e-8; per iteration both species: the two direction kernels
+    # 116 + 100 B (r, v, in the first p; neighbour indices, flux and the
+    # reciprocal diagonals for the preconditioner; p or s, and the FP32
+    # direction written), two operator applications of 76 B (direction, own
+    # vector, neighbour indices, flux; result written), update 112 B per fluid
+    # node
+    per_it_np = 116 + 76 + 100 + 76 + 112
     try:
         s.np_steady(tol=1e-8, max_iter=20, allow_not_converged=True)  # first launches
         res = {}

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, doub
 // (no convergence at -20). The coefficients are formed again from flux and
 // potential where they are needed, 16 bytes a node instead of 48 for stored
 // ones. The sweeps run on the block in LDS; what bounds the direction kernels
-// is their streams (112 and 96 bytes a node) about as much as their arithmetic.
+// is their streams (116 and 100 bytes a node) about as much as their arithmetic.
 // 192^3, 4.2 M nodes, to 1e-10: 141 -> 52 ms, 300 -> 118 iterations of 383 ->
 // 372 us.
 // Nodes per thread of the direction kernels: two. A node's row and its loads

@@ -44,14 +44,14 @@ def kernel_source_hash() -> str:
 
 
 def _variant(name: str):
-    """step_kernel<L, ST, ODD, LBM, NP, STG> -> readable label, or None."""
-    m = re.search(r"step_kernel<cdi::(D2Q9|D3Q19), (\d), (\d), (\d), (\d)(?:, (\d))?>", name)
+    """step_kernel<L, ST, ODD, LBM, NP, STG, PSI> -> readable label, or None."""
+    m = re.search(r"step_kernel<cdi::(D2Q9|D3Q19), (\d), (\d), (\d), (\d)(?:, (\d))?(?:, \d)?>", name)
     if not m:
         return None
     lat, st, odd, lbm, np_, stg = m.groups()
     kind = "fused" if lbm == "1" and np_ == "1" else ("lbm" if lbm == "1" else "np")
     # ion-only steps and moment storage have no AA parity; 2 = pull streaming
-    if kind == "np" or st == "2":
+    if kind == "np" or st in "24":
         parity = ""
     else:
         parity = {"0": " even", "1": " odd", "2": " pull"}[odd]
@@ -263,36 +263,33 @@ def main():
 
 # per-iteration kernels of the two iterative solvers: role and algorithmic
 # bytes per fluid node (the bench's byte model)
-POT_KERNELS = {"pot_dirspmv_kernel": ("direction + A p (stencil), FP32 vectors", 41),
-               "pot_axpy_kernel": ("x, r update, FP32 vectors", 25)}
+POT_KERNELS = {"pot_spmv32_kernel": ("direction + A p (stencil), FP32 vectors", 41),
+               "pot_update32_kernel": ("x, r update, z = M r by block sweeps, FP32 vectors", 57)}
 # the same CG on FP64 vectors (cdi_potential.fp64 = 1, or a round handed over)
-POT64_KERNELS = {"pot_dirspmv_kernel<double>": ("direction + A p (stencil), FP64 vectors", 57),
-                 "pot_axpy_kernel<double>": ("x, r update, FP64 vectors", 49)}
+POT64_KERNELS = {"pot_dirspmv_kernel": ("direction + A p (stencil), FP64 vectors", 57),
+                 "pot_axpy_kernel": ("x, r update, FP64 vectors", 49)}
 # once per refinement round of the potential solve (not per iteration)
 POT_ROUND_KERNELS = {"pot_refine_kernel": ("FP64 residual b - A x, FP32 correction start", 53),
                      "pot_correct_kernel": ("x += FP32 correction", 20)}
-NPS_KERNELS = {"nps_dir_kernel": ("direction p^ = K^-1 p", 72),
-               "nps_apply_kernel<0>": ("v = A p^", 78),
-               "nps_sdir_kernel": ("s^ = K^-1 (r - alpha v)", 56),
-               "nps_apply_kernel<1>": ("t = A s^", 70),
-               "nps_update_kernel": ("x, r update", 120)}
+NPS_KERNELS = {"nps_dir_kernel<0>": ("p, p^ = M p by block sweeps", 116),
+               "nps_apply_kernel<0>": ("v = A p^", 76),
+               "nps_dir_kernel<1>": ("s, s^ = M s by block sweeps", 100),
+               "nps_apply_kernel<1>": ("t = A s^", 76),
+               "nps_update_kernel": ("x, r update", 112)}
 
 
 def _solver_kernel(name: str):
-    m = re.search(r"nps_apply_kernel<[^,>]+, (\d)>", name)
+    m = re.search(r"(nps_apply_kernel|nps_dir_kernel)<[^,>]+, (\d)>", name)
     if m:
-        return f"nps_apply_kernel<{m.group(1)}>"
-    m = re.search(r"(pot_dirspmv_kernel|pot_axpy_kernel)<(?:[^<>]*, )?double>", name)
-    if m:
-        return f"{m.group(1)}<double>"
-    for k in list(POT_KERNELS) + list(POT_ROUND_KERNELS) + list(NPS_KERNELS):
+        return f"{m.group(1)}<{m.group(2)}>"
+    for k in list(POT_KERNELS) + list(POT64_KERNELS) + list(POT_ROUND_KERNELS) + list(NPS_KERNELS):
         if "<" not in k and k in name:
             return k
     return None
 
 
 def summarise_potential(trace, fetch, write, bench_log, copy_mib, commands=(), rdreq=None):
-    """Per-iteration kernels of the potential solve (Jacobi-PCG) and of the
+    """Per-iteration kernels of the potential solve (PCG) and of the
     implicit ion solve (BiCGSTAB): mean duration, HBM bytes per fluid node and
     GB/s over the dispatches that did work (launches after the device-side
     stop return at once and are left out: below 5% of the kernel's longest
@@ -375,7 +372,7 @@ def summarise_potential(trace, fetch, write, bench_log, copy_mib, commands=(), r
           "per fluid node; measured: the HBM counters"
           + (" (reads: the L2's memory read requests by size, exact at every size)." if rq else
              " (reads: FETCH_SIZE times the copy's scale)."), ""]
-    for key, title, kernels in (("cg", "Potential, Eq. 4-5: Jacobi-PCG iterations of the mixed-precision refinement",
+    for key, title, kernels in (("cg", "Potential, Eq. 4-5: PCG iterations of the mixed-precision refinement",
                                  POT_KERNELS),
                                 ("cg64", "Potential: the same CG on FP64 vectors alone (fp64 = 1)", POT64_KERNELS),
                                 ("bicgstab", "Steady ion state (implicit scheme): BiCGSTAB, both species, FP64",
