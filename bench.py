@@ -506,7 +506,7 @@ def main():
                      "algorithmic_bytes_per_node": BYTES_FUSED[FP32_FORM]},
         "fp32": form(FP32_FORM, r32),
         "fp16": form("fp16", rh16),
-        "fp16_dev": form("fp16_dev", r16),
+        "fp16_dev": form(FP32_FORM, r16),  # (tau = 1: held as moments too)
         "moments": form("moments", rmo),
         "device": torch.cuda.get_device_name(0),
     }
