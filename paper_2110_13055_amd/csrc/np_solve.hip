@@ -654,9 +654,9 @@ hipError_t nps_workgroups(int dim, int ntiles, int *G, int *Gd)
     const void *k = dim == 2 ? (const void *)nps_apply_kernel<D2Q9, 1> : (const void *)nps_apply_kernel<D3Q19, 1>;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kTile, 0);
     if (e != hipSuccess) return e;
-    // at most 4 per CU (measured on the 512^3 electrode: 5.68 ms per
-    // iteration at 4, 5.90 at the occupancy limit of 5, 6.05 at 3): fewer
-    // tiles in flight per XCD leave more of its L2 to the neighbours' lines
+    // at most 4 per CU (steady ions at 192^3: 50.2 ms at 4, 55.5 at 6, 54.8 at
+    // 8): fewer tiles in flight per XCD leave more of its L2 to the neighbours'
+    // lines
     if (per_cu > kNpsWorkgroupsPerCU) per_cu = kNpsWorkgroupsPerCU;
     long long g = (long long)cus * (per_cu > 0 ? per_cu : 1);
     g = g < kNpsMaxWorkgroups ? g : kNpsMaxWorkgroups;
