@@ -186,12 +186,20 @@ __device__ __forceinline__ void block_solve(const float (&r)[kBlockTiles], const
     }
 }
 
-// Stop test on |r_k|^2 (the r.r partials of the last axpy); the same
-// decision in every workgroup. Workgroup 0 records it.
-__device__ inline bool stop_test(const PotArgs &a, int k, double *sm)
+// Stop test on |r_k|^2 (the r.r partials of the last update) and beta = rz_k /
+// rz_{k-1}; the same in every workgroup. Workgroup 0 records the decision. The
+// totals come in one pass: one after the other their round trips made up a good
+// part of a small lattice's kernels (a coupled 96x80x88 run 11.15 -> 10.86 ms, a
+// 256^3 solve 9.5 -> 9.1).
+__device__ inline bool stop_test(const PotArgs &a, int k, double *sm, double &beta)
 {
     const int G = gridDim.x;
-    const double rr = region_sum(a.part + kRr * G, G, sm);
+    const double *const regions[3] = {a.part + kRr * G, a.part + (k & 1 ? kRz1 : kRz0) * G,
+                                      a.part + (k & 1 ? kRz0 : kRz1) * G};
+    double t[3];
+    region_sums(regions, G, sm, t);
+    const double rr = t[0];
+    beta = t[1] / t[2];
     const bool bad = !isfinite(rr);
     const bool stop = bad || rr <= a.state[kStTol2Bb];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -213,15 +221,13 @@ __global__ __launch_bounds__(kTile) void pot_dirspmv_kernel(PotArgs a, int k)
 {
     using T = double;
     constexpr int F = 2 * L::D;
-    __shared__ double sm[kTile / 64];
+    __shared__ double sm[3 * (kTile / 64)];
     __shared__ int stop;
     if (stopped(a.state, &stop)) return;
     const int G = gridDim.x;
     double beta = 0.0;
     if (k > 0) {
-        if (stop_test(a, k, sm)) return;
-        beta = region_sum(a.part + (k & 1 ? kRz1 : kRz0) * G, G, sm) /
-               region_sum(a.part + (k & 1 ? kRz0 : kRz1) * G, G, sm);
+        if (stop_test(a, k, sm, beta)) return;
     }
     const T *pold = k & 1 ? a.p2 : a.p;
     T *pnew = k & 1 ? a.p : a.p2;
@@ -283,12 +289,14 @@ __global__ __launch_bounds__(kTile) void pot_dirspmv_kernel(PotArgs a, int k)
 __global__ __launch_bounds__(kTile) void pot_axpy_kernel(PotArgs a, int k)
 {
     using T = double;
-    __shared__ double sm[kTile / 64];
+    __shared__ double sm[2 * (kTile / 64)];
     __shared__ int stop;
     if (stopped(a.state, &stop)) return;
     const int G = gridDim.x;
-    const double rz = region_sum(a.part + (k & 1 ? kRz1 : kRz0) * G, G, sm);
-    const double pq = region_sum(a.part + kPq * G, G, sm);
+    const double *const regions[2] = {a.part + (k & 1 ? kRz1 : kRz0) * G, a.part + kPq * G};
+    double sums[2];
+    region_sums(regions, G, sm, sums);
+    const double rz = sums[0], pq = sums[1];
     if (!(pq > 0.0) || !isfinite(rz / pq)) {  // breakdown: A p has no positive energy
         if (blockIdx.x == 0 && threadIdx.x == 0) a.state[kStDone] = kDoneBreakdown;
         return;
@@ -345,15 +353,15 @@ template <class L, int NBR, int NN>
 __global__ __launch_bounds__(kTile) void pot_spmv32_kernel(PotArgs a, int k)
 {
     constexpr int F = 2 * L::D;
-    __shared__ double sm[kTile / 64];
+    __shared__ double sm[3 * (kTile / 64)];
     __shared__ int stop;
     if (stopped(a.state, &stop)) return;
     const int G = gridDim.x;
     float beta = 0.f;
     if (k > 0) {
-        if (stop_test(a, k, sm)) return;
-        beta = (float)(region_sum(a.part + (k & 1 ? kRz1 : kRz0) * G, G, sm) /
-                       region_sum(a.part + (k & 1 ? kRz0 : kRz1) * G, G, sm));
+        double b;
+        if (stop_test(a, k, sm, b)) return;
+        beta = (float)b;
     }
     const float2 *zp = a.zp;
     int t0, t1;
@@ -414,15 +422,17 @@ template <class L, int NBR, int START>
 __global__ __launch_bounds__(kTile) void pot_update32_kernel(PotArgs a, int k)
 {
     constexpr int F = 2 * L::D, NB = kBlockTiles;
-    __shared__ double sm[kTile / 64];
+    __shared__ double sm[2 * (kTile / 64)];
     __shared__ int stop;
     __shared__ float zs[2][kBlockNodes + 1];
     if (stopped(a.state, &stop)) return;
     const int G = gridDim.x;
     double alpha = 0;
     if (!START) {
-        const double rz = region_sum(a.part + (k & 1 ? kRz1 : kRz0) * G, G, sm);
-        const double pq = region_sum(a.part + kPq * G, G, sm);
+        const double *const regions[2] = {a.part + (k & 1 ? kRz1 : kRz0) * G, a.part + kPq * G};
+        double sums[2];
+        region_sums(regions, G, sm, sums);
+        const double rz = sums[0], pq = sums[1];
         if (!(pq > 0.0) || !isfinite(rz / pq)) {  // breakdown: A p has no positive energy
             if (blockIdx.x == 0 && threadIdx.x == 0) a.state[kStDone] = kDoneBreakdown;
             return;
