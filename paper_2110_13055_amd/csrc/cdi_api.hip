@@ -271,7 +271,7 @@ static bool plain_pops(int st) { return st == kF32 || st == kH16; }
 // part of the result.
 static int held_form(int prec, double tau, int drive, int64_t P)
 {
-    const bool eq = tau == 1.0 && drive == CDI_INLET_OUTLET && P * 16 <= 4294967295LL;
+    const bool eq = tau == 1.0 && drive == CDI_INLET_OUTLET && offsets_fit(kMom, P);
     return eq && (prec == kF32 || prec == kF16) ? kMom : prec;
 }
 
@@ -378,7 +378,11 @@ const float *cur_rref(const cdi_solver *s) { return s->rlive ? s->node.rref[s->r
 int stream_arg(const cdi_solver *s) { return s->pull ? kPull : s->parity; }
 
 // Storage form of the kernels that work on the state.
-int kernel_form(const cdi_solver *s) { return s->st == kMom && s->rlive ? kMomR : s->st; }
+int kernel_form(const cdi_solver *s)
+{
+    if (s->st == kH16 && !offsets_fit(kH16, s->P)) return kH16L;
+    return s->st == kMom && s->rlive ? kMomR : s->st;
+}
 
 // Sets the form the state is held in.
 void set_form(cdi_solver *s, int st)
@@ -837,9 +841,8 @@ int cdi_flow_init(const cdi_geometry *geom, const cdi_params *params, void *vox_
     if (vox_ws_bytes < V.bytes) return fail(CDI_E_BUFFER, "vox_ws too small");
     const int st_kind = params->precision;
     const int64_t P = (n_fluid + kTile - 1) / kTile * kTile;
-    // per-node arrays are addressed with 32-bit byte offsets (16-byte moments)
-    // (the two planes of a direction and its opposite from one base: 2P elements)
-    if (P * (st_kind == kF32 ? 8 : moment_buffers(st_kind) ? 16 : 4) > 4294967295LL)
+    // per-node arrays are addressed with 32-bit byte offsets
+    if (!offsets_fit(st_kind == kH16 ? kH16L : st_kind, P))
         return fail(CDI_E_INVALID,
                     "too many fluid nodes for one instance (limit 2^29 FP32, 2^30 FP16, 2^28 with moment buffers)");
     NodeLayout N = node_layout(node_ws, geom->dim, st_kind, params->streaming == CDI_STREAM_PULL, P,
@@ -1856,7 +1859,7 @@ int step_class(const cdi_solver *s, int mode)
     switch (mode) {
     case kModeFlow: return base + (odd == kPull ? kClassFlowPull : odd ? kClassFlowOdd : kClassFlowEven);
     case kModeFused: return base + (odd == kPull ? kClassFusedPull : odd ? kClassFusedOdd : kClassFusedEven);
-    case kModeIons: return kClassIons;
+    case kModeIons: return kernel_form(s) == kH16L ? kClassIonsL : kClassIons;
     default: return -1;
     }
 }

@@ -183,16 +183,25 @@ struct Bufs {
 // from the emitter's equilibrium with FP32 moment buffers, moments only.
 // kMomR: moments only, with rho - 1 relative to the plane references (see
 // PlaneRef): the kernels of an FP32 instance held as moments once its
-// references have been renewed.
-constexpr int kF32 = 0, kF16 = 1, kMom = 2, kH16 = 3, kMomR = 4, kForms = 5;
+// references have been renewed. kH16L: FP16 populations of an instance beyond
+// 2^29 nodes, whose ion kernels form the concentrations' addresses in 64 bits.
+constexpr int kF32 = 0, kF16 = 1, kMom = 2, kH16 = 3, kMomR = 4, kH16L = 5, kForms = 6;
+// The widest element that a form's kernels address by node with a 32-bit byte
+// offset (ldu, stu): a moment, the concentrations' pair, or one FP32 value.
+constexpr int offset_elem(int form)
+{
+    return form == kF16 || form == kMom || form == kMomR ? 16 : form == kH16L ? 4 : 8;
+}
+// Whether that offset fits for an instance of P nodes.
+constexpr bool offsets_fit(int form, int64_t P) { return P * offset_elem(form) <= 4294967295LL; }
 template <int ST>
 constexpr bool kMoments = ST == kMom || ST == kMomR;  // no populations stored
 template <int ST>
-constexpr bool kRefs = ST == kF32 || ST == kH16 || ST == kMomR;  // relative to the plane references
+constexpr bool kRefs = ST == kF32 || ST == kH16 || ST == kH16L || ST == kMomR;  // relative to the plane references
 template <int ST>
-constexpr bool kPlain = ST == kF32 || ST == kH16;  // populations relative to the plane references
+constexpr bool kPlain = ST == kF32 || ST == kH16 || ST == kH16L;  // populations relative to the plane references
 template <int ST>
-constexpr bool kHalfPop = ST == kF16 || ST == kH16;  // populations stored in FP16
+constexpr bool kHalfPop = ST == kF16 || ST == kH16 || ST == kH16L;  // populations stored in FP16
 
 // One instance of a batched launch.
 constexpr int kModeIdle = 0, kModeFlow = 1, kModeIons = 2, kModeFused = 3;
@@ -203,10 +212,11 @@ struct BatchInst {
 };
 // Step classes of a batched step (kernel variants): per storage form, LBM
 // only or fused by parity (class kClassesPerForm * form + ...; the moment
-// forms have no parity and use the even ones), and ions only.
+// forms have no parity and use the even ones), and ions only (kClassIonsL: of
+// kH16L members).
 constexpr int kClassFlowEven = 0, kClassFlowOdd = 1, kClassFlowPull = 2, kClassFusedEven = 3, kClassFusedOdd = 4,
               kClassFusedPull = 5, kClassesPerForm = 6, kClassIons = kForms * kClassesPerForm,
-              kClasses = kClassIons + 1;
+              kClassIonsL = kClassIons + 1, kClasses = kClassIons + 2;
 
 // Value of the kernels' parity argument for pull streaming (AA uses 0 / 1).
 constexpr int kPull = 2;

@@ -50,6 +50,22 @@ __device__ __forceinline__ void stu(T *base, uint32_t idx, T v)
     *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + idx * (uint32_t)sizeof(T)) = v;
 }
 
+// Both species' concentrations of node n.
+template <int ST>
+__device__ __forceinline__ float2 ld_conc(const float2 *C, uint32_t n)
+{
+    static_assert(ST == kH16L || offset_elem(ST) >= (int)sizeof(float2), "a pair's byte offset has to fit");
+    if constexpr (ST == kH16L) return C[n];
+    else return ldu(C, n);
+}
+
+template <int ST>
+__device__ __forceinline__ void st_conc(float2 *C, uint32_t n, float2 v)
+{
+    if constexpr (ST == kH16L) C[n] = v;
+    else stu(C, n, v);
+}
+
 // No instruction is scheduled across this point: loads written before it are
 // issued before what uses them. (Left alone, the scheduler moves each load down
 // to its use to save registers, two in flight at a time.)
@@ -492,7 +508,7 @@ __device__ inline float gather(const void *F, int P, const Nbrs<L> &nb, int n, i
 {
     const float raw = gather_raw<L, ST, ODD>(F, P, nb, n, i);
     if (ST == kF32) return raw;
-    if (ST == kH16) return raw * p.hs_inv;
+    if (kPlain<ST>) return raw * p.hs_inv;
     const int j = L::opp[i];
     return from_emitter<L, ST>(raw * p.hs_inv, i, i != 0 && nb.fl[j], ldu(M, (uint32_t)(i == 0 ? n : nb.n[j])), p, pr);
 }

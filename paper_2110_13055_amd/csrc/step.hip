@@ -48,7 +48,7 @@ namespace {
 // and a global load into one generic-address access (which goes through the
 // vector memory path and waits on both counters).
 template <class L, int ST, int ODD, int LBM, int NP>
-constexpr bool kStageOdd = LBM && ODD == 1 && (ST == kF32 || ST == kH16);
+constexpr bool kStageOdd = LBM && ODD == 1 && kPlain<ST>;
 
 template <int ST>
 using StageT = typename std::conditional<kHalfPop<ST>, uint16_t, float>::type;  // FP16 as its bits
@@ -219,7 +219,7 @@ __device__ __attribute__((always_inline)) inline void lbm_node(const Phys &p, co
     const EqTerms eq = eq_terms(drho, rho, ux, uy, uz, p.linear_eq);
     const float om = p.omega;
     // FP16 populations are stored times hs
-    const float sc = ST == kH16 ? p.hs : 1.f;
+    const float sc = kPlain<ST> && kHalfPop<ST> ? p.hs : 1.f;
     if (kPlain<ST> && om == 1.f && !p.forced) {
         // tau = 1: BGK (Eq. 8) relaxes every population to the equilibrium
 #pragma unroll
@@ -363,7 +363,7 @@ __device__ __forceinline__ void ion_faces_wide(const Grid &g, const Phys &p, con
         }
         const float sg = (k & 1) ? -1.f : 1.f;
         const float h = 0.25f * sg * ((axis == 0 ? j0 : (axis == 1 ? j1 : j2)) + jN);
-        const float2 cm = ldu(b.Cin, (uint32_t)m);
+        const float2 cm = ld_conc<ST>(b.Cin, (uint32_t)m);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const float hs = axis == 0 ? h + sg * p.hr[s] : h, cp = s ? c1 : c0, cn = s ? cm.y : cm.x;
@@ -420,7 +420,7 @@ __device__ __forceinline__ void ion_end_face(const Grid &g, const Phys &p, const
             jN = ldu(b.jin, (uint32_t)m);
         }
         if (psi) dpsi = ldu(p.psi, (uint32_t)m) - psiP;
-        const float2 cm = ldu(b.Cin, (uint32_t)m);
+        const float2 cm = ld_conc<ST>(b.Cin, (uint32_t)m);
 #pragma unroll
         for (int s = 0; s < 2; ++s)
             f.out[s] += sg_flux(p.D[s], 2.f * p.invD[s], 0.25f * (jP0 + jN) * sg - hzD[s] * dpsi, cP[s], s ? cm.y : cm.x);
@@ -549,7 +549,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
     float2 cn[F];
     float jn[F], psin[F];
     if (NP && active) {
-        const float2 c = ldu(b.Cin, (uint32_t)n);
+        const float2 c = ld_conc<ST>(b.Cin, (uint32_t)n);
         cP[0] = c.x;
         cP[1] = c.y;
         elo = ldu(b.Clin, (uint32_t)n);
@@ -566,7 +566,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
             cn[k] = make_float2(0.f, 0.f);
             jn[k] = 0.f;
             if (nb.fl[k + 1]) {
-                cn[k] = ldu(b.Cin, q);
+                cn[k] = ld_conc<ST>(b.Cin, q);
                 if (kEarlyJ) jn[k] = ldu(b.jin + (size_t)(k >> 1) * P, q);
             }
             psin[k] = kEarlyPsi && p.psi ? ldu(p.psi, q) : 0.f;
@@ -667,7 +667,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
             dsums.add_to(sums);
         } else if (do_flow) {
             if (kStage) {
-                const float sc = ST == kH16 ? p.hs_inv : 1.f;
+                const float sc = kHalfPop<ST> ? p.hs_inv : 1.f;
                 StageT<ST> raw[Q];
                 staged_gather<L, ST>(b.f, nb, stg, slots, raw);
                 stage_forget(slots);
@@ -729,7 +729,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
         float e0, e1;
         const float c0 = two_sum(cP[0], lo_decode(__low2half(elo)) - p.dt * (fx.out[0] + fa[0]), e0);
         const float c1 = two_sum(cP[1], lo_decode(__high2half(elo)) - p.dt * (fx.out[1] + fa[1]), e1);
-        stu(b.Cout, (uint32_t)n, make_float2(c0, c1));
+        st_conc<ST>(b.Cout, (uint32_t)n, make_float2(c0, c1));
         stu(b.Clout, (uint32_t)n, __halves2half2(lo_encode(e0), lo_encode(e1)));
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -897,6 +897,10 @@ size_t cap_lds(int pad)
     return (size_t)pad > stage ? (size_t)pad - stage : 0;
 }
 
+// Form of the flow-only kernels, which read no concentrations.
+template <int ST>
+constexpr int kFlowForm = ST == kH16L ? kH16 : ST;
+
 template <class L, int ST>
 void launch_batch_t(int cls, const BatchInst *inst, const int2 *tiles, int ntiles, int wg, int pad,
                     hipStream_t s)
@@ -909,9 +913,9 @@ void launch_batch_t(int cls, const BatchInst *inst, const int2 *tiles, int ntile
             batch_kernel<L, ST, 0, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles);
     } else {
         switch (cls) {
-        case kClassFlowEven: batch_kernel<L, ST, 0, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-        case kClassFlowOdd: batch_kernel<L, ST, 1, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-        case kClassFlowPull: batch_kernel<L, ST, kPull, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        case kClassFlowEven: batch_kernel<L, kFlowForm<ST>, 0, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        case kClassFlowOdd: batch_kernel<L, kFlowForm<ST>, 1, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
+        case kClassFlowPull: batch_kernel<L, kFlowForm<ST>, kPull, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
         case kClassFusedEven: batch_kernel<L, ST, 0, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
         case kClassFusedOdd: batch_kernel<L, ST, 1, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
         default: batch_kernel<L, ST, kPull, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
@@ -949,9 +953,9 @@ void launch_mode(int lbm, int np, const Grid &g, const Phys &p, const Bufs &b, h
     if (lbm && np)
         launch_t<L, ST, ODD, 1, 1>(g, p, b, s);
     else if (lbm)
-        launch_t<L, ST, ODD, 1, 0>(g, p, b, s);
+        launch_t<L, kFlowForm<ST>, ODD, 1, 0>(g, p, b, s);
     else
-        launch_t<L, kF32, 0, 0, 1>(g, p, b, s);
+        launch_t<L, ST == kH16L ? kH16L : kF32, 0, 0, 1>(g, p, b, s);
 }
 
 template <class L, int ST>
@@ -977,6 +981,7 @@ void launch_prec(int st, int odd, int lbm, int np, const Grid &g, const Phys &p,
     case kMom: launch_form<L, kMom>(odd, lbm, np, g, p, b, s); break;
     case kMomR: launch_form<L, kMomR>(odd, lbm, np, g, p, b, s); break;
     case kH16: launch_form<L, kH16>(odd, lbm, np, g, p, b, s); break;
+    case kH16L: launch_form<L, kH16L>(odd, lbm, np, g, p, b, s); break;
     case kF16: launch_form<L, kF16>(odd, lbm, np, g, p, b, s); break;
     default: launch_form<L, kF32>(odd, lbm, np, g, p, b, s); break;
     }
@@ -990,11 +995,16 @@ void launch_batch_l(int cls, const BatchInst *inst, const int2 *tiles, int ntile
         batch_kernel<L, kF32, 0, 0, 1><<<wg, kTile, (size_t)pad, s>>>(inst, tiles, ntiles);
         return;
     }
+    if (cls == kClassIonsL) {
+        batch_kernel<L, kH16L, 0, 0, 1><<<wg, kTile, (size_t)pad, s>>>(inst, tiles, ntiles);
+        return;
+    }
     const int k = cls % kClassesPerForm;
     switch (cls / kClassesPerForm) {
     case kMom: launch_batch_t<L, kMom>(k, inst, tiles, ntiles, wg, pad, s); break;
     case kMomR: launch_batch_t<L, kMomR>(k, inst, tiles, ntiles, wg, pad, s); break;
     case kH16: launch_batch_t<L, kH16>(k, inst, tiles, ntiles, wg, pad, s); break;
+    case kH16L: launch_batch_t<L, kH16L>(k, inst, tiles, ntiles, wg, pad, s); break;
     case kF16: launch_batch_t<L, kF16>(k, inst, tiles, ntiles, wg, pad, s); break;
     default: launch_batch_t<L, kF32>(k, inst, tiles, ntiles, wg, pad, s); break;
     }
