@@ -275,10 +275,6 @@ __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, doub
 // compute unit (per iteration of 4.2 M nodes, p^ and s^: 124 and 109 us at four,
 // 95 and 72 at two, 108 and 87 at one; capped at 168 or 128 registers the four
 // spill, 148 and 95, 231 and 220).
-#ifndef SWEEPS
-#define SWEEPS 6
-#endif
-constexpr int kSweeps = SWEEPS;
 constexpr int kDirNodes = 2, kDirThreads = kBlockNodes / kDirNodes;
 
 template <class L>
@@ -346,12 +342,14 @@ template <class L>
 __device__ __forceinline__ void block_solve(const float (&r)[kDirNodes][2], const BlockRows<L> &b,
                                             float2 (*zs)[kBlockNodes], float (&z)[kDirNodes][2])
 {
+    constexpr ChebCoef c = cheb_coef();
+    float d[kDirNodes][2];
 #pragma unroll
     for (int j = 0; j < kDirNodes; ++j)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) z[j][s] = r[j][s] * b.dinv[j][s];
+        for (int s = 0; s < 2; ++s) z[j][s] = d[j][s] = c.first * (r[j][s] * b.dinv[j][s]);
 #pragma unroll
-    for (int k = 1; k < kSweeps; ++k) {
+    for (int k = 1; k < kChebSteps; ++k) {
         float2 *const q = zs[k & 1];
 #pragma unroll
         for (int j = 0; j < kDirNodes; ++j) q[j * kDirThreads + threadIdx.x] = make_float2(z[j][0], z[j][1]);
@@ -366,7 +364,10 @@ __device__ __forceinline__ void block_solve(const float (&r)[kDirNodes][2], cons
                 y[1] = fmaf(b.be[j][1][f], v.y, y[1]);
             }
 #pragma unroll
-            for (int s = 0; s < 2; ++s) z[j][s] = b.dinv[j][s] * y[s];
+            for (int s = 0; s < 2; ++s) {
+                d[j][s] = fmaf(c.r[k], fmaf(b.dinv[j][s], y[s], -z[j][s]), c.d[k] * d[j][s]);
+                z[j][s] += d[j][s];
+            }
             keep_order();  // one node's gathers at a time (all at once take 48 more registers)
         }
     }
