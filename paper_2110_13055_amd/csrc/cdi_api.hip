@@ -1520,10 +1520,12 @@ int np_solve(cdi_solver *s, double idt, double tol, int32_t max_iter, void *ws, 
     a.di = W.di;
     a.part = W.part;
     a.state = W.state;
-    HIPCHK(nps_workgroups(s->dim, s->ntiles, &a.G, a.Gd));
+    HIPCHK(nps_workgroups(s->dim, s->ntiles, &a.G));
     HIPCHK(launch_nps_setup(s->dim, a, tol, s->stream));
     double st[kNsSlots];
     if ((rc = d2h(s, st, W.state, sizeof st)) != CDI_OK) return rc;
+    a.plain = nps_plain(st[kNsPe]);
+    HIPCHK(nps_dir_workgroups(s->dim, s->ntiles, a.plain, a.Gd));
     int k = 0;
     while (st[kNsDone] == 0 && k < max_iter) {
         const int n = std::min(32, max_iter - k);

@@ -189,6 +189,7 @@ __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
     int t0, t1;
     tile_range(a.g.P / kTile, t0, t1);
     double bb[2] = {0, 0}, rho[2] = {0, 0}, rr[2] = {0, 0};
+    float pe = 0.f;
     for (int t = t0; t < t1; ++t) {
         const int n = t * kTile + threadIdx.x;
         double xv[2] = {0, 0}, rv[2] = {0, 0};
@@ -205,7 +206,10 @@ __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
                 double ax = (c.diag[s] + a.idt) * xv[s];
 #pragma unroll
                 for (int k = 0; k < 2 * L::D; ++k)
-                    if (c.m[k] >= 0) ax -= (double)c.be[s][k] * (double)of_species(cN[k], s);
+                    if (c.m[k] >= 0) {
+                        ax -= (double)c.be[s][k] * (double)of_species(cN[k], s);
+                        pe = fmaxf(pe, fabsf(c.al[s][k] - c.be[s][k]) * a.p.invD[s]);
+                    }
                 const double rhs = a.idt * xv[s] + c.b[s];
                 rv[s] = rhs - ax;
                 const float d = (float)(c.diag[s] + a.idt);
@@ -233,11 +237,17 @@ __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
             reg(a, kTt, s)[blockIdx.x] = blockIdx.x == 0 ? 1.0 : 0.0;
         }
     }
+    const double s_pe = wg_max(pe, sm);
+    if (threadIdx.x == 0) reg(a, kRho1, 0)[blockIdx.x] = s_pe;  // (free until the first update)
 }
 
 __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, double tol)
 {
     __shared__ double sm[kTile / 64];
+    float pe = 0.f;
+    for (int k = threadIdx.x; k < G; k += blockDim.x) pe = fmaxf(pe, (float)reg(a, kRho1, 0)[k]);
+    const double s_pe = wg_max(pe, sm);
+    if (threadIdx.x == 0) a.state[kNsPe] = s_pe;
     for (int s = 0; s < 2; ++s) {
         const double bb = region_sum(a.part + ((size_t)kBb * 2 + s) * G, G, sm);
         const double rr = region_sum(a.part + ((size_t)kRr * 2 + s) * G, G, sm);
@@ -254,22 +264,38 @@ __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, doub
 }
 
 // The preconditioner: M is block diagonal over blocks of kBlockNodes
-// consecutive nodes (16 x 16 x 7 voxels of a brick at porosity 0.6), in a
-// block the kChebSteps-th iterate of the Chebyshev iteration for D^-1 A_b z =
-// D^-1 r on [kChebLow, 2], from z = 0 (D the diagonal; what leaves a cell
-// enters its neighbours, so that the columns of A D^-1 - I sum to at most 1
-// and the spectrum ends at 2), on FP32 numbers, with r scaled by a power of two
-// per solve (which scales M). The blocks take the cells' own coefficients:
-// BiCGSTAB needs 0.4 of the diagonal's iterations (207 and 249 -> 89 and 91 for
-// the two ions on a 96^3 electrode at porosity 0.6 in the ramp's field, 249 and
-// 263 -> 98 and 101 with an electrode at -20 thermal voltages), where a
-// diffusion-only block does as well in weak fields and fails in steep ones
-// (no convergence at -20). The coefficients are formed again from flux and
+// consecutive nodes (16 x 16 x 7 voxels of a brick at porosity 0.6), in a block
+// a few sweeps towards A_b z = r from z = 0, on FP32 numbers, with r scaled by a
+// power of two per solve (which scales M). With A_b = D - O (D the diagonal, O >=
+// 0): what leaves a cell enters its neighbours, so that the columns of O D^-1 sum
+// to at most 1 and the eigenvalues of D^-1 A_b lie in the disc |lambda - 1| <= 1.
+// They are real, in (0, 2), without drift; a drift adds imaginary parts of up
+// to half of its cell Peclet number.
+//   Chebyshev: the kChebSteps-th iterate of the Chebyshev iteration for D^-1 A_b
+//   on [kChebLow, 2]. Its residual polynomial stays below 1 in the ellipse with
+//   these foci that goes through 0, whose half height is 0.447, and reaches 16
+//   at 1 +- i. Taken while the largest |Pe| of the faces is below kChebMaxPe,
+//   twice that height.
+//   plain: z <- D^-1 (r + O z), kPlainSweeps terms of the Neumann series. O D^-1 is
+//   not negative and its powers' columns sum to at most 1: no drift amplifies. An
+//   odd number, as after an even one nothing is left of lambda = 2.
+// Iterations and ms of steady solves to 1e-10 (64^3 at porosity 0.6; the
+// diagonal took 90 to 290 iterations, whatever the drift): largest |Pe| 0.36
+// Chebyshev 102 and 5.7, plain 90 and 5.1; 192^3 at |Pe| 0.3: 108 and 49, 123 and
+// 57; 0.9: 79 and 4.3, 74 and 4.4; 3.6: 51 and 2.9, 57 and 3.4; 9 and 60:
+// Chebyshev breaks down, 42 and 2.6, 25 and 1.5; an electrode at -5 and -20
+// thermal voltages: 104 and 5.8, 105 and 5.9 against 116 and 6.5, 105 and 6.0. (5, 6, 7 and 10 plain sweeps at |Pe| 4, 96^3:
+// 58, 49, 48 and 41 iterations, nine 42.) The blocks take the cells' own
+// coefficients: a diffusion-only block does as well in weak fields and fails
+// in steep ones (no convergence at -20). The coefficients are formed again from flux and
 // potential where they are needed, 16 bytes a node instead of 48 for stored
 // ones. The sweeps run on the block in LDS; what bounds the direction kernels
 // is their streams (116 and 100 bytes a node) about as much as their arithmetic.
 // 192^3, 4.2 M nodes, to 1e-10: 141 -> 52 ms, 300 -> 118 iterations of 383 ->
 // 372 us.
+constexpr double kChebMaxPe = 0.89;
+constexpr int kPlainSweeps = 9;
+
 // Nodes per thread of the direction kernels: two. A node's row and its loads
 // take about 45 registers; at four a thread only two workgroups of 256 fit a
 // compute unit (per iteration of 4.2 M nodes, p^ and s^: 124 and 109 us at four,
@@ -337,8 +363,8 @@ __device__ __forceinline__ void block_rows(const NpsArgs &a, int base, BlockRows
     }
 }
 
-// z = M r of this thread's nodes. zs: two buffers of a block.
-template <class L>
+// z = M r of this thread's nodes, PLAIN or Chebyshev sweeps. zs: two buffers of a block.
+template <class L, int PLAIN>
 __device__ __forceinline__ void block_solve(const float (&r)[kDirNodes][2], const BlockRows<L> &b,
                                             float2 (*zs)[kBlockNodes], float (&z)[kDirNodes][2])
 {
@@ -347,9 +373,9 @@ __device__ __forceinline__ void block_solve(const float (&r)[kDirNodes][2], cons
 #pragma unroll
     for (int j = 0; j < kDirNodes; ++j)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) z[j][s] = d[j][s] = c.first * (r[j][s] * b.dinv[j][s]);
+        for (int s = 0; s < 2; ++s) z[j][s] = d[j][s] = (PLAIN ? 1.f : c.first) * (r[j][s] * b.dinv[j][s]);
 #pragma unroll
-    for (int k = 1; k < kChebSteps; ++k) {
+    for (int k = 1; k < (PLAIN ? kPlainSweeps : kChebSteps); ++k) {
         float2 *const q = zs[k & 1];
 #pragma unroll
         for (int j = 0; j < kDirNodes; ++j) q[j * kDirThreads + threadIdx.x] = make_float2(z[j][0], z[j][1]);
@@ -365,6 +391,10 @@ __device__ __forceinline__ void block_solve(const float (&r)[kDirNodes][2], cons
             }
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
+                if (PLAIN) {
+                    z[j][s] = b.dinv[j][s] * y[s];
+                    continue;
+                }
                 d[j][s] = fmaf(c.r[k], fmaf(b.dinv[j][s], y[s], -z[j][s]), c.d[k] * d[j][s]);
                 z[j][s] += d[j][s];
             }
@@ -375,7 +405,7 @@ __device__ __forceinline__ void block_solve(const float (&r)[kDirNodes][2], cons
 
 // The two halves of an iteration that make a direction. WHICH 0 (dir): the
 // stop test, p and p^ = M p; WHICH 1 (sdir): s = r - alpha v and s^ = M s.
-template <class L, int WHICH>
+template <class L, int WHICH, int PLAIN>
 __global__ __launch_bounds__(kDirThreads) void nps_dir_kernel(NpsArgs a, int k)
 {
     __shared__ double sm[12 * (kDirThreads / 64)];
@@ -454,7 +484,7 @@ __global__ __launch_bounds__(kDirThreads) void nps_dir_kernel(NpsArgs a, int k)
         }
         keep_order();
         __syncthreads();  // the sweeps of the block before may still read zs
-        block_solve<L>(rf, rows, zs, z);
+        block_solve<L, PLAIN>(rf, rows, zs, z);
 #pragma unroll
         for (int j = 0; j < kDirNodes; ++j) {
             const int n = base + j * kDirThreads + (int)threadIdx.x;
@@ -645,7 +675,9 @@ __global__ __launch_bounds__(kTile) void nps_rates_kernel(Grid g, Phys p, const 
 
 uint64_t nps_part_doubles() { return (uint64_t)kRegions * 2 * kNpsMaxWorkgroups; }
 
-hipError_t nps_workgroups(int dim, int ntiles, int *G, int *Gd)
+int nps_plain(double pe) { return !(pe <= kChebMaxPe); }
+
+hipError_t nps_workgroups(int dim, int ntiles, int *G)
 {
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -661,14 +693,25 @@ hipError_t nps_workgroups(int dim, int ntiles, int *G, int *Gd)
     long long g = (long long)cus * (per_cu > 0 ? per_cu : 1);
     g = g < kNpsMaxWorkgroups ? g : kNpsMaxWorkgroups;
     *G = (int)(ntiles < g ? ntiles : g);
-    // the direction kernels: as many workgroups as are resident together, none
-    // left over for a second wave
-    int fit = 0;
-    e = hipSuccess;
+    return hipSuccess;
+}
+
+template <class L>
+const void *dir_kernel(int which, int plain)
+{
+    return plain ? (which ? (const void *)nps_dir_kernel<L, 1, 1> : (const void *)nps_dir_kernel<L, 0, 1>)
+                 : (which ? (const void *)nps_dir_kernel<L, 1, 0> : (const void *)nps_dir_kernel<L, 0, 0>);
+}
+
+// As many workgroups as are resident together, none left over for a second wave.
+hipError_t nps_dir_workgroups(int dim, int ntiles, int plain, int *Gd)
+{
+    int dev = 0, cus = 0, fit = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     for (int w = 0; w < 2 && e == hipSuccess; ++w) {
-        const void *const d[2][2] = {{(const void *)nps_dir_kernel<D2Q9, 0>, (const void *)nps_dir_kernel<D2Q9, 1>},
-                                     {(const void *)nps_dir_kernel<D3Q19, 0>, (const void *)nps_dir_kernel<D3Q19, 1>}};
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, d[dim == 3][w], kDirThreads, 0);
+        const void *k = dim == 2 ? dir_kernel<D2Q9>(w, plain) : dir_kernel<D3Q19>(w, plain);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, k, kDirThreads, 0);
         const long long most = (long long)cus * std::min(std::max(fit, 1), kNpsWorkgroupsPerCU);
         const long long blocks = ((long long)ntiles + kBlockTiles - 1) / kBlockTiles;
         Gd[w] = (int)std::min(std::min(blocks, most), (long long)kNpsMaxWorkgroups);
@@ -686,19 +729,21 @@ hipError_t launch_nps_setup(int dim, const NpsArgs &a, double tol, hipStream_t s
     return hipGetLastError();
 }
 
+template <class L, int PLAIN>
+void iter_l(const NpsArgs &a, int k, hipStream_t s)
+{
+    nps_dir_kernel<L, 0, PLAIN><<<a.Gd[0], kDirThreads, 0, s>>>(a, k);
+    nps_apply_kernel<L, 0><<<a.G, kTile, 0, s>>>(a);
+    nps_dir_kernel<L, 1, PLAIN><<<a.Gd[1], kDirThreads, 0, s>>>(a, k);
+    nps_apply_kernel<L, 1><<<a.G, kTile, 0, s>>>(a);
+}
+
 hipError_t launch_nps_iter(int dim, const NpsArgs &a, int k, hipStream_t s)
 {
-    if (dim == 2) {
-        nps_dir_kernel<D2Q9, 0><<<a.Gd[0], kDirThreads, 0, s>>>(a, k);
-        nps_apply_kernel<D2Q9, 0><<<a.G, kTile, 0, s>>>(a);
-        nps_dir_kernel<D2Q9, 1><<<a.Gd[1], kDirThreads, 0, s>>>(a, k);
-        nps_apply_kernel<D2Q9, 1><<<a.G, kTile, 0, s>>>(a);
-    } else {
-        nps_dir_kernel<D3Q19, 0><<<a.Gd[0], kDirThreads, 0, s>>>(a, k);
-        nps_apply_kernel<D3Q19, 0><<<a.G, kTile, 0, s>>>(a);
-        nps_dir_kernel<D3Q19, 1><<<a.Gd[1], kDirThreads, 0, s>>>(a, k);
-        nps_apply_kernel<D3Q19, 1><<<a.G, kTile, 0, s>>>(a);
-    }
+    if (dim == 2)
+        a.plain ? iter_l<D2Q9, 1>(a, k, s) : iter_l<D2Q9, 0>(a, k, s);
+    else
+        a.plain ? iter_l<D3Q19, 1>(a, k, s) : iter_l<D3Q19, 0>(a, k, s);
     nps_update_kernel<<<a.G, kTile, 0, s>>>(a, k);
     return hipGetLastError();
 }

@@ -21,7 +21,8 @@ enum {
     kNsThr = 8,     // + s
     kNsDone = 10,   // 0 running, 1 converged, 2 diverged / breakdown
     kNsScale = 11,  // + s: the power of two that brings |r_0| to 1 to 2
-    kNsSlots = 13
+    kNsPe = 13,     // largest |Pe| of a face between fluid cells
+    kNsSlots = 14
 };
 
 struct NpsArgs {
@@ -29,7 +30,8 @@ struct NpsArgs {
     Phys p;
     const float2 *C;   // concentrations of the state the step starts from
     const float *j;    // frozen advecting mass flux (d planes of P)
-    int G, Gd[2];      // workgroups (nps_workgroups)
+    int G, Gd[2];      // workgroups (nps_workgroups, nps_dir_workgroups)
+    int plain;         // the preconditioner's sweeps (nps_plain), set after the set-up
     double idt;        // 1 / dt of a backward-Euler step, 0 for the steady state
     // FP64 vectors of P, both species of a node side by side (r holds s between
     // the halves of an iteration), and the preconditioned directions
@@ -43,8 +45,12 @@ struct NpsArgs {
 
 uint64_t nps_part_doubles();
 // Workgroups of the kernels that leave partial sums, and of the two direction kernels.
-hipError_t nps_workgroups(int dim, int ntiles, int *G, int *Gd);
-// x = C, r = rhat = C idt + b - A x, reciprocal diagonals, |rhs|^2, rho_0 and the state.
+hipError_t nps_workgroups(int dim, int ntiles, int *G);
+hipError_t nps_dir_workgroups(int dim, int ntiles, int plain, int *Gd);
+// Whether a system whose largest |Pe| is pe takes plain sweeps (np_solve.hip).
+int nps_plain(double pe);
+// x = C, r = rhat = C idt + b - A x, reciprocal diagonals, |rhs|^2, rho_0, the largest
+// |Pe| and the state.
 hipError_t launch_nps_setup(int dim, const NpsArgs &a, double tol, hipStream_t s);
 // BiCGSTAB iteration k (direction, A p, s, A s, update); returns at once after the stop.
 hipError_t launch_nps_iter(int dim, const NpsArgs &a, int k, hipStream_t s);

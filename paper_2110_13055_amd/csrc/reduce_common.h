@@ -31,6 +31,19 @@ __device__ inline double wg_sum(double v, double *sm)
     return s;
 }
 
+// Largest v over the workgroup, returned to every thread.
+__device__ inline double wg_max(double v, double *sm)
+{
+    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __syncthreads();  // sm may still be read from a previous call
+    if (lane == 0) sm[wave] = v;
+    __syncthreads();
+    double s = sm[0];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) s = fmax(s, sm[w]);
+    return s;
+}
+
 // Whether the solve has stopped (state[slot] != 0), read once per workgroup
 // so that all its waves take the same branch.
 __device__ inline bool stopped_at(const double *state, int slot, int *flag)
@@ -75,8 +88,9 @@ __device__ inline double region_sum(const double *part, int G, double *sm)
 }
 
 // Chebyshev sweeps of the solvers' block preconditioners: kChebSteps steps on
-// [kChebLow, 2] (the spectrum of the diagonally scaled matrix ends at 2) over
-// blocks of kBlockNodes consecutive nodes. Whole solves (steady ions at 192^3,
+// [kChebLow, 2] over blocks of kBlockNodes consecutive nodes. The spectrum of the
+// diagonally scaled matrix is real and ends at 2 for the potential and for ions
+// without drift; with drift np_solve.hip says how far they may be taken. Whole solves (steady ions at 192^3,
 // Laplace at 256^3, a coupled 96x80x88 run): six steps on [0.1, 2] 50.2, 9.4 and
 // 11.9 ms; four on [0.2, 2] 64.6, 10.6 and 12.3; eight on [0.06, 2] 48.9, 9.2 and 12.2.
 constexpr int kBlockTiles = 4, kBlockNodes = kBlockTiles * kTile;

@@ -1,0 +1,73 @@
+"""Implicit ion solves where the drift dominates (largest cell Peclet number of
+1.5 to 70; the block preconditioner's sweeps change at 0.89): a porous
+electrode's flow, a steep ramp, and recirculation in a channel. Against the FP64
+oracle, which solves with the diagonal, to the implicit tests' bar (the
+coefficients are FP32: 1e-4 of the largest concentration), and in no more
+iterations than the diagonal takes to the same tolerance (the oracle's count is
+the sum over the species, the solver's the larger one)."""
+import numpy as np
+import pytest
+
+from helpers import oracle_solver
+
+pytestmark = pytest.mark.gpu
+
+P = pytest.importorskip("paper_2110_13055_amd")
+from paper_2110_13055_amd import _lib as L  # noqa: E402
+from paper_2110_13055_amd import Geometry, Params, Solver  # noqa: E402
+
+
+def solve_both(s, o, dt):
+    if dt is None:
+        it = s.np_steady(tol=1e-10, max_iter=1000)
+        rc, diagonal = o.np_steady(tol=1e-10)
+    else:
+        it = s.np_implicit(dt, 2, tol=1e-10, max_iter=1000)
+        rc, diagonal = o.np_implicit(dt, 2, tol=1e-10)
+    print(f"{it} iterations, the diagonal {diagonal / 2}", flush=True)
+    assert rc == 0 and it <= diagonal / 2
+    assert np.abs(s.concentration() - o.conc()).max() <= 1e-4 * np.abs(o.conc()).max()
+
+
+@pytest.mark.parametrize("dt", [None, 20.0], ids=["steady", "dt20"])
+@pytest.mark.parametrize("D,pe", [((0.01, 0.015), (1, 4)), ((0.002, 0.003), (5, 20)), ((0.0003, 0.0004), (30, 85))])
+def test_flow_dominated(D, pe, dt):
+    g = Geometry(dim=3, nx=48, ny=45, nz=50, kind=L.SPHERES, porosity=0.6, r_min=3.0, r_max=6.0, seed=3)
+    p = Params(u_in=2e-3, D=D, dpsi_vt=5.0)
+    s, o = Solver(g, p), oracle_solver(g, p)
+    s.flow_steps(300)
+    o.flow_steps(300)
+    o.freeze_velocity()
+    assert pe[0] <= np.abs(s.np_velocity()).max() / D[0] <= pe[1]
+    solve_both(s, o, dt)
+
+
+@pytest.mark.parametrize("dt", [None, 20.0], ids=["steady", "dt20"])
+def test_steep_ramp(dt):
+    g = Geometry(dim=3, nx=48, ny=45, nz=50, kind=L.SPHERES, porosity=0.6, r_min=3.0, r_max=6.0, seed=3)
+    p = Params(u_in=1e-3, dpsi_vt=400.0)
+    s, o = Solver(g, p), oracle_solver(g, p)
+    s.flow_steps(100)
+    o.flow_steps(100)
+    o.freeze_velocity()
+    solve_both(s, o, dt)
+
+
+@pytest.mark.parametrize("pe", [1.5, 5.0, 25.0])
+def test_recirculation(pe):
+    # vortices of 32 cells in a channel with an absorbing outlet and a few
+    # electrode voxels; j is a discrete curl: no face balance is disturbed
+    nx, ny, D = 64, 32, 0.02
+    lab = np.zeros((1, ny, nx), np.uint8)
+    lab[0, 5::8, 20:44:8] = 1
+    g = Geometry(dim=2, nx=nx, ny=ny, nz=1, kind=L.USER_LABELS, user_labels=lab)
+    p = Params(u_in=1e-3, Ka=1e-3, D=(D, 1.2 * D), np_x_bc=L.NPX_DIRICHLET, c_out=0.2)
+    y, x = np.mgrid[-1:ny + 1, -1:nx + 1]
+    psi = np.sin(2 * np.pi * y / 32) * np.where((x > 1) & (x < nx - 2), np.sin(2 * np.pi * (x - 2) / 30), 0.0)
+    u = (psi[2:, 1:-1] - psi[:-2, 1:-1]) / 2, -(psi[1:-1, 2:] - psi[1:-1, :-2]) / 2
+    j = np.stack([a[lab[0] == 0] for a in u])
+    j *= pe * D / np.abs(j).max()
+    s, o = Solver(g, p), oracle_solver(g, p)
+    s.set_np_velocity(j.astype(np.float32))
+    o.set_velocity(j.astype(np.float32).astype(np.float64))
+    solve_both(s, o, None)
