@@ -364,7 +364,7 @@ struct SnapHeader {
     uint64_t magic, bytes;
     int32_t parity, mcur, jcur, ccur, jstate, fcur;
     int32_t psi_on;  // the potential in use is the field in the state (else the ramp)
-    int32_t rstate;  // rcur | rpend << 1 | rlive << 2 | (FP32 held as moments) << 3 |
+    int32_t rstate;  // rcur | rpend << 1 | rlive << 2 | (populations held as moments) << 3 |
                      // (concentrations in pairs) << 4
     int64_t flow_steps, np_steps, nf;
 };
@@ -1662,7 +1662,7 @@ int cdi_snapshot(cdi_solver *s, void *host, uint64_t bytes)
     if (bytes < sizeof(SnapHeader) + s->node.state_bytes) return fail(CDI_E_BUFFER, "snapshot buffer too small");
     SnapHeader h{kSnapMagic, s->node.state_bytes, s->parity, s->mcur, s->jcur, s->ccur, s->jstate, s->fcur,
                  s->p.psi != nullptr,
-                 s->rcur | (s->rpend << 1) | (s->rlive << 2) | ((s->prec == kF32 && s->st == kMom) << 3) | (1 << 4),
+                 s->rcur | (s->rpend << 1) | (s->rlive << 2) | ((s->prec != kMom && s->st == kMom) << 3) | (1 << 4),
                  s->flow_steps, s->np_steps, s->nf};
     std::memcpy(host, &h, sizeof h);
     return d2h(s, (uint8_t *)host + sizeof h, s->node.base, s->node.state_bytes);
@@ -1677,12 +1677,11 @@ int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes)
     if (h.magic != kSnapMagic || h.bytes != s->node.state_bytes || h.nf != s->nf ||
         bytes < sizeof h + h.bytes)
         return fail(CDI_E_INVALID, "snapshot does not belong to this solver layout");
-    int held = held_form(s->prec, s->params.tau, s->params.drive, s->P);
-    if (s->prec == kF32) {
-        const int saved = (h.rstate >> 3) & 1 ? kMom : kF32;
-        if (saved == kMom && held != kMom) return fail(CDI_E_INVALID, "snapshot holds the moments of a tau = 1 flow");
-        held = saved;
-    }
+    // a snapshot may hold populations (FP16 deviations) where this solver holds
+    // moments: its state is stepped on as the populations it is
+    const bool moments = (h.rstate >> 3) & 1;
+    const int held = moments ? held_form(s->prec, s->params.tau, s->params.drive, s->P) : s->prec;
+    if (moments && held == kF32) return fail(CDI_E_INVALID, "snapshot holds the moments of a tau = 1 flow");
     int rc = h2d(s, s->node.base, (const uint8_t *)host + sizeof h, s->node.state_bytes);
     if (rc) return rc;
     if (!((h.rstate >> 4) & 1))  // written with the species in planes
@@ -1690,8 +1689,9 @@ int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes)
             HIPCHK(hipMemcpyAsync(s->node.tmp, c, 8ull * s->P, hipMemcpyDeviceToDevice, s->stream));
             HIPCHK(launch_pair_planes(s->node.tmp, (float *)c, s->P, 1, s->stream));
         }
-    // an FP32 snapshot may hold populations where this solver holds moments:
-    // its state is stepped on as the populations it is
+    if (moments && held == kF16)  // what the deviations' place holds is older than the moments
+        for (void *f : {s->node.f, s->node.f2})
+            if (f) HIPCHK(launch_fill_u32((uint32_t *)f, 0u, (int64_t)s->Q * s->P / 2, s->stream));
     set_form(s, held);
     s->parity = h.parity;
     s->fcur = h.fcur;

@@ -1,0 +1,56 @@
+"""Snapshots restored into a solver with other parameters (same lattice and
+storage), whose state may be held in another form: FP32 populations or FP16
+deviations where tau = 1 would hold moments, and the reverse. What is read back
+right after the restore is the saved state, and it is stepped on as that state."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+P = pytest.importorskip("paper_2110_13055_amd")
+from paper_2110_13055_amd import _lib as L  # noqa: E402
+from paper_2110_13055_amd import Geometry, Params, Solver  # noqa: E402
+
+RSTATE = 16 + 7 * 4  # byte offset of the state bits in a snapshot's header
+
+
+def solver(**pk):
+    g = Geometry(dim=3, nx=40, ny=32, nz=28, kind=L.SPHERES, porosity=0.5, r_min=3.0, r_max=6.0, seed=7)
+    return Solver(g, Params(**{"u_in": 1e-3, "dpsi_vt": 20.0, **pk}))
+
+
+@pytest.mark.parametrize("streaming", [L.STREAM_AA, L.STREAM_PULL], ids=["aa", "pull"])
+def test_fp16_deviations_of_another_tau_are_kept(streaming):
+    pk = dict(precision=L.FP16_DEV, streaming=streaming)
+    a, b, c = solver(tau=0.8, **pk), solver(tau=1.0, **pk), solver(tau=0.8, **pk)
+    a.flow_steps(31)
+    blob = a.snapshot()
+    b.restore(blob)
+    # the same stored state: bitwise the same moments, with or without a copy on the way
+    c.restore(b.snapshot())
+    for s in (b, c):
+        assert np.array_equal(s.velocity(), a.velocity()) and np.array_equal(s.density(), a.density())
+    # and stepped on as it is: FP32 populations of the same history
+    f = solver(tau=0.8, streaming=streaming), solver(tau=1.0, streaming=streaming)
+    f[0].flow_steps(31)
+    f[1].restore(f[0].snapshot())
+    b.flow_steps(1)
+    f[1].flow_steps(1)
+    u, v = b.velocity(), f[1].velocity()
+    # FP16 rounds the deviations to 2^-11 of themselves; dropped, they change u
+    # by as much as a step of the other relaxation time does
+    assert np.linalg.norm(u - v) <= 1e-3 * np.linalg.norm(v)
+
+
+def test_moments_leave_no_older_deviations_behind():
+    pk = dict(precision=L.FP16_DEV)
+    old, m, t = solver(tau=0.8, **pk), solver(tau=1.0, **pk), solver(tau=0.8, **pk)
+    old.flow_steps(20)
+    m.restore(old.snapshot())  # deviations in the solver's memory ...
+    fresh = solver(tau=1.0, **pk)
+    fresh.flow_steps(20)
+    blob = fresh.snapshot()
+    assert blob[RSTATE] & 8
+    m.restore(blob)            # ... and then moments
+    t.restore(m.snapshot())
+    assert np.array_equal(t.velocity(), fresh.velocity()) and np.array_equal(t.density(), fresh.density())
