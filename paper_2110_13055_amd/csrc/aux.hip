@@ -196,6 +196,21 @@ __global__ void j_from_m_kernel(Grid g, const float4 *M, const float *rref, floa
     if (D == 3) j[2 * (size_t)g.P + n] = r * m.w;
 }
 
+// Each node's equilibrium, which is what it sent at tau = 1 (see held_form).
+template <class L>
+__global__ __launch_bounds__(256) void pops_from_m_kernel(Grid g, int pull, int linear_eq, const float4 *M,
+                                                          const float *rref, float *F)
+{
+    const int n = blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= g.n_f) return;
+    int x, y, z;
+    unpack_xyz(g, g.fluid[n], x, y, z);
+    const float4 m = M[n];
+    const EqTerms t = eq_terms(m.x, 1.f + (rref ? rref[x] : 0.f) + m.x, m.y, m.z, m.w, linear_eq);
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i) *pop_at<L::Q, float>(F, pull ? i : L::opp[i], n) = feq_dir<L>(i, t, m.y, m.z, m.w);
+}
+
 // Single block of 1024 threads; fixed summation order.
 __global__ __launch_bounds__(1024) void reduce_tiles_kernel(const double *in, int ntiles, int stride,
                                                             int width, double *out)
@@ -411,6 +426,18 @@ hipError_t launch_j_from_m(int dim, const Grid &g, const float4 *M, const float 
         j_from_m_kernel<2><<<blocks, 256, 0, s>>>(g, M, rref, j);
     else
         j_from_m_kernel<3><<<blocks, 256, 0, s>>>(g, M, rref, j);
+    return hipGetLastError();
+}
+
+hipError_t launch_pops_from_m(int dim, const Grid &g, int pull, int linear_eq, const float4 *M, const float *rref,
+                              float *F, hipStream_t s)
+{
+    const unsigned blocks = (unsigned)((g.n_f + 255) / 256);
+    if (blocks == 0) return hipSuccess;
+    if (dim == 2)
+        pops_from_m_kernel<D2Q9><<<blocks, 256, 0, s>>>(g, pull, linear_eq, M, rref, F);
+    else
+        pops_from_m_kernel<D3Q19><<<blocks, 256, 0, s>>>(g, pull, linear_eq, M, rref, F);
     return hipGetLastError();
 }
 

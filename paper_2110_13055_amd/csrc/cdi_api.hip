@@ -442,6 +442,24 @@ int step_once(cdi_solver *s, int lbm, int np, int flags)
     return CDI_OK;
 }
 
+// Turns the state of an FP32 instance from moments, at whose place it has them
+// (set_form done), into the populations that they stand for.
+int moments_to_pops(cdi_solver *s)
+{
+    const float4 *M = s->node.M[s->mcur];
+    if (s->jstate == J_IN_M) {
+        HIPCHK(launch_j_from_m(s->dim, s->g, M, cur_rref(s), s->node.j[s->jcur], s->stream));
+        s->jstate = J_VALID;
+    }
+    // (aside: the moments lie in the populations' place)
+    HIPCHK(hipMemcpyAsync(s->node.xfer, M, 16ull * s->P, hipMemcpyDeviceToDevice, s->stream));
+    HIPCHK(launch_pops_from_m(s->dim, s->g, s->pull, s->p.linear_eq, (const float4 *)s->node.xfer, cur_rref(s),
+                              (float *)s->node.f, s->stream));
+    s->fcur = 0;
+    s->parity = 1;
+    return CDI_OK;
+}
+
 int ensure_j(cdi_solver *s)
 {
     if (s->jstate == J_VALID) return CDI_OK;
@@ -1681,7 +1699,6 @@ int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes)
     // moments: its state is stepped on as the populations it is
     const bool moments = (h.rstate >> 3) & 1;
     const int held = moments ? held_form(s->prec, s->params.tau, s->params.drive, s->P) : s->prec;
-    if (moments && held == kF32) return fail(CDI_E_INVALID, "snapshot holds the moments of a tau = 1 flow");
     int rc = h2d(s, s->node.base, (const uint8_t *)host + sizeof h, s->node.state_bytes);
     if (rc) return rc;
     if (!((h.rstate >> 4) & 1))  // written with the species in planes
@@ -1705,7 +1722,7 @@ int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes)
     s->flow_steps = h.flow_steps;
     s->np_steps = h.np_steps;
     s->p.psi = h.psi_on ? s->node.psi : nullptr;
-    return CDI_OK;
+    return moments && held == kF32 ? moments_to_pops(s) : CDI_OK;
 }
 
 int cdi_set_tuning(cdi_solver *s, const cdi_tuning *t)

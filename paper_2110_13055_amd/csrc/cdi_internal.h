@@ -288,6 +288,11 @@ hipError_t launch_build_nbr(int dim, const Grid &g, int *nbr, hipStream_t s);
 // j = rho u from the moments buffer (FP16 and moment storage; rref: the
 // plane references its densities are relative to, nullptr: zero).
 hipError_t launch_j_from_m(int dim, const Grid &g, const float4 *M, const float *rref, float *j, hipStream_t s);
+// The FP32 populations of a state held as moments (M, relative to the plane
+// references rref, nullptr: zero), in the nodes' own slots: those of an AA state
+// of parity 1, or (pull) of a pull-streaming one. F and M do not overlap.
+hipError_t launch_pops_from_m(int dim, const Grid &g, int pull, int linear_eq, const float4 *M, const float *rref,
+                              float *F, hipStream_t s);
 // Deterministic single-block sums: out[k] = sum_t in[t*stride + k], k < width.
 hipError_t launch_reduce_tiles(const double *in, int ntiles, int stride, int width, double *out,
                                hipStream_t s);

@@ -54,3 +54,40 @@ def test_moments_leave_no_older_deviations_behind():
     m.restore(blob)            # ... and then moments
     t.restore(m.snapshot())
     assert np.array_equal(t.velocity(), fresh.velocity()) and np.array_equal(t.density(), fresh.density())
+
+
+def as_populations(s):
+    """The rest state's snapshot marked as populations (all zeros in both forms)."""
+    blob = bytearray(s.snapshot())
+    blob[RSTATE] &= ~8 & 0xFF
+    return bytes(blob)
+
+
+@pytest.mark.parametrize("other", [dict(tau=0.8), dict(drive=L.BODY_FORCE, body_force=(1e-5, 0.0, 0.0))],
+                         ids=["tau", "force"])
+@pytest.mark.parametrize("streaming", [L.STREAM_AA, L.STREAM_PULL], ids=["aa", "pull"])
+@pytest.mark.parametrize("refs", [False, True])
+def test_fp32_moments_become_populations_elsewhere(refs, streaming, other):
+    m, p = solver(streaming=streaming), solver(streaming=streaming)
+    p.restore(as_populations(p))  # the same run, held as populations
+    for s in (m, p):
+        if refs:  # renewed plane references, the last renewal still pending
+            s.flow_to_steady(tol=0.0, max_steps=40, check_every=10)
+        s.np_step(21, fused=True)  # an odd number of steps: own slots on both sides
+        if refs:
+            s.flow_to_steady(tol=0.0, max_steps=10, check_every=10)
+    a, b = solver(streaming=streaming, **other), solver(streaming=streaming, **other)
+    if refs:  # 71 steps
+        assert m.snapshot()[RSTATE] & 2
+    a.restore(m.snapshot())
+    b.restore(p.snapshot())
+    assert m.snapshot()[RSTATE] & 8 and not a.snapshot()[RSTATE] & 8
+    # both round FP32 values of the same state: some 80 steps of 6e-8 each, well below 1e-5
+    for k in range(2):
+        assert np.linalg.norm(a.velocity() - b.velocity()) <= 1e-5 * np.linalg.norm(b.velocity())
+        assert np.abs(a.density() - b.density()).max() <= 1e-6
+        assert np.abs(a.np_velocity() - b.np_velocity()).max() <= 1e-5 * np.abs(b.np_velocity()).max()
+        for s in (a, b):
+            s.np_step(7, fused=True)
+            s.flow_steps(4)
+    assert np.abs(a.concentration() - b.concentration()).max() <= 1e-5
