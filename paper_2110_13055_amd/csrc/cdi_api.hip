@@ -365,7 +365,7 @@ struct SnapHeader {
     int32_t parity, mcur, jcur, ccur, jstate, fcur;
     int32_t psi_on;  // the potential in use is the field in the state (else the ramp)
     int32_t rstate;  // rcur | rpend << 1 | rlive << 2 | (populations held as moments) << 3 |
-                     // (concentrations in pairs) << 4
+                     // (concentrations in pairs) << 4 | (equilibrium recorded) << 5 | (linear) << 6
     int64_t flow_steps, np_steps, nf;
 };
 constexpr uint64_t kSnapMagic = 0x43444931534e4150ull;
@@ -443,8 +443,9 @@ int step_once(cdi_solver *s, int lbm, int np, int flags)
 }
 
 // Turns the state of an FP32 instance from moments, at whose place it has them
-// (set_form done), into the populations that they stand for.
-int moments_to_pops(cdi_solver *s)
+// (set_form done), into the populations that they stand for: the (linear)
+// equilibrium.
+int moments_to_pops(cdi_solver *s, int linear_eq)
 {
     const float4 *M = s->node.M[s->mcur];
     if (s->jstate == J_IN_M) {
@@ -453,7 +454,7 @@ int moments_to_pops(cdi_solver *s)
     }
     // (aside: the moments lie in the populations' place)
     HIPCHK(hipMemcpyAsync(s->node.xfer, M, 16ull * s->P, hipMemcpyDeviceToDevice, s->stream));
-    HIPCHK(launch_pops_from_m(s->dim, s->g, s->pull, s->p.linear_eq, (const float4 *)s->node.xfer, cur_rref(s),
+    HIPCHK(launch_pops_from_m(s->dim, s->g, s->pull, linear_eq, (const float4 *)s->node.xfer, cur_rref(s),
                               (float *)s->node.f, s->stream));
     s->fcur = 0;
     s->parity = 1;
@@ -1680,7 +1681,8 @@ int cdi_snapshot(cdi_solver *s, void *host, uint64_t bytes)
     if (bytes < sizeof(SnapHeader) + s->node.state_bytes) return fail(CDI_E_BUFFER, "snapshot buffer too small");
     SnapHeader h{kSnapMagic, s->node.state_bytes, s->parity, s->mcur, s->jcur, s->ccur, s->jstate, s->fcur,
                  s->p.psi != nullptr,
-                 s->rcur | (s->rpend << 1) | (s->rlive << 2) | ((s->prec != kMom && s->st == kMom) << 3) | (1 << 4),
+                 s->rcur | (s->rpend << 1) | (s->rlive << 2) | ((s->prec != kMom && s->st == kMom) << 3) | (3 << 4) |
+                     ((s->p.linear_eq != 0) << 6),
                  s->flow_steps, s->np_steps, s->nf};
     std::memcpy(host, &h, sizeof h);
     return d2h(s, (uint8_t *)host + sizeof h, s->node.base, s->node.state_bytes);
@@ -1698,7 +1700,10 @@ int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes)
     // a snapshot may hold populations (FP16 deviations) where this solver holds
     // moments: its state is stepped on as the populations it is
     const bool moments = (h.rstate >> 3) & 1;
-    const int held = moments ? held_form(s->prec, s->params.tau, s->params.drive, s->P) : s->prec;
+    int held = moments ? held_form(s->prec, s->params.tau, s->params.drive, s->P) : s->prec;
+    // moments stand for the equilibrium that the saved flow was collided with
+    const int linear_eq = (h.rstate >> 5) & 1 ? (h.rstate >> 6) & 1 : s->p.linear_eq != 0;
+    if (moments && s->prec == kF32 && linear_eq != (s->p.linear_eq != 0)) held = kF32;
     int rc = h2d(s, s->node.base, (const uint8_t *)host + sizeof h, s->node.state_bytes);
     if (rc) return rc;
     if (!((h.rstate >> 4) & 1))  // written with the species in planes
@@ -1722,7 +1727,7 @@ int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes)
     s->flow_steps = h.flow_steps;
     s->np_steps = h.np_steps;
     s->p.psi = h.psi_on ? s->node.psi : nullptr;
-    return moments && held == kF32 ? moments_to_pops(s) : CDI_OK;
+    return moments && held == kF32 ? moments_to_pops(s, linear_eq) : CDI_OK;
 }
 
 int cdi_set_tuning(cdi_solver *s, const cdi_tuning *t)

@@ -91,3 +91,22 @@ def test_fp32_moments_become_populations_elsewhere(refs, streaming, other):
             s.np_step(7, fused=True)
             s.flow_steps(4)
     assert np.abs(a.concentration() - b.concentration()).max() <= 1e-5
+
+
+def test_fp32_moments_of_the_other_equilibrium():
+    # the populations of a Stokes flow restored where the quadratic equilibrium is
+    # set: velocities of 0.08, whose squares the two differ by
+    m, p = solver(u_in=0.02, equilibrium=L.EQ_LINEAR), solver(u_in=0.02, equilibrium=L.EQ_LINEAR)
+    p.restore(as_populations(p))
+    for s in (m, p):
+        s.flow_steps(31)
+    a, b = solver(u_in=0.02), solver(u_in=0.02)
+    a.restore(m.snapshot())
+    b.restore(p.snapshot())
+    for k in range(2):
+        assert np.linalg.norm(a.velocity() - b.velocity()) <= 1e-5 * np.linalg.norm(b.velocity())
+        for s in (a, b):
+            s.flow_steps(1)
+    c = solver(u_in=0.02, equilibrium=L.EQ_LINEAR)  # and back: still moments
+    c.restore(m.snapshot())
+    assert c.snapshot()[RSTATE] & 8
