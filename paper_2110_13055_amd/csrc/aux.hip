@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void moments_kernel(Grid g, Phys p, int nee, c
         set_nbr<L>(nb, i, (ODD || !kPlain<ST>) ? nb_map<L>(g, sx, y, z, i, g.periodic_x) : kOutside, src);
     float f[Q];
     // relative to the plane reference of the node read (see PlaneRef)
-    const PlaneRef pr = kRefs<ST> ? plane_ref<0>(g, rref, rref, sx) : PlaneRef{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+    const PlaneRef pr = kRefs<ST> ? plane_ref<0>(g, rref, rref, sx) : PlaneRef{};
     float ref = pr.rout;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {

@@ -335,20 +335,24 @@ struct PlaneRef {
     float rout;   // Rout[x]
     float dIn[3]; // Rin[x - ex] - Rout[x], ex = -1, 0, 1
     float dOut[3];// Rout[x] - Rout[x + ex]
+    float rin[3]; // Rin[x - ex] (a node's density is formed with its plane's own value
+                  // wherever two nodes have to agree on it: rout + dIn rounds)
 };
 
 // (dOut only for the odd AA parity, which writes into neighbours' slots)
 template <int ODD>
 __device__ inline PlaneRef plane_ref(const Grid &g, const float *rin, const float *rout, int x)
 {
-    PlaneRef r{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+    PlaneRef r{};
     if (!rin) return r;
     const int xm = x > 0 ? x - 1 : (g.periodic_x ? g.nx - 1 : 0);
     const int xp = x < g.nx - 1 ? x + 1 : (g.periodic_x ? 0 : g.nx - 1);
     r.rout = ldu(rout, (uint32_t)x);
-    r.dIn[0] = ldu(rin, (uint32_t)xp) - r.rout;  // ex = -1: the slot's node is at x + 1
-    r.dIn[1] = ldu(rin, (uint32_t)x) - r.rout;
-    r.dIn[2] = ldu(rin, (uint32_t)xm) - r.rout;  // ex = +1: at x - 1
+    r.rin[0] = ldu(rin, (uint32_t)xp);  // ex = -1: the slot's node is at x + 1
+    r.rin[1] = ldu(rin, (uint32_t)x);
+    r.rin[2] = ldu(rin, (uint32_t)xm);  // ex = +1: at x - 1
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r.dIn[k] = r.rin[k] - r.rout;
     if (ODD == 1) {
         r.dOut[0] = r.rout - ldu(rout, (uint32_t)xm);
         r.dOut[2] = r.rout - ldu(rout, (uint32_t)xp);

@@ -587,7 +587,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
     float f[kMoments<ST> ? 1 : Q];
     MomSums sums;  // with the moment buffers: their moments
     bool do_flow = false;
-    PlaneRef pr{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};  // the node's plane references
+    PlaneRef pr{};  // the node's plane references
     if (LBM && active) {
         // a boundary node with a fluid interior neighbour is advanced by that neighbour
         do_flow = !(edge && ((x == 0 && nb.fl[1]) || (x == g.nx - 1 && nb.fl[2])));
@@ -626,8 +626,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
                 if (jm) {
                     auto rho_of = [&](int k, float mx) {  // face k's emitter (k < 0: the node)
                         if (ST != kMomR) return 1.f + mx;
-                        const float d = k < 0 || k > 1 || !nb.fl[k + 1] ? pr.dIn[1] : pr.dIn[k == 0 ? 0 : 2];
-                        return 1.f + (pr.rout + d) + mx;
+                        return 1.f + (k < 0 || k > 1 || !nb.fl[k + 1] ? pr.rin[1] : pr.rin[k == 0 ? 0 : 2]) + mx;
                     };
                     const float r = rho_of(-1, mg[0].x);
                     jP[0] = r * mg[0].y;
@@ -753,7 +752,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
             // extrapolated non-equilibrium part carries none
             const int bn = inl ? nb.n[2] : nb.n[1];
             const int xb = inl ? 0 : g.nx - 1;
-            PlaneRef pb{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+            PlaneRef pb{};
             if (kRefs<ST>) pb = plane_ref<ODD>(g, b.rin, b.rout, xb);
             MomSums sb;
             if constexpr (!kPlain<ST>) sb = nee_moments(p, inl, sums, pr.rout, pb.rout);
