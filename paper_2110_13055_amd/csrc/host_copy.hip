@@ -107,7 +107,8 @@ hipError_t staged_copy(uint8_t *area, uint8_t *dst, const uint8_t *src, uint64_t
 
 hipError_t copy_to_host(void *dst, const void *src, uint64_t bytes, hipStream_t s)
 {
-    void *area = bytes >= kStagedCopyMin ? take_area() : nullptr;
+    // (hipStreamPerThread names another stream in every worker)
+    void *area = bytes >= kStagedCopyMin && s != hipStreamPerThread ? take_area() : nullptr;
     if (!area) return plain_copy(dst, src, bytes, s);
     const hipError_t e = staged_copy((uint8_t *)area, (uint8_t *)dst, (const uint8_t *)src, bytes, s);
     give_area();
