@@ -30,10 +30,27 @@ void *g_area = nullptr;
 bool g_taken = false;
 int g_users = 0;
 
+// Pinned memory is made and freed whatever is captured meanwhile, in this thread
+// or another: it takes no part in a graph, and the default mode would have the
+// call refused and the capture invalidated.
+struct WhileCapturing {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    WhileCapturing() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~WhileCapturing() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+void free_area()
+{
+    WhileCapturing relaxed;
+    (void)hipHostFree(g_area);
+    g_area = nullptr;
+}
+
 void *take_area()
 {
     std::lock_guard<std::mutex> lock(g_mu);
     if (g_taken) return nullptr;
+    WhileCapturing relaxed;
     if (!g_area && hipHostMalloc(&g_area, kPiece * kSlots, hipHostMallocPortable) != hipSuccess) {
         (void)hipGetLastError();
         g_area = nullptr;
@@ -47,10 +64,7 @@ void give_area()
 {
     std::lock_guard<std::mutex> lock(g_mu);
     g_taken = false;
-    if (g_users <= 0) {
-        (void)hipHostFree(g_area);
-        g_area = nullptr;
-    }
+    if (g_users <= 0) free_area();
 }
 
 hipError_t plain_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s)
@@ -124,10 +138,7 @@ void staging_user_added()
 void staging_user_removed()
 {
     std::lock_guard<std::mutex> lock(g_mu);
-    if (--g_users <= 0 && !g_taken && g_area) {
-        (void)hipHostFree(g_area);
-        g_area = nullptr;
-    }
+    if (--g_users <= 0 && !g_taken && g_area) free_area();
 }
 
 }  // namespace cdi
