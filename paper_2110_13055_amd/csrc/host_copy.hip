@@ -77,8 +77,8 @@ hipError_t plain_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s)
 // piece's event, moves it out and sends the slot's next piece on its way.
 hipError_t staged_copy(uint8_t *area, uint8_t *dst, const uint8_t *src, uint64_t bytes, hipStream_t s)
 {
-    int dev = 0;
-    hipError_t err = hipGetDevice(&dev);
+    int dev = 0;  // the stream's: the caller's current device may be another
+    hipError_t err = s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev);
     if (err != hipSuccess) return err;
     const int64_t pieces = (int64_t)((bytes + kPiece - 1) / kPiece);
     std::atomic<int> failed{hipSuccess};

@@ -28,8 +28,10 @@ def solver(stream=None):
                   Params(u_in=1e-3), stream=stream)
 
 
-def test_per_thread_stream():
-    s, t = solver(PerThread()), solver()
+@pytest.mark.parametrize("own", [False, True], ids=["per_thread", "own"])
+def test_reads_wait_for_the_streams_steps(own):
+    torch = pytest.importorskip("torch")
+    s, t = solver(torch.cuda.Stream() if own else PerThread()), solver()
     for n in (150, 151):
         s.flow_steps(n)  # still running when the copy is asked for
         u = s.velocity()
