@@ -230,18 +230,28 @@ __global__ __launch_bounds__(1024) void reduce_tiles_kernel(const double *in, in
     }
 }
 
-__global__ __launch_bounds__(1024) void max_tiles_kernel(const double *in, int ntiles, double *out)
+// Totals of the stability kernel's tiles: the largest bound, the share of tiles beyond.
+__global__ __launch_bounds__(1024) void stability_total_kernel(const double2 *in, int ntiles, double *out)
 {
-    __shared__ double sm[1024];
-    double s = 0;
-    for (int t = threadIdx.x; t < ntiles; t += 1024) s = fmax(s, in[t]);
+    __shared__ double2 sm[1024];
+    double2 s = make_double2(0.0, 0.0);
+    for (int t = threadIdx.x; t < ntiles; t += 1024) {
+        const double2 v = in[t];
+        s = make_double2(fmax(s.x, v.x), s.y + v.y);
+    }
     sm[threadIdx.x] = s;
     __syncthreads();
     for (int h = 512; h > 0; h >>= 1) {
-        if (threadIdx.x < h) sm[threadIdx.x] = fmax(sm[threadIdx.x], sm[threadIdx.x + h]);
+        if (threadIdx.x < h) {
+            const double2 a = sm[threadIdx.x], b = sm[threadIdx.x + h];
+            sm[threadIdx.x] = make_double2(fmax(a.x, b.x), a.y + b.y);
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[0] = sm[0];
+    if (threadIdx.x == 0) {
+        out[0] = sm[0].x;
+        out[1] = sm[0].y / ntiles;
+    }
 }
 
 __global__ __launch_bounds__(kTile) void mass_kernel(Grid g, const float2 *C, const __half2 *Clo, double *part)
@@ -266,13 +276,14 @@ __global__ __launch_bounds__(kTile) void mass_kernel(Grid g, const float2 *C, co
 __device__ inline float bern(float x) { return x == 0.f ? 1.f : x / expm1f(x); }
 
 // dt * (sum of the coefficients multiplying C_P in the outflow), per node,
-// maximum over the block. Positivity of the explicit update needs <= 1.
+// maximum over the block. Positivity of the explicit update needs <= 1. Also
+// whether a face of the block is beyond the flux series' range.
 template <class L>
-__global__ __launch_bounds__(kTile) void stability_kernel(Grid g, Phys p, const float *j, double *part)
+__global__ __launch_bounds__(kTile) void stability_kernel(Grid g, Phys p, const float *j, double2 *part)
 {
     constexpr int D = L::D;
     const int n = blockIdx.x * kTile + threadIdx.x;
-    float worst = 0.f;
+    float worst = 0.f, hmax = 0.f;
     if (n < g.n_f) {
         int x, y, z;
         unpack_xyz(g, g.fluid[n], x, y, z);
@@ -325,6 +336,7 @@ __global__ __launch_bounds__(kTile) void stability_kernel(Grid g, Phys p, const 
                     const float dpsi = p.psi ? psiN[k] - psiP : (axis == 0 ? -sg * p.dpsi_dx : 0.f);
                     const float w = un - p.z[s] * Ds * dpsi;
                     dg += Ds * bern(-w / Ds);
+                    hmax = fmaxf(hmax, fabsf(w) * 0.5f);
                 }
             }
             worst = fmaxf(worst, p.dt * dg);
@@ -337,7 +349,8 @@ __global__ __launch_bounds__(kTile) void stability_kernel(Grid g, Phys p, const 
         if (threadIdx.x < h) sm[threadIdx.x] = fmaxf(sm[threadIdx.x], sm[threadIdx.x + h]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = sm[0];
+    const int beyond = __syncthreads_or(!p.psi && !p.steep && !(hmax * hmax <= p.h2_max));
+    if (threadIdx.x == 0) part[blockIdx.x] = make_double2(sm[0], beyond ? 1.0 : 0.0);
 }
 
 }  // namespace
@@ -463,10 +476,10 @@ hipError_t launch_stability(int dim, const Grid &g, const Phys &p, const float *
     const int tiles = g.P / kTile;
     if (tiles == 0) return hipSuccess;
     if (dim == 2)
-        stability_kernel<D2Q9><<<tiles, kTile, 0, s>>>(g, p, j, part);
+        stability_kernel<D2Q9><<<tiles, kTile, 0, s>>>(g, p, j, (double2 *)part);
     else
-        stability_kernel<D3Q19><<<tiles, kTile, 0, s>>>(g, p, j, part);
-    max_tiles_kernel<<<1, 1024, 0, s>>>(part, tiles, out);
+        stability_kernel<D3Q19><<<tiles, kTile, 0, s>>>(g, p, j, (double2 *)part);
+    stability_total_kernel<<<1, 1024, 0, s>>>((const double2 *)part, tiles, out);
     return hipGetLastError();
 }
 

@@ -145,9 +145,10 @@ struct Phys {
     // Scharfetter-Gummel series in the half drift h (see sg_series): D Bs =
     // D + c1 h^2 + .. + c4 h^8 per species, valid while h^2 <= h2_max (|Pe| <= 1
     // for both species); hr: the ramp's half drift across an x face; steep: the
-    // ramp alone comes near that bound
+    // ramp alone comes near that bound; far: the flow takes faces beyond it (as of
+    // the last positivity check; chooses between kernels of the same results)
     float sgc[2][4], h2_max, hr[2];
-    int steep;
+    int steep, far;
     int npx;
     float dt;
     const float *psi;  // optional field (fluid order), else ramp
@@ -298,7 +299,9 @@ hipError_t launch_reduce_tiles(const double *in, int ntiles, int stride, int wid
                                hipStream_t s);
 // FP64 sum of each concentration field with its remainders (solute mass): out[0..1].
 hipError_t launch_mass(const Grid &g, const float2 *C, const __half2 *Clo, double *part, double *out, hipStream_t s);
-// max over nodes/species of dt * (sum of outflow coefficients); out[0].
+// max over nodes/species of dt * (sum of outflow coefficients), out[0]; the
+// share of the tiles with a face beyond the flux series' range, out[1] (0 in a
+// potential field and in a steep ramp).
 hipError_t launch_stability(int dim, const Grid &g, const Phys &p, const float *j, double *part,
                             double *out, hipStream_t s);
 

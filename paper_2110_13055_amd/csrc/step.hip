@@ -302,8 +302,8 @@ struct IonFlux {
     float ads = 0.f;  // adsorbing faces
 };
 
-// The fluxes to fluid cells with no potential field and a ramp that is not
-// steep. on: the faces to fluid cells; jn the neighbours' flux along the face's
+// The fluxes to fluid cells with no potential field, a ramp that is not steep
+// and hardly a face beyond the series' range. on: the faces to fluid cells; jn the neighbours' flux along the face's
 // axis, cn their concentrations (0 where the face is not fluid: its flux is
 // formed and multiplied by 0). Straight-line code, without a branch
 // per face; y and z faces, where the ramp has no gradient, share the half drift
@@ -373,7 +373,31 @@ __device__ __forceinline__ void ion_faces_wide(const Grid &g, const Phys &p, con
     }
 }
 
-// The same in a potential field (psi; the migration of every face from the
+// The same values in line, for flows that take many faces beyond the series'
+// range. Bound by the number of vector memory instructions like ion_faces, whose
+// detour adds dependent ones (160^3, every tile beyond: ion step 53 -> 37 us,
+// fused with moments 84 -> 67, FP16 101 -> 84, FP32 populations 158 -> 142,
+// a batch of 16 cubes 45 -> 30; with the potential's form in the same kernel 41).
+template <class L>
+__device__ __forceinline__ void ion_faces_far(const Phys &p, const bool (&on)[2 * L::D], const float (&cP)[2],
+                                              const float (&jP)[3], const float2 (&cn)[2 * L::D],
+                                              const float (&jn)[2 * L::D], IonFlux &f)
+{
+#pragma unroll
+    for (int k = 0; k < 2 * L::D; ++k) {
+        if (on[k]) {
+            const float h = ((k & 1) ? -0.25f : 0.25f) * (jP[k >> 1] + jn[k]);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const float hs = k < 2 ? h + ((k & 1) ? -p.hr[s] : p.hr[s]) : h, cN = s ? cn[k].y : cn[k].x;
+                f.out[s] += hs * hs <= p.h2_max ? sg_series(p.D[s], p.sgc[s], hs, cP[s], cN)
+                                                : sg_flux(p.D[s], 2.f * p.invD[s], hs, cP[s], cN);
+            }
+        }
+    }
+}
+
+// The fluxes in a potential field (psi; the migration of every face from the
 // potential's difference) or in a steep ramp.
 template <class L>
 __device__ __forceinline__ void ion_faces_any(const Phys &p, bool psi, const bool (&on)[2 * L::D], const float (&cP)[2],
@@ -449,9 +473,10 @@ __device__ __forceinline__ void ion_end_face(const Grid &g, const Phys &p, const
 
 // One 256-node tile of one instance (all threads of the workgroup call it;
 // sm: (kTile/64)*6 doubles of LDS; stg: the stage of kStageOdd steps).
-// PSI: whether the ions migrate in a potential field or a steep ramp, kPsiAny:
-// as p says.
-constexpr int kPsiAny = 2;
+// PSI: the form of the ions' fluxes: in a ramp (0), in a potential field or a
+// steep ramp, in a flow that takes many faces beyond the series' range, or as p
+// says.
+constexpr int kPsiField = 1, kPsiFar = 2, kPsiAny = 3;
 
 template <class L, int ST, int ODD, int LBM, int NP, int PSI, int STG = 0>
 __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, const Phys &p, const Bufs &b, int tile, double *sm,
@@ -542,8 +567,9 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
     // batched kernels, whose per-instance descriptor leaves no registers to
     // spare (their ion-only and FP16 / moment fused forms lose a wave per
     // SIMD, which costs the served requests, all in the ramp, 10 %)
-    constexpr bool kEarlyPsi = kEarlyJ && PSI == 1;
-    const bool psi = PSI && p.psi, any = PSI == kPsiAny ? p.psi || p.steep : PSI == 1;
+    constexpr bool kEarlyPsi = kEarlyJ && PSI == kPsiField;
+    const int form = PSI != kPsiAny ? PSI : p.psi || p.steep ? kPsiField : p.far ? kPsiFar : 0;
+    const bool psi = (PSI == kPsiField || PSI == kPsiAny) && p.psi;
     float cP[2] = {0.f, 0.f}, jP[3] = {0.f, 0.f, 0.f};
     __half2 elo = __floats2half2_rn(0.f, 0.f);
     float2 cn[F];
@@ -705,7 +731,7 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
             for (int k = 0; k < F; ++k) fx.ads -= m[k] == kInert && !(k < 2 && end[k & 1]) ? 1.f : 0.f;
         }
         float psiP = 0.f;
-        if (any) {
+        if (form == kPsiField) {
             if (psi) {
                 psiP = ldu(p.psi, (uint32_t)n);
                 if (!kEarlyPsi) {
@@ -714,6 +740,8 @@ __device__ __attribute__((always_inline)) inline void step_tile(const Grid &g, c
                 }
             }
             ion_faces_any<L>(p, psi, on, cP, jP, psiP, cn, jn, psin, fx);
+        } else if (form == kPsiFar) {
+            ion_faces_far<L>(p, on, cP, jP, cn, jn, fx);
         } else if (!ion_faces<L>(p, on, cP, jP, cn, jn, fx)) {  // rare
             if (!coords) unpack_xyz(g, ldu(g.fluid, (uint32_t)n), x, y, z);
             ion_faces_wide<L, ST>(g, p, b, x, y, z, jm, end, cP[0], cP[1], jP[0], jP[1], jP[2], fx);
@@ -935,13 +963,16 @@ void launch_psi(const Grid &g, const Phys &p, const Bufs &b, hipStream_t s)
     step_kernel<L, ST, ODD, LBM, NP, 0, PSI><<<T, kTile, (size_t)g.lds_pad, s>>>(g, p, b);
 }
 
-// A kernel of its own for ions in a potential field or a steep ramp, whose code
-// would cost the others registers.
+// Kernels of their own for ions in a potential field or a steep ramp, and for
+// flows with many faces beyond the series' range, whose code would cost the
+// others registers.
 template <class L, int ST, int ODD, int LBM, int NP>
 void launch_t(const Grid &g, const Phys &p, const Bufs &b, hipStream_t s)
 {
     if (NP && (p.psi || p.steep))
-        launch_psi<L, ST, ODD, LBM, NP, NP>(g, p, b, s);
+        launch_psi<L, ST, ODD, LBM, NP, NP * kPsiField>(g, p, b, s);
+    else if (NP && p.far)
+        launch_psi<L, ST, ODD, LBM, NP, NP * kPsiFar>(g, p, b, s);
     else
         launch_psi<L, ST, ODD, LBM, NP, 0>(g, p, b, s);
 }

@@ -211,3 +211,32 @@ def test_both_sides_of_a_face_see_the_same_density():
     drift = np.abs(s.mass_balance()[:, 0] - m0)
     print(f"solute drift {drift} of {s.n_fluid}")
     assert drift.max() <= 4 * 1.2e-9 * steps * np.sqrt(s.n_fluid)
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("form", [dict(), dict(precision=L.FP16), dict(tau=0.8), dict(tau=0.8, precision=L.FP16_DEV),
+                                  dict(precision=L.MOMENTS)], ids=["fp32", "fp16", "tau0.8", "fp16dev", "moments"])
+def test_drift_kernels_give_the_same_values(form, dim):
+    # cell Peclet numbers of up to about 8. One call keeps the kernel that its
+    # first check chooses (the fluid is at rest there), a call per step chooses anew
+    # as the flow sets in, a batch for itself
+    n = 40
+    g = (Geometry(dim=3, nx=n, ny=24, nz=20, kind=L.SPHERES, porosity=0.6, r_min=3.0, r_max=5.0, seed=2) if dim == 3 else
+         Geometry(dim=2, nx=2 * n, ny=48, nz=1, kind=L.DISKS, porosity=0.7, r_min=4.0, r_max=6.0, min_gap=2.0, seed=2,
+                  walls_y=1))
+    a, b, c = (Solver(g, Params(u_in=0.02, dpsi_vt=0.2 * n, D=(0.006, 0.009), **form)) for _ in range(3))
+    a.np_step(60, fused=True)
+    for _ in range(60):
+        b.np_step(1, fused=True)
+    bt = Batch([c])
+    for k in (1, 19, 40):
+        bt.advance(k, L.MODE_FUSED)
+    assert np.abs(a.np_velocity()).max() > 4 * 0.006
+    for k in range(2):
+        for s in (b, c):
+            assert np.array_equal(a.concentration(), s.concentration()) and np.array_equal(a.velocity(), s.velocity())
+            assert np.array_equal(a.mass_balance(), s.mass_balance())
+        for s in (a, b):
+            s.np_step(7)
+        bt.advance(7, L.MODE_IONS)
+    bt.close()
