@@ -160,17 +160,10 @@ __global__ __launch_bounds__(256) void build_rows_kernel(Grid g, int4 *rows, int
     rows[r] = out;
 }
 
-__global__ __launch_bounds__(256) void pair_planes_kernel(const float *src, float *dst, int P, int to_pairs)
+__global__ __launch_bounds__(256) void pair_planes_kernel(const float *src, float2 *dst, int P)
 {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= P) return;
-    if (to_pairs)
-        reinterpret_cast<float2 *>(dst)[n] = make_float2(src[n], src[P + n]);
-    else {
-        const float2 v = reinterpret_cast<const float2 *>(src)[n];
-        dst[n] = v.x;
-        dst[P + n] = v.y;
-    }
+    if (n < P) dst[n] = make_float2(src[n], src[P + n]);
 }
 
 __global__ void tile_heads_kernel(Grid g, uint32_t *heads)
@@ -375,9 +368,9 @@ hipError_t launch_build_rows(const Grid &g, int4 *rows, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_pair_planes(const float *src, float *dst, int P, int to_pairs, hipStream_t s)
+hipError_t launch_pair_planes(const float *src, float2 *dst, int P, hipStream_t s)
 {
-    if (P > 0) pair_planes_kernel<<<(unsigned)((P + 255) / 256), 256, 0, s>>>(src, dst, P, to_pairs);
+    if (P > 0) pair_planes_kernel<<<(unsigned)((P + 255) / 256), 256, 0, s>>>(src, dst, P);
     return hipGetLastError();
 }
 

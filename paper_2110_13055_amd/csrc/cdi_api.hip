@@ -1217,16 +1217,17 @@ int cdi_set_np_velocity(cdi_solver *s, const float *j)
 int cdi_copy_concentration(cdi_solver *s, float *c)
 {
     if (!s || !c) return fail(CDI_E_INVALID, "NULL argument");
-    HIPCHK(launch_pair_planes((const float *)s->node.C[s->ccur], s->node.tmp, s->P, 0, s->stream));
-    return planes_d2h(s, c, s->node.tmp, 2);
+    HIPCHK(launch_permute_pairs(s->node.xfer, s->node.C[s->ccur], s->vox.lex2int, (int)s->nf, 1, s->stream));
+    HIPCHK(copy_to_host(c, s->node.xfer, 8ull * s->nf, s->stream));
+    return CDI_OK;
 }
 
 int cdi_set_concentration(cdi_solver *s, const float *c)
 {
     if (!s || !c) return fail(CDI_E_INVALID, "NULL argument");
-    int rc = planes_h2d(s, s->node.tmp, c, 2);
-    if (rc) return rc;
-    HIPCHK(launch_pair_planes(s->node.tmp, (float *)s->node.C[s->ccur], s->P, 1, s->stream));
+    HIPCHK(hipMemcpyAsync(s->node.xfer, c, 8ull * s->nf, hipMemcpyHostToDevice, s->stream));
+    HIPCHK(launch_permute_pairs(s->node.xfer, s->node.C[s->ccur], s->vox.lex2int, (int)s->nf, 0, s->stream));
+    HIPCHK(hipStreamSynchronize(s->stream));
     HIPCHK(launch_fill_u32((uint32_t *)s->node.Clo[s->ccur], 0u, s->P, s->stream));  // no remainders
     return CDI_OK;
 }
@@ -1719,7 +1720,7 @@ int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes)
     if (!((h.rstate >> 4) & 1))  // written with the species in planes
         for (float2 *c : s->node.C) {
             HIPCHK(hipMemcpyAsync(s->node.tmp, c, 8ull * s->P, hipMemcpyDeviceToDevice, s->stream));
-            HIPCHK(launch_pair_planes(s->node.tmp, (float *)c, s->P, 1, s->stream));
+            HIPCHK(launch_pair_planes(s->node.tmp, c, s->P, s->stream));
         }
     if (moments && held == kF16)  // what the deviations' place holds is older than the moments
         for (void *f : {s->node.f, s->node.f2})

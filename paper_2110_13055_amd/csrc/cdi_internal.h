@@ -242,6 +242,8 @@ int64_t brick_enum_size(const Bricks &bk);
 // inverse scatter.
 hipError_t launch_permute(const float *src, float *dst, const int *lex2int, int n_f, int P, int d,
                           int to_lex, hipStream_t s);
+// The same between two planes in lexicographic order and a float2 per node.
+hipError_t launch_permute_pairs(float *lex, float2 *pairs, const int *lex2int, int n_f, int to_lex, hipStream_t s);
 
 // Streaming kernels of known traffic over bytes (a multiple of 16): copy,
 // XOR checksum of every 8 KiB block of src into dst (16 bytes per block),
@@ -281,9 +283,8 @@ hipError_t launch_tile_heads(const Grid &g, uint32_t *heads, hipStream_t s);
 // The rows of the lattice (Grid::rows), brick_enum_size / 2^bsx of them.
 int64_t row_count(const Bricks &bk);
 hipError_t launch_build_rows(const Grid &g, int4 *rows, hipStream_t s);
-// Both species between a float2 per node and two planes of P (in either order
-// of nodes): to_pairs: dst is the float2 array.
-hipError_t launch_pair_planes(const float *src, float *dst, int P, int to_pairs, hipStream_t s);
+// Both species from two planes of P to a float2 per node.
+hipError_t launch_pair_planes(const float *src, float2 *dst, int P, hipStream_t s);
 // Neighbour list of every fluid node (see Grid::nbr), 2 d planes of P.
 hipError_t launch_build_nbr(int dim, const Grid &g, int *nbr, hipStream_t s);
 // j = rho u from the moments buffer (FP16 and moment storage; rref: the

@@ -308,6 +308,21 @@ __global__ void permute_kernel(const float *src, float *dst, const int *lex2int,
         dst[(size_t)c * P + n] = src[(size_t)c * n_f + k];
 }
 
+// The same for two planes in lexicographic order and pairs in internal order.
+__global__ void permute_pairs_kernel(float *lex, float2 *pairs, const int *lex2int, int n_f, int to_lex)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n_f) return;
+    const int n = lex2int[k];
+    if (to_lex) {
+        const float2 v = pairs[n];
+        lex[k] = v.x;
+        lex[(size_t)n_f + k] = v.y;
+    } else {
+        pairs[n] = make_float2(lex[k], lex[(size_t)n_f + k]);
+    }
+}
+
 template <class T>
 __global__ void fill_kernel(T *p, T v, int64_t n)
 {
@@ -386,6 +401,13 @@ hipError_t launch_permute(const float *src, float *dst, const int *lex2int, int 
     const int64_t n = (int64_t)n_f * d;
     if (n <= 0) return hipSuccess;
     permute_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(src, dst, lex2int, n_f, P, d, to_lex);
+    return hipGetLastError();
+}
+
+hipError_t launch_permute_pairs(float *lex, float2 *pairs, const int *lex2int, int n_f, int to_lex, hipStream_t s)
+{
+    if (n_f <= 0) return hipSuccess;
+    permute_pairs_kernel<<<(unsigned)(((int64_t)n_f + 255) / 256), 256, 0, s>>>(lex, pairs, lex2int, n_f, to_lex);
     return hipGetLastError();
 }
 
