@@ -1554,7 +1554,7 @@ int np_solve(cdi_solver *s, double idt, double tol, int32_t max_iter, void *ws, 
     HIPCHK(launch_nps_setup(s->dim, a, tol, s->stream));
     double st[kNsSlots];
     if ((rc = d2h(s, st, W.state, sizeof st)) != CDI_OK) return rc;
-    a.plain = nps_plain(st[kNsPe]);
+    a.plain = nps_plain(st[kNsPe], st[kNsRange]);
     HIPCHK(nps_dir_workgroups(s->dim, s->ntiles, a.plain, a.Gd));
     int k = 0;
     while (st[kNsDone] == 0 && k < max_iter) {

@@ -79,6 +79,7 @@ struct NpNode {
     float al[2][2 * L::D], be[2][2 * L::D];
     double b[2];
     float diag[2];
+    float adv;  // largest half drift of the flow across a face to a fluid cell
 };
 
 // Its neighbours, from the list when the instance has one built with the ions'
@@ -125,6 +126,7 @@ __device__ __forceinline__ void np_coefs(const Grid &g, const Phys &p, const flo
     const float invD2[2] = {2.f * p.invD[0], 2.f * p.invD[1]};
     const float hzD[2] = {0.5f * p.z[0] * p.D[0], 0.5f * p.z[1] * p.D[1]};
     c.b[0] = c.b[1] = 0.0;
+    c.adv = 0.f;
 #pragma unroll
     for (int k = 0; k < 2 * D; ++k) {
         const int i = k + 1;
@@ -160,6 +162,7 @@ __device__ __forceinline__ void np_coefs(const Grid &g, const Phys &p, const flo
             for (int s = 0; s < 2; ++s) c.al[s][k] = p.keff[s];
         } else if (m >= 0) {
             const float hun = 0.25f * (jP[axis] + jN[k]) * sg;
+            c.adv = fmaxf(c.adv, fabsf(hun));
             const bool mig = p.psi || axis == 0;  // the ramp has no y/z gradient
             const float dpsi = p.psi ? psiN[k] - psiP : -sg * p.dpsi_dx;
 #pragma unroll
@@ -189,14 +192,27 @@ __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
     int t0, t1;
     tile_range(a.g.P / kTile, t0, t1);
     double bb[2] = {0, 0}, rho[2] = {0, 0}, rr[2] = {0, 0};
-    float pe = 0.f;
+    float adv = 0.f;
+    double range = a.p.psi ? 0.0 : 16.0 * fabs((double)a.p.dpsi_dx);  // (16 voxels of a brick)
     for (int t = t0; t < t1; ++t) {
         const int n = t * kTile + threadIdx.x;
+        if (a.p.psi) {  // the range in the tile's block
+            float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+            for (int q = 0; q < kBlockTiles; ++q) {
+                const int m = (t / kBlockTiles * kBlockTiles + q) * kTile + (int)threadIdx.x;
+                const float v = a.p.psi[m < a.g.n_f ? m : t * kTile];
+                lo = fminf(lo, v);
+                hi = fmaxf(hi, v);
+            }
+            range = fmax(range, wg_max(hi, sm) + wg_max(-lo, sm));
+        }
         double xv[2] = {0, 0}, rv[2] = {0, 0};
         float di[2] = {0, 0};
         if (n < a.g.n_f) {
             NpNode<L> c;
             np_node<L>(a.g, a.p, a.j, n, c);
+            adv = fmaxf(adv, c.adv);
             float2 cN[2 * L::D];
 #pragma unroll
             for (int k = 0; k < 2 * L::D; ++k) cN[k] = a.C[c.m[k] >= 0 ? c.m[k] : n];
@@ -206,10 +222,7 @@ __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
                 double ax = (c.diag[s] + a.idt) * xv[s];
 #pragma unroll
                 for (int k = 0; k < 2 * L::D; ++k)
-                    if (c.m[k] >= 0) {
-                        ax -= (double)c.be[s][k] * (double)of_species(cN[k], s);
-                        pe = fmaxf(pe, fabsf(c.al[s][k] - c.be[s][k]) * a.p.invD[s]);
-                    }
+                    if (c.m[k] >= 0) ax -= (double)c.be[s][k] * (double)of_species(cN[k], s);
                 const double rhs = a.idt * xv[s] + c.b[s];
                 rv[s] = rhs - ax;
                 const float d = (float)(c.diag[s] + a.idt);
@@ -237,17 +250,22 @@ __global__ __launch_bounds__(kTile) void nps_setup_kernel(NpsArgs a)
             reg(a, kTt, s)[blockIdx.x] = blockIdx.x == 0 ? 1.0 : 0.0;
         }
     }
-    const double s_pe = wg_max(pe, sm);
-    if (threadIdx.x == 0) reg(a, kRho1, 0)[blockIdx.x] = s_pe;  // (free until the first update)
+    const double s_pe = wg_max(2.0 * adv * fmaxf(a.p.invD[0], a.p.invD[1]), sm);
+    if (threadIdx.x == 0) {  // (free until the first update)
+        reg(a, kRho1, 0)[blockIdx.x] = s_pe;
+        reg(a, kRho1, 1)[blockIdx.x] = range * fmaxf(fabsf(a.p.z[0]), fabsf(a.p.z[1]));
+    }
 }
 
 __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, double tol)
 {
     __shared__ double sm[kTile / 64];
-    float pe = 0.f;
-    for (int k = threadIdx.x; k < G; k += blockDim.x) pe = fmaxf(pe, (float)reg(a, kRho1, 0)[k]);
-    const double s_pe = wg_max(pe, sm);
-    if (threadIdx.x == 0) a.state[kNsPe] = s_pe;
+    for (int q = 0; q < 2; ++q) {
+        double v = 0;
+        for (int k = threadIdx.x; k < G; k += blockDim.x) v = fmax(v, reg(a, kRho1, q)[k]);
+        v = wg_max(v, sm);
+        if (threadIdx.x == 0) a.state[q ? kNsRange : kNsPe] = v;
+    }
     for (int s = 0; s < 2; ++s) {
         const double bb = region_sum(a.part + ((size_t)kBb * 2 + s) * G, G, sm);
         const double rr = region_sum(a.part + ((size_t)kRr * 2 + s) * G, G, sm);
@@ -269,31 +287,33 @@ __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, doub
 // power of two per solve (which scales M). With A_b = D - O (D the diagonal, O >=
 // 0): what leaves a cell enters its neighbours, so that the columns of O D^-1 sum
 // to at most 1 and the eigenvalues of D^-1 A_b lie in the disc |lambda - 1| <= 1.
-// They are real, in (0, 2), without drift; a drift adds imaginary parts of up
-// to half of its cell Peclet number.
+// They are real, in (0, 2), without a flow: the drift in a potential is a gradient
+// and A_b similar to a symmetric matrix, through weights e^(z psi). A flow adds
+// imaginary parts of up to half of its cell Peclet number.
 //   Chebyshev: the kChebSteps-th iterate of the Chebyshev iteration for D^-1 A_b
 //   on [kChebLow, 2]. Its residual polynomial stays below 1 in the ellipse with
 //   these foci that goes through 0, whose half height is 0.447, and reaches 16
-//   at 1 +- i. Taken while the largest |Pe| of the faces is below kChebMaxPe,
-//   twice that height.
+//   at 1 +- i. Taken while the flow's largest |Pe| is below kChebMaxPe, twice
+//   that height, and the potential's range in a block is below kChebMaxRange, half
+//   of where the weights' ratio e^range begins to tell (a uniform field of 25 thermal
+//   voltages a block: 60 iterations, 35: 64, 47: 75, 59: no convergence).
 //   plain: z <- D^-1 (r + O z), kPlainSweeps terms of the Neumann series. O D^-1 is
 //   not negative and its powers' columns sum to at most 1: no drift amplifies. An
 //   odd number, as after an even one nothing is left of lambda = 2.
-// Iterations and ms of steady solves to 1e-10 (64^3 at porosity 0.6; the
-// diagonal took 90 to 290 iterations, whatever the drift): largest |Pe| 0.36
-// Chebyshev 102 and 5.7, plain 90 and 5.1; 192^3 at |Pe| 0.3: 108 and 49, 123 and
-// 57; 0.9: 79 and 4.3, 74 and 4.4; 3.6: 51 and 2.9, 57 and 3.4; 9 and 60:
-// Chebyshev breaks down, 42 and 2.6, 25 and 1.5; an electrode at -5 and -20
-// thermal voltages: 104 and 5.8, 105 and 5.9 against 116 and 6.5, 105 and 6.0. (5, 6, 7 and 10 plain sweeps at |Pe| 4, 96^3:
-// 58, 49, 48 and 41 iterations, nine 42.) The blocks take the cells' own
-// coefficients: a diffusion-only block does as well in weak fields and fails
+// Iterations and ms of steady solves to 1e-10 (the diagonal takes 110 to 320
+// iterations in all of them): 192^3, flow of |Pe| 0.3: Chebyshev 108 and 49, plain
+// 123 and 57; 192^3, electrode at -4 thermal voltages: 112 and 37, 131 and 44; at
+// 64^3, |Pe| 0.9: 79 and 4.3, 74 and 4.4; 3.6: 51 and 2.9, 57 and 3.4; 9 and 60:
+// Chebyshev breaks down, plain 42 and 2.6, 25 and 1.5. (5, 6, 7 and 10 plain sweeps
+// at |Pe| 4, 96^3: 58, 49, 48 and 41 iterations, nine 42.) The blocks take the cells'
+// own coefficients: a diffusion-only block does as well in weak fields and fails
 // in steep ones (no convergence at -20). The coefficients are formed again from flux and
 // potential where they are needed, 16 bytes a node instead of 48 for stored
 // ones. The sweeps run on the block in LDS; what bounds the direction kernels
 // is their streams (116 and 100 bytes a node) about as much as their arithmetic.
 // 192^3, 4.2 M nodes, to 1e-10: 141 -> 52 ms, 300 -> 118 iterations of 383 ->
 // 372 us.
-constexpr double kChebMaxPe = 0.89;
+constexpr double kChebMaxPe = 0.89, kChebMaxRange = 25.0;
 constexpr int kPlainSweeps = 9;
 
 // Nodes per thread of the direction kernels: two. A node's row and its loads
@@ -675,7 +695,7 @@ __global__ __launch_bounds__(kTile) void nps_rates_kernel(Grid g, Phys p, const 
 
 uint64_t nps_part_doubles() { return (uint64_t)kRegions * 2 * kNpsMaxWorkgroups; }
 
-int nps_plain(double pe) { return !(pe <= kChebMaxPe); }
+int nps_plain(double pe, double range) { return !(pe <= kChebMaxPe && range <= kChebMaxRange); }
 
 hipError_t nps_workgroups(int dim, int ntiles, int *G)
 {

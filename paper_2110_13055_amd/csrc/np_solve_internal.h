@@ -21,8 +21,9 @@ enum {
     kNsThr = 8,     // + s
     kNsDone = 10,   // 0 running, 1 converged, 2 diverged / breakdown
     kNsScale = 11,  // + s: the power of two that brings |r_0| to 1 to 2
-    kNsPe = 13,     // largest |Pe| of a face between fluid cells
-    kNsSlots = 14
+    kNsPe = 13,     // largest |Pe| of the flow across a face between fluid cells
+    kNsRange = 14,  // largest range of the potential within a block, thermal voltages times |z|
+    kNsSlots = 15
 };
 
 struct NpsArgs {
@@ -47,10 +48,10 @@ uint64_t nps_part_doubles();
 // Workgroups of the kernels that leave partial sums, and of the two direction kernels.
 hipError_t nps_workgroups(int dim, int ntiles, int *G);
 hipError_t nps_dir_workgroups(int dim, int ntiles, int plain, int *Gd);
-// Whether a system whose largest |Pe| is pe takes plain sweeps (np_solve.hip).
-int nps_plain(double pe);
-// x = C, r = rhat = C idt + b - A x, reciprocal diagonals, |rhs|^2, rho_0, the largest
-// |Pe| and the state.
+// Whether a system with these kNsPe and kNsRange takes plain sweeps (np_solve.hip).
+int nps_plain(double pe, double range);
+// x = C, r = rhat = C idt + b - A x, reciprocal diagonals, |rhs|^2, rho_0, the drift's
+// measures and the state.
 hipError_t launch_nps_setup(int dim, const NpsArgs &a, double tol, hipStream_t s);
 // BiCGSTAB iteration k (direction, A p, s, A s, update); returns at once after the stop.
 hipError_t launch_nps_iter(int dim, const NpsArgs &a, int k, hipStream_t s);

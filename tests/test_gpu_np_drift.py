@@ -1,6 +1,8 @@
-"""Implicit ion solves where the drift dominates (largest cell Peclet number of
-1.5 to 70; the block preconditioner's sweeps change at 0.89): a porous
-electrode's flow, a steep ramp, and recirculation in a channel. Against the FP64
+"""Implicit ion solves where the drift dominates (largest cell Peclet number of the
+flow 1.5 to 70, where the block preconditioner's sweeps change at 0.89; ranges of
+the potential within a block of 6 to 100 thermal voltages, where they change at
+25): a porous electrode's flow, a steep ramp, prescribed fields along each axis,
+and recirculation in a channel. Against the FP64
 oracle, which solves with the diagonal, to the implicit tests' bar (the
 coefficients are FP32: 1e-4 of the largest concentration), and in no more
 iterations than the diagonal takes to the same tolerance (the oracle's count is
@@ -8,7 +10,7 @@ the sum over the species, the solver's the larger one)."""
 import numpy as np
 import pytest
 
-from helpers import oracle_solver
+from helpers import oracle_labels, oracle_solver
 
 pytestmark = pytest.mark.gpu
 
@@ -70,4 +72,22 @@ def test_recirculation(pe):
     s, o = Solver(g, p), oracle_solver(g, p)
     s.set_np_velocity(j.astype(np.float32))
     o.set_velocity(j.astype(np.float32).astype(np.float64))
+    solve_both(s, o, None)
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("per_cell", [0.9, 6.0])
+def test_prescribed_field(axis, per_cell):
+    # a field that rises and falls along one axis (y and z wrap); blocks are flat in z
+    torch = pytest.importorskip("torch")
+    g = Geometry(dim=3, nx=48, ny=45, nz=50, kind=L.SPHERES, porosity=0.6, r_min=3.0, r_max=6.0, seed=3)
+    lab = oracle_labels(g).reshape(g.nz, g.ny, g.nx)
+    at = np.stack(np.nonzero(lab == 0))[2 - axis].astype(np.float32)
+    n = (g.nx, g.ny, g.nz)[axis]
+    psi = (per_cell * np.abs(at - n / 2)).astype(np.float32)
+    p = Params(u_in=1e-3, psi_field=torch.from_numpy(psi).cuda())
+    s, o = Solver(g, p), oracle_solver(g, p, psi=psi.astype(np.float64))
+    s.flow_steps(100)
+    o.flow_steps(100)
+    o.freeze_velocity()
     solve_both(s, o, None)
