@@ -301,6 +301,11 @@ __global__ __launch_bounds__(kTile) void stability_kernel(Grid g, Phys p, const 
             jN[k] = j[(size_t)(k >> 1) * P + q];
             psiN[k] = p.psi ? p.psi[q] : 0.f;
         }
+        // (of a face that is not fluid, the node's own flux)
+        const float hr = fmaxf(fabsf(p.hr[0]), fabsf(p.hr[1]));
+#pragma unroll
+        for (int k = 0; k < 2 * D; ++k)
+            hmax = fmaxf(hmax, fmaf(0.25f, fabsf(j[(size_t)(k >> 1) * P + n] + jN[k]), k < 2 ? hr : 0.f));
         for (int s = 0; s < 2; ++s) {
             const float Ds = p.D[s];
             float dg = 0.f;
@@ -329,21 +334,19 @@ __global__ __launch_bounds__(kTile) void stability_kernel(Grid g, Phys p, const 
                     const float dpsi = p.psi ? psiN[k] - psiP : (axis == 0 ? -sg * p.dpsi_dx : 0.f);
                     const float w = un - p.z[s] * Ds * dpsi;
                     dg += Ds * bern(-w / Ds);
-                    hmax = fmaxf(hmax, fabsf(w) * 0.5f);
                 }
             }
             worst = fmaxf(worst, p.dt * dg);
         }
     }
-    __shared__ float sm[kTile];
-    sm[threadIdx.x] = worst;
-    __syncthreads();
-    for (int h = kTile / 2; h > 0; h >>= 1) {
-        if (threadIdx.x < h) sm[threadIdx.x] = fmaxf(sm[threadIdx.x], sm[threadIdx.x + h]);
-        __syncthreads();
-    }
+    __shared__ float sm[kTile / 64];
+    for (int off = 32; off > 0; off >>= 1) worst = fmaxf(worst, __shfl_xor(worst, off, 64));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = worst;
     const int beyond = __syncthreads_or(!p.psi && !p.steep && !(hmax * hmax <= p.h2_max));
-    if (threadIdx.x == 0) part[blockIdx.x] = make_double2(sm[0], beyond ? 1.0 : 0.0);
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kTile / 64; ++w) worst = fmaxf(worst, sm[w]);
+        part[blockIdx.x] = make_double2(worst, beyond ? 1.0 : 0.0);
+    }
 }
 
 }  // namespace
