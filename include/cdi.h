@@ -482,14 +482,18 @@ int cdi_copy_potential(cdi_solver *s, float *psi);
  * step's face fluxes, adsorption and ghost terms; coefficients evaluated in
  * FP32 as the explicit step does, applied in FP64). A backward-Euler step of
  * length dt solves (I/dt + A) C' = C/dt + b; the steady state solves A C = b;
- * both by BiCGSTAB with the diagonal as preconditioner, both species
- * together, to the relative residual tol (|rhs - M C'| <= tol |rhs|). The
+ * both by BiCGSTAB on FP64 vectors, both species together, to the relative
+ * residual tol (|rhs - M C'| <= tol |rhs|), preconditioned by sweeps within
+ * blocks of 1024 nodes: Chebyshev sweeps while the flow's largest cell Peclet
+ * number |j| / D is below 0.89 and the potential varies by less than 25 thermal
+ * voltages over a block, else plain ones, which no drift amplifies. (Cell Peclet
+ * numbers beyond 88, flow and field together, overflow the FP32 coefficients.) The
  * stop is decided on the device; the iterate is bitwise repeatable on one
  * device. The scheme is unconditionally positive and stable (no positivity
  * check is needed or made). */
 
-/* Device workspace of the ion solves (7 FP64 vector pairs and an FP32 pair
- * per node, plus per-workgroup sums); needed only during a call. */
+/* Device workspace of the ion solves (6 FP64 and 3 FP32 vector pairs per node,
+ * 120 B, plus per-workgroup sums); needed only during a call. */
 int cdi_np_solve_bytes(const cdi_solver *s, uint64_t *bytes);
 
 /* The steady concentrations on the frozen flow, from the current ones
@@ -543,7 +547,12 @@ int cdi_salt_removal(const cdi_solver *s, const double bal0[8], const double bal
                      int64_t n_inlet, double U, double out[4]);
 
 /* Checkpoint: the complete device state (populations, moments, fields,
- * potential, accumulators, counters, AA parity) to and from host memory. */
+ * potential, accumulators, counters, AA parity) to and from host memory. A
+ * snapshot restores into any solver of the same lattice, storage and streaming,
+ * whatever its other parameters: a state held as moments (see precision) becomes
+ * populations where the solver holds those, and populations are stepped on as
+ * such where it would hold moments. Snapshots written before the moment form
+ * are accepted. */
 int cdi_snapshot_bytes(cdi_solver *s, uint64_t *bytes);
 int cdi_snapshot(cdi_solver *s, void *host, uint64_t bytes);
 int cdi_restore(cdi_solver *s, const void *host, uint64_t bytes);

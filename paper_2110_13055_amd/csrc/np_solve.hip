@@ -300,11 +300,12 @@ __global__ __launch_bounds__(kTile) void nps_state_kernel(NpsArgs a, int G, doub
 //   plain: z <- D^-1 (r + O z), kPlainSweeps terms of the Neumann series. O D^-1 is
 //   not negative and its powers' columns sum to at most 1: no drift amplifies. An
 //   odd number, as after an even one nothing is left of lambda = 2.
-// Iterations and ms of steady solves to 1e-10 (the diagonal takes 110 to 320
-// iterations in all of them): 192^3, flow of |Pe| 0.3: Chebyshev 108 and 49, plain
-// 123 and 57; 192^3, electrode at -4 thermal voltages: 112 and 37, 131 and 44; at
-// 64^3, |Pe| 0.9: 79 and 4.3, 74 and 4.4; 3.6: 51 and 2.9, 57 and 3.4; 9 and 60:
-// Chebyshev breaks down, plain 42 and 2.6, 25 and 1.5. (5, 6, 7 and 10 plain sweeps
+// Iterations and ms of steady solves to 1e-10, with the diagonal, Chebyshev and
+// plain sweeps: 192^3, flow of |Pe| 0.3: 299 and 129, 108 and 49, 123 and 57; 192^3,
+// electrode at -4 thermal voltages: 318 and 105, 112 and 37, 131 and 44; 64^3,
+// |Pe| 0.9: 205 and 11.8, 79 and 4.3, 74 and 4.4; 3.6: 157 and 9.1, 51 and 2.9, 57
+// and 3.4; 9 and 60: 154 and 9.1, 133 and 8.3, Chebyshev breaks down, 42 and 2.6,
+// 25 and 1.5. (5, 6, 7 and 10 plain sweeps
 // at |Pe| 4, 96^3: 58, 49, 48 and 41 iterations, nine 42.) The blocks take the cells'
 // own coefficients: a diffusion-only block does as well in weak fields and fails
 // in steep ones (no convergence at -20). The coefficients are formed again from flux and

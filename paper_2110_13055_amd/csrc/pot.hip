@@ -1,7 +1,7 @@
 // pot.hip -- the electric potential of Poisson's equation, Eq. (4), with the
 // charge density of Eq. (5) and the electrode's Dirichlet value (Sec. 2),
-// solved on the compacted fluid lattice by Jacobi-preconditioned conjugate
-// gradients inside mixed-precision iterative refinement: the iterate x and
+// solved on the compacted fluid lattice by preconditioned conjugate gradients
+// inside mixed-precision iterative refinement: the iterate x and
 // each round's residual b - A x are FP64, each round's correction solve runs
 // CG on FP32 vectors (dot products and alpha, beta in FP64), and a round that
 // no longer gains hands over to CG on the FP64 vectors.
@@ -638,9 +638,10 @@ __global__ __launch_bounds__(kTile) void pot_store_kernel(const double *x, float
 
 uint64_t pot_part_doubles() { return (uint64_t)kRegions * kPotMaxWorkgroups; }
 
-// As many persistent workgroups as the stencil kernel (the largest register
-// footprint of the solve) keeps resident on the device at once: a workgroup
-// that had to wait for a free slot would double the kernel's time.
+// As many persistent workgroups as the FP64 stencil kernel (the largest register
+// footprint of the solve: 102 against 85 and 56 of the FP32 rounds' kernels in
+// 3D, 4, 5 and 8 workgroups a compute unit) keeps resident on the device at once:
+// a workgroup that had to wait for a free slot would double the kernel's time.
 hipError_t pot_workgroups(int dim, int ntiles, bool nbr, int *G)
 {
     int dev = 0, cus = 0, per_cu = 0;

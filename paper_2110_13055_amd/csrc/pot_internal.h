@@ -1,6 +1,8 @@
 // pot_internal.h -- argument block and launchers of the potential solve
 // (pot.hip): Poisson's equation, Eq. (4), with the charge of Eq. (5), by
-// Jacobi-preconditioned conjugate gradients on the compacted lattice.
+// conjugate gradients on the compacted lattice: FP32 correction solves with a
+// block preconditioner inside FP64 iterative refinement, and Jacobi-
+// preconditioned FP64 ones.
 #pragma once
 
 #include "cdi_internal.h"

@@ -279,7 +279,7 @@ NPS_KERNELS = {"nps_dir_kernel<0>": ("p, p^ = M p by block sweeps", 116),
 
 
 def _solver_kernel(name: str):
-    m = re.search(r"(nps_apply_kernel|nps_dir_kernel)<[^,>]+, (\d)>", name)
+    m = re.search(r"(nps_apply_kernel|nps_dir_kernel)<[^,>]+, (\d)(?:, \d)?>", name)
     if m:
         return f"{m.group(1)}<{m.group(2)}>"
     for k in list(POT_KERNELS) + list(POT64_KERNELS) + list(POT_ROUND_KERNELS) + list(NPS_KERNELS):
