@@ -1887,14 +1887,23 @@ int batch_workgroups(const cdi_batch *b, int count)
     return wg < 1 ? 1 : wg;
 }
 
-int step_class(const cdi_solver *s, int mode)
+// Whether a member's ions need the kernels with every form of the flux. If one
+// does, the batch's others go with it: a launch of their own costs more than the
+// registers (25 cubes, half of them in their ion phase: 49 us a step, 57 apart).
+bool any_form(const cdi_solver *s, int mode)
+{
+    return (mode == kModeIons || mode == kModeFused) && (s->p.psi || s->p.steep || s->p.far);
+}
+
+int step_class(const cdi_solver *s, int mode, bool any_flux)
 {
     const int base = kernel_form(s) * kClassesPerForm;
     const int odd = s->st == kMom ? 0 : stream_arg(s);
+    const int any = any_flux ? kClassAny : 0;
     switch (mode) {
     case kModeFlow: return base + (odd == kPull ? kClassFlowPull : odd ? kClassFlowOdd : kClassFlowEven);
-    case kModeFused: return base + (odd == kPull ? kClassFusedPull : odd ? kClassFusedOdd : kClassFusedEven);
-    case kModeIons: return kernel_form(s) == kH16L ? kClassIonsL : kClassIons;
+    case kModeFused: return base + any + (odd == kPull ? kClassFusedPull : odd ? kClassFusedOdd : kClassFusedEven);
+    case kModeIons: return kernel_form(s) == kH16L ? kClassIonsL : any ? kClassIonsAny : kClassIons;
     default: return -1;
     }
 }
@@ -1916,13 +1925,15 @@ void fill_slot(cdi_batch *bt, int slot, const int32_t *modes, int64_t idx, int64
 {
     BatchInst *h = bt->hstage + (size_t)slot * bt->cap_n;
     int count[kClasses] = {};
+    bool any = false;
+    for (int k = 0; k < bt->n; ++k) any = any || any_form(bt->m[k], modes[k]);
     for (int k = 0; k < bt->n; ++k) {
         const cdi_solver *s = bt->m[k];
         BatchInst &I = h[k];
         I.g = s->g;
         I.p = s->p;
         I.b = make_bufs(s, batch_flags(s, modes[k], idx, nsteps, want_resid));
-        const int c = step_class(s, modes[k]);
+        const int c = step_class(s, modes[k], any);
         if (c >= 0) count[c] += s->ntiles;
     }
     int *beg = bt->cls_begin[slot];
@@ -1932,7 +1943,7 @@ void fill_slot(cdi_batch *bt, int slot, const int32_t *modes, int64_t idx, int64
     for (int c = 0; c < kClasses; ++c) pos[c] = beg[c];
     int2 *t = bt->htiles + (size_t)slot * bt->cap_tiles;
     for (int k = 0; k < bt->n; ++k) {
-        const int c = step_class(bt->m[k], modes[k]);
+        const int c = step_class(bt->m[k], modes[k], any);
         if (c < 0) continue;
         for (int q = 0; q < bt->m[k]->ntiles; ++q) t[pos[c]++] = make_int2(k, q);
     }

@@ -214,10 +214,12 @@ struct BatchInst {
 // Step classes of a batched step (kernel variants): per storage form, LBM
 // only or fused by parity (class kClassesPerForm * form + ...; the moment
 // forms have no parity and use the even ones), and ions only (kClassIonsL: of
-// kH16L members).
+// kH16L members). While no member is in a potential field, a steep ramp or a flow
+// beyond the flux series' range, the ion-carrying classes take kernels without the
+// code of those fluxes, which costs registers; else the ones kClassAny further on.
 constexpr int kClassFlowEven = 0, kClassFlowOdd = 1, kClassFlowPull = 2, kClassFusedEven = 3, kClassFusedOdd = 4,
-              kClassFusedPull = 5, kClassesPerForm = 6, kClassIons = kForms * kClassesPerForm,
-              kClassIonsL = kClassIons + 1, kClasses = kClassIons + 2;
+              kClassFusedPull = 5, kClassAny = 3, kClassesPerForm = 9, kClassIons = kForms * kClassesPerForm,
+              kClassIonsAny = kClassIons + 1, kClassIonsL = kClassIons + 2, kClasses = kClassIons + 3;
 
 // Value of the kernels' parity argument for pull streaming (AA uses 0 / 1).
 constexpr int kPull = 2;

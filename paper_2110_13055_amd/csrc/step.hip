@@ -884,7 +884,7 @@ __device__ __forceinline__ void load_inst(const BatchInst *inst, int k, Grid &g,
 // parameters and buffers, so uneven sizes share the launch; the descriptor is
 // copied once per tile into registers. Tile results do not depend on which
 // workgroup computes them.
-template <class L, int ST, int ODD, int LBM, int NP>
+template <class L, int ST, int ODD, int LBM, int NP, int PSI>
 __global__ __launch_bounds__(kTile) void batch_kernel(const BatchInst *__restrict__ inst,
                                                       const int2 *__restrict__ tiles, int ntiles)
 {
@@ -909,7 +909,7 @@ __global__ __launch_bounds__(kTile) void batch_kernel(const BatchInst *__restric
         Phys p;
         Bufs b;
         load_inst(inst, e.x, g, p, b);
-        step_tile<L, ST, ODD, LBM, NP, kPsiAny>(g, p, b, e.y, sm, nullptr);  // not staged
+        step_tile<L, ST, ODD, LBM, NP, PSI>(g, p, b, e.y, sm, nullptr);  // not staged
         if (NP && q + stride < hi) __syncthreads();  // the next tile reuses the sums
     }
 }
@@ -933,21 +933,21 @@ void launch_batch_t(int cls, const BatchInst *inst, const int2 *tiles, int ntile
                     hipStream_t s)
 {
     const size_t lds = (size_t)pad;
-    if constexpr (kMoments<ST>) {  // no parity
-        if (cls == kClassFlowEven)
-            batch_kernel<L, ST, 0, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles);
-        else
-            batch_kernel<L, ST, 0, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles);
-    } else {
-        switch (cls) {
-        case kClassFlowEven: batch_kernel<L, kFlowForm<ST>, 0, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-        case kClassFlowOdd: batch_kernel<L, kFlowForm<ST>, 1, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-        case kClassFlowPull: batch_kernel<L, kFlowForm<ST>, kPull, 1, 0><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-        case kClassFusedEven: batch_kernel<L, ST, 0, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-        case kClassFusedOdd: batch_kernel<L, ST, 1, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-        default: batch_kernel<L, ST, kPull, 1, 1><<<wg, kTile, lds, s>>>(inst, tiles, ntiles); break;
-        }
+    constexpr int F = kFlowForm<ST>, R = ST == kH16L ? kPsiAny : 0;  // (kH16L: rare)
+    constexpr int O1 = kMoments<ST> ? 0 : 1, OP = kMoments<ST> ? 0 : kPull;  // the moment forms have no parity
+#define BK(S, O, NP, PSI) batch_kernel<L, S, O, 1, NP, PSI><<<wg, kTile, lds, s>>>(inst, tiles, ntiles)
+    switch (cls) {
+    case kClassFlowEven: BK(F, 0, 0, 0); break;
+    case kClassFlowOdd: BK(F, O1, 0, 0); break;
+    case kClassFlowPull: BK(F, OP, 0, 0); break;
+    case kClassFusedEven: BK(ST, 0, 1, R); break;
+    case kClassFusedOdd: BK(ST, O1, 1, R); break;
+    case kClassFusedPull: BK(ST, OP, 1, R); break;
+    case kClassAny + kClassFusedEven: BK(ST, 0, 1, kPsiAny); break;
+    case kClassAny + kClassFusedOdd: BK(ST, O1, 1, kPsiAny); break;
+    default: BK(ST, OP, 1, kPsiAny); break;
     }
+#undef BK
 }
 
 template <class L, int ST, int ODD, int LBM, int NP, int PSI>
@@ -1021,12 +1021,13 @@ template <class L>
 void launch_batch_l(int cls, const BatchInst *inst, const int2 *tiles, int ntiles, int wg, int pad,
                     hipStream_t s)
 {
-    if (cls == kClassIons) {
-        batch_kernel<L, kF32, 0, 0, 1><<<wg, kTile, (size_t)pad, s>>>(inst, tiles, ntiles);
-        return;
-    }
-    if (cls == kClassIonsL) {
-        batch_kernel<L, kH16L, 0, 0, 1><<<wg, kTile, (size_t)pad, s>>>(inst, tiles, ntiles);
+    if (cls >= kClassIons) {
+        if (cls == kClassIonsL)
+            batch_kernel<L, kH16L, 0, 0, 1, kPsiAny><<<wg, kTile, (size_t)pad, s>>>(inst, tiles, ntiles);
+        else if (cls == kClassIonsAny)
+            batch_kernel<L, kF32, 0, 0, 1, kPsiAny><<<wg, kTile, (size_t)pad, s>>>(inst, tiles, ntiles);
+        else
+            batch_kernel<L, kF32, 0, 0, 1, 0><<<wg, kTile, (size_t)pad, s>>>(inst, tiles, ntiles);
         return;
     }
     const int k = cls % kClassesPerForm;

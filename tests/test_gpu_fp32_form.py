@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 P = pytest.importorskip("paper_2110_13055_amd")
 from paper_2110_13055_amd import _lib as L  # noqa: E402
-from paper_2110_13055_amd import Batch, Geometry, Params, Solver  # noqa: E402
+from paper_2110_13055_amd import Batch, Geometry, Params, Potential, Solver  # noqa: E402
 
 RSTATE = 16 + 7 * 4  # byte offset of the state bits in a snapshot's header
 
@@ -240,3 +240,29 @@ def test_drift_kernels_give_the_same_values(form, dim):
             s.np_step(7)
         bt.advance(7, L.MODE_IONS)
     bt.close()
+
+
+@pytest.mark.parametrize("alone_in_ramp", [False, True])
+def test_members_of_every_flux_form_in_one_batch(alone_in_ramp):
+    # ramp, steep ramp, drift-dominated flow and a solved potential: together they
+    # take the batched kernels with every form, ramps alone those without
+    pk = [dict(dpsi_vt=5.0), dict(dpsi_vt=3.0)] if alone_in_ramp else \
+        [dict(dpsi_vt=5.0), dict(dpsi_vt=60.0), dict(u_in=0.02, D=(0.006, 0.009)), dict()]
+    alone, both = [], []
+    for to in (alone, both):
+        for k, q in enumerate(pk):
+            g = Geometry(dim=3, nx=24 + 3 * k, ny=21, nz=20, kind=L.SPHERES, porosity=0.6, r_min=3.0, r_max=5.0, seed=k + 1)
+            s = Solver(g, Params(**{"u_in": 1e-3, **q}))
+            s.flow_steps(30)
+            if not q:
+                s.solve_potential(Potential(psi_electrode=-2.0, x_bc=(L.PSIX_DIRICHLET, L.PSIX_NEUMANN), tol=1e-8))
+            to.append(s)
+    b = Batch(both)
+    for n, mode in ((6, L.MODE_FUSED), (5, L.MODE_IONS), (4, L.MODE_FLOW), (7, L.MODE_FUSED)):
+        b.advance(n, mode)
+        for s in alone:
+            s.flow_steps(n) if mode == L.MODE_FLOW else s.np_step(n, fused=mode == L.MODE_FUSED)
+    b.close()
+    for s, t in zip(alone, both):
+        assert np.array_equal(s.concentration(), t.concentration()) and np.array_equal(s.velocity(), t.velocity())
+        assert np.array_equal(s.mass_balance(), t.mass_balance())
