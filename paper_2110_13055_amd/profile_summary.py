@@ -31,7 +31,7 @@ from collections import defaultdict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ("step.hip", "device_common.h", "cdi_internal.h")
-STORAGE = {"0": "fp32", "1": "fp16_dev", "2": "moments", "3": "fp16", "4": "moments_refs"}
+STORAGE = {"0": "fp32", "1": "fp16_dev", "2": "moments", "3": "fp16", "4": "moments_refs", "5": "fp16_large"}
 
 
 def kernel_source_hash() -> str:
